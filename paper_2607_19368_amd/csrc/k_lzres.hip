@@ -1,18 +1,17 @@
 // Implicit Lanczos with full re-orthogonalization (Algorithm 2; operator of
-// Eq. 4, A v = Phi (Phi^T v)) for one window whose Phi fits in the register
-// files of the device, as one persistent kernel for the whole run.
+// Eq. 4, A v = Phi (Phi^T v)) for windows whose Phi fit in the register files of
+// the device together, as one persistent kernel for the whole run.
 //
-// Block b of nb (one per compute unit) holds rows [RB b, RB b + RB) of Phi in
-// registers for the whole run, loaded once, and its rows of the basis Q in
-// LDS.  Each step is the same computation as the pass and the reduction of
-// the streaming path (k_lz_step, k_lz_reduce: q_j by the second Gram-Schmidt
-// pass of step j-1 in row space, u = A q_j from the row dots with t~ and the
-// Lanczos relation, z1 by the three-term recurrence, then t~ = Phi^T z1 / |z1|
-// and h2 = Q_j^T z1), in two phases:
+// Block b of a window's nb holds rows [RB b, RB b + RB) of Phi in registers for
+// the whole run, loaded once, and its rows of the basis Q in LDS.  Each step is
+// the same computation as the pass and the reduction of the streaming path
+// (k_lz_step, k_lz_reduce: q_j by the second Gram-Schmidt pass of step j-1 in
+// row space, u = A q_j from the row dots with t and the Lanczos relation, z1 by
+// the three-term recurrence, then t = Phi^T z1 and h2 = Q_j^T z1), in two phases:
 //   rows     every block: its rows of q_j and z1, and its partials of Phi^T z1,
-//            of h2 and of |z1|^2 (alpha~ = |t~|^2 it sums from the t~ it holds);
-//   columns  block b: t~ over its m / nb columns (written to every copy of t~);
-//            h2 entries b, b + nb, ...; |z1|^2 (every block).
+//            of h2 and of |z1|^2 (|t|^2 it sums from the t it holds);
+//   columns  block b: t over the columns it owns (written to every copy of t);
+//            h2 entries b, b + nb, ... (|z1|^2 among them).
 // The scalars of a step (alpha, beta, the breakdown test) are computed by
 // every block from the same reduced values in the same order, so all blocks
 // agree and leave the loop together.  Results are bitwise reproducible.
@@ -31,16 +30,17 @@
 // others, seeing it, leave too.  A block's own stores are acknowledged
 // before its waves start polling: its polls and its stores share the CU's path
 // to memory, and its stores are what the other blocks are waiting for.  The
-// host launches the kernel only when all nb blocks are resident at once (one
-// per compute unit; checked with the occupancy calculator).
+// host launches the kernel only when all blocks are resident at once (checked
+// with the occupancy calculator).
 #include "slh_device.h"
 #include "slh_internal.h"
+
+#include <algorithm>
 
 namespace slh {
 
 namespace {
 
-constexpr int LR_T = 256;          // threads per block at m = 1024 (one wave per SIMD); 512 at m = 2048
 constexpr int LR_SPIN = 1 << 20;   // polls before a barrier gives up
 
 __device__ __forceinline__ void st_flag(unsigned* p, unsigned v) {
@@ -53,7 +53,10 @@ __device__ __forceinline__ unsigned ld_flag(unsigned* p) {
 // bar: [LR_ERR] error word
 constexpr int LR_ERR = LZ_BAR_ERR;
 // copies of t~ (T holds [ldq][m] doubles)
-__host__ __device__ constexpr int res_copies(int ldq) { return ldq < 8 ? ldq : 8; }
+__host__ __device__ inline int res_copies(int ldq, int nb) {
+  const int c = nb < 32 ? 1 : nb < 64 ? 2 : nb < 128 ? 4 : 8;
+  return ldq < c ? ldq : c;
+}
 
 // v tagged with step e into *p
 __device__ __forceinline__ void st_tag(double* p, double v, int e) {
@@ -77,15 +80,16 @@ __device__ __forceinline__ long long ld_raw(double* p) {
 }
 __device__ __forceinline__ bool tag_is(long long x, int e) { return (int)(x & 3) == 1 + (e & 1); }
 
-// v[u] = *addr(u) of step e for the u with bit u of act set (0 for the others),
-// polling until every tag matches; false after spin polls or when the error
-// word is set (the error word is then set)
+// x[u] = *addr(u) of step e for the u with bit u of act set, polling until every
+// tag matches (the addresses of the others must be readable too: the first
+// loads carry no branches, so that they go out together); false after spin
+// polls or when the error word is set (the error word is then set)
 template <int N, class ADDR>
 __device__ __forceinline__ bool ld_wait(ADDR addr, unsigned act, int e, unsigned* bar, int spin,
                                         double (&v)[N]) {
   long long x[N];
 #pragma unroll
-  for (int u = 0; u < N; ++u) x[u] = ((act >> u) & 1) ? ld_raw(addr(u)) : 0;
+  for (int u = 0; u < N; ++u) x[u] = ld_raw(addr(u));
   bool ok = true;
   for (int s = 0;; ++s) {
     bool all = true;
@@ -106,6 +110,46 @@ __device__ __forceinline__ bool ld_wait(ADDR addr, unsigned act, int e, unsigned
   return ok;
 }
 
+// Sum over the lanes at distances CB, 2 CB, ... 32 (CB a power of two >= 4; the
+// same bits in every lane of the sum)
+__device__ __forceinline__ double strided_sum(double v, int CB) {
+  if (CB <= 32) v = swap32_add(v, v);
+  if (CB <= 16) v = swap16_add(v, v);
+  if (CB <= 8) v += dpp_f64<DPP_ROR8>(v);
+  if (CB <= 4) v += dpp_f64<DPP_ROR4>(v);       // period 8 within the row by now: lane ^ 4
+  return v;
+}
+// Sum over each group of LP consecutive lanes (LP a power of two <= 64)
+__device__ __forceinline__ double group_sum(double v, int LP) {
+  if (LP >= 64) v = swap32_add(v, v);
+  if (LP >= 32) v = swap16_add(v, v);
+  if (LP >= 16) v += dpp_f64<DPP_ROR8>(v);
+  if (LP >= 8) v += dpp_f64<DPP_HALF_MIRROR>(v);
+  if (LP >= 4) v += dpp_f64<DPP_XOR2>(v);
+  if (LP >= 2) v += dpp_f64<DPP_XOR1>(v);
+  return v;
+}
+
+// beta = sqrt(x) and 1 / beta for x > 0: the hardware reciprocal square root,
+// two Newton steps, and a last correction of the root (a short chain of
+// dependent operations, where sqrt and a division take several times as long)
+__device__ __forceinline__ void sqrt_rsqrt(double x, double& r, double& ir) {
+  // scaled into the range of the approximation (x = 2^-2k-exact power of two)
+  const int ex = __builtin_amdgcn_frexp_exp(x) & ~1;
+  const double xs = ldexp(x, -ex);
+  double y = __builtin_amdgcn_rsq(xs);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double h = 0.5 * y;
+    y = fma(h, fma(-xs * y, y, 1.0), y);
+  }
+  double s = xs * y;
+  s = fma(fma(-s, s, xs), 0.5 * y, s);
+  y = fma(fma(-s, y, 1.0), y, y);               // 1 / s from y close to it
+  r = ldexp(s, ex >> 1);
+  ir = ldexp(y, -(ex >> 1));
+}
+
 // Every store this thread issued acknowledged (vmcnt counts stores as well as
 // loads here), then a block barrier: the block's polls that follow do not
 // compete in the CU's memory path with its own stores, which other blocks are
@@ -115,505 +159,564 @@ __device__ __forceinline__ void stores_done_barrier() {
   __syncthreads();
 }
 
-// true in every thread when no thread of the block saw a failure (a barrier)
-__device__ __forceinline__ bool block_ok(bool ok) {
-  __shared__ int bad;
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  if (!ok) bad = 1;
-  __syncthreads();
-  return bad == 0;
-}
-
-// The float4 of one Phi row as an opaque value at its point of use, so that its
-// conversion to fp64 is not hoisted (the converted rows would need twice the
-// registers).
-__device__ __forceinline__ float4 pin4(float4 x) {
-  asm volatile("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w));
-  return x;
-}
-
-// three block sums at once (fixed order: wave sums, then the NW waves in order)
-template <int NW>
-__device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double (*red)[NW]) {
-  a = wave_sum_f64(a);
-  b = wave_sum_f64(b);
-  c = wave_sum_f64(c);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = a;
-    red[1][threadIdx.x >> 6] = b;
-    red[2][threadIdx.x >> 6] = c;
-  }
-  __syncthreads();
-  a = red[0][0];
-  b = red[1][0];
-  c = red[2][0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    a += red[0][w];
-    b += red[1][w];
-    c += red[2][w];
-  }
-}
-
 // The held rows of Phi marked as rewritten (an empty statement, in place), so
 // that their fp64 conversions are neither hoisted out of the step loop nor
 // shared between a step's two uses (converted once they would need twice the
 // registers).  In place: the registers must all be VGPRs, or each one held in
 // an accumulation register is moved out and back.
-template <int RB, int NH>
-__device__ __forceinline__ void launder_rows(float4 (&ph)[RB][NH]) {
+template <int RW>
+__device__ __forceinline__ void launder_rows(float4 (&ph)[RW]) {
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
-#pragma unroll
-    for (int h = 0; h < NH; ++h)
-      asm volatile("" : "+v"(ph[r][h].x), "+v"(ph[r][h].y), "+v"(ph[r][h].z), "+v"(ph[r][h].w));
+  for (int r = 0; r < RW; ++r)
+    asm volatile("" : "+v"(ph[r].x), "+v"(ph[r].y), "+v"(ph[r].z), "+v"(ph[r].w));
 }
 
 }  // namespace
 
-// RB rows per block; CPL = m / NT columns per lane (the lane's columns are
-// 64 CPL w + 256 h + 4 lane + e for wave w, h < CPL / 4, e < 4).
-// Workspace use: Spart [m / CB][nb][CB] (CB = m / nb), H2part [nb][ldq + 1], H2 [ldq + 1],
-// T [C][m] with C = res_copies(ldq) (t~ written to every copy, block b reading
-// copy b mod C, so that the blocks' polls of t~ spread over C times as many
-// lines); outputs alpha, beta, neff, stop and Q[1..] as the streaming path.
-// A block waits for its own stores before it starts polling (stores_done_barrier).
+// NS = m / 256 column slices and P row subsets: wave (sl, p) of the NW = NS P
+// waves holds RW rows of the block's RB = P RW rows, 4 columns a lane (columns
+// 256 sl + 4 lane + e), at most 128 floats a lane.
+// Workspace use per window: Spart [m / CB][nb][CB] (CB = 2^cbl: columns per
+// owner, the smallest power of two >= 4 with CB nb >= m, so that blocks
+// b < m / CB own the columns), H2part [nb][ldq + 1], H2 [ldq + 1], T [C][m] with
+// C = res_copies (t written to every copy, block b reading copy b mod C, so that
+// the blocks' polls of t spread over C times as many lines); outputs alpha,
+// beta, neff, stop and Q[1..] as the streaming path.
 // Dynamic LDS: the block's rows of Q, (n_it + 1) (RB + 1) doubles.
-// NT threads per block (NW = NT / 64 waves); INPLACE: the held rows fit in
-// VGPRs (two waves per SIMD: 128 floats a lane) and are laundered in place once
-// per use, else (one wave per SIMD, 256 floats a lane, part of them in
-// accumulation registers) each use goes through pin4.
-template <int RB, int CPL, int NT, bool SPIN>
-__global__ __launch_bounds__(NT, 1) void k_lz_resident(LanczosWS w, unsigned* bar,
-                                                       const double* __restrict__ q1) {
-  constexpr int NW = NT / 64, NH = CPL / 4, KG = NT / RB, QS = RB + 1;   // QS: row stride of Qs (bank spread)
-  constexpr bool INPLACE = RB * CPL <= 128;
-  static_assert(CPL % 4 == 0 && RB % 8 == 0 && NT % RB == 0, "shape");
-  const int b = blockIdx.x, nb = gridDim.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int L = w.L, m = w.m, n_it = w.n_it, ldq = w.ldq, hs = ldq + 1;
+//
+// t is Phi^T z1 unscaled (the streaming path's t~ times |z1|): in
+//   u = (Phi t - Q g - beta h2_last q) / beta,  alpha = (|t|^2 - h2^T g) / beta^2 - 2 h2_last
+// |z1| drops out, so that t leaves the block that owns its columns as soon as
+// their sums are there, and |z1|^2, needed only by beta, travels with h2.
+//
+// What bounds it: the serial chain of a step, not Phi (held) or the exchanged
+// bytes.  A step is two exchanges between blocks (a store and the poll that
+// sees it, about 2000 cycles each) and six block barriers with the dots, sums
+// and scalars between them.
+template <int NS, int P, int RW, bool SPIN>
+__global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, unsigned* bar,
+                                                                const double* __restrict__ q1,
+                                                                int nb, int cbl) {
+  constexpr int NW = NS * P, NT = 64 * NW, RB = P * RW, KG = NT / RB, QS = RB + 1;   // QS: row stride of Qs (bank spread)
+  constexpr int CPT = P <= 4 ? 4 / P : 1;        // columns whose partials a thread stores
+  // column partials a thread reads: CB nb is m rounded up to a power of two, or
+  // 4 nb <= 4 * 256 at the smallest CB
+  constexpr int M2 = NS <= 4 ? 1024 : 2048;
+  constexpr int UL = (M2 + NT - 1) / NT;
+  constexpr int RP = 64 / RB;                    // lanes of wave 0 per row
+  constexpr int m = 256 * NS;
+  static_assert(RW % 8 == 0 && NT % RB == 0 && RB <= 64 && RB >= 8 && NT >= 256, "shape");
+  const int CB = 1 << cbl;
+  // window a, block b of its nb (consecutive blocks on one XCD where n_act is a
+  // multiple of 8: the dispatch deals blocks to the XCDs in turn)
+  const int a = blockIdx.x % w.n_act, b = blockIdx.x / w.n_act;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int sl = wv % NS, pw = wv / NS;
+  const int L = w.L, n_it = w.n_it, ldq = w.ldq, hs = ldq + 1;
   // SPIN: the wait limit from w.spin (SLH_OPT_WAIT_POLLS), else the constant
   const int spin = SPIN ? (w.spin > 0 ? w.spin : LR_SPIN) : LR_SPIN;
   const int r0 = b * RB;
-  const int cb = wv * 64 * CPL + 4 * lane;
+  const int cb = 256 * sl + 4 * lane;
   extern __shared__ double Qs[];                 // [n_it + 1][QS]
   __shared__ double h2s[256], gs[256], als[256], bes[256];
-  __shared__ double prw[NW][RB];
-  __shared__ double zs[RB], qr[RB], qmr[RB], sgr[RB];
-  __shared__ double rq[KG][RB + 1], rg[KG][RB + 1];
-  __shared__ double red[3][NW];
-  __shared__ double cpart[NT];
-  const int ntc = res_copies(ldq);
-  double* Spart = w.Spart;
-  double* Hpart = w.H2part;
-  double* H2 = w.H2;
-  double* Tv = w.T;
-  double* const Tr = w.T + (int64_t)(b % ntc) * m;   // the copy of t~ this block reads
+  __shared__ double prw[NS][RB];
+  __shared__ double zs[RB], zw[RB], ws[RB];
+  __shared__ double rq[NW][RB + 1], rg[NW][RB + 1];
+  __shared__ double red[3][NW], z2s;
+  __shared__ double cpart[NT], hw[NW];
+  __shared__ double cr[P > 1 ? P : 1][P > 1 ? m : 1];
+  __shared__ int bad;
+  const int ntc = res_copies(ldq, nb);
+  double* Spart = w.Spart + (int64_t)a * nb * m;
+  double* Hpart = w.H2part + (int64_t)a * nb * hs;
+  double* H2 = w.H2 + (int64_t)a * hs;
+  double* Tv = w.T + (int64_t)a * ldq * m;
+  double* const Tr = Tv + (int64_t)(b % ntc) * m;   // the copy of t this block reads
+  double* Qa = w.Q + (int64_t)a * ldq * L;
+  double* alpha_o = w.alpha + (int64_t)a * n_it;
+  double* beta_o = w.beta + (int64_t)a * n_it;
+  const int lpl = 31 - __builtin_clz(nb);        // LP = nb = 2^lpl threads sum one entry of h2
 
-  // the block's rows of Phi (rows past L are zero) and of q_0
-  float4 ph[RB][NH];
+  // the wave's rows of Phi (rows past L are zero), the block's rows of q_0 and
+  // their weights
+  float4 ph[RW];
+  {
+    const float* src = w.Phi + (int64_t)a * L * m + cb;
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    const int row = min(r0 + r, L - 1);
+    for (int r = 0; r < RW; ++r)
+      ph[r] = *(const float4*)(src + (int64_t)min(r0 + pw * RW + r, L - 1) * m);
+    if (r0 + RB > L) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h) ph[r][h] = *(const float4*)(w.Phi + (int64_t)row * m + cb + 256 * h);
+      for (int r = 0; r < RW; ++r)
+        if (r0 + pw * RW + r >= L) ph[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
   }
-  if (r0 + RB > L) {
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-      if (r0 + r >= L) {
-#pragma unroll
-        for (int h = 0; h < NH; ++h) ph[r][h] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-  }
+  if (tid == 0) bad = 0;
   if (tid < RB) {
-    const double q = (r0 + tid < L) ? q1[r0 + tid] : 0.0;
+    const double q = (r0 + tid < L) ? q1[(int64_t)a * L + r0 + tid] : 0.0;
+    const double wr = (w.wt && r0 + tid < L) ? w.wt[(int64_t)a * L + r0 + tid] : 1.0;
     Qs[tid] = q;
     zs[tid] = q;
+    zw[tid] = wr * q;
+    ws[tid] = wr;
   }
   __syncthreads();
 
-  // partials of Phi^T zs over the block's rows, tagged with step e
+  // partials of Phi^T diag(weights) zs over the block's rows, tagged with step e
   auto col_partials = [&](int e) {
-    double col[CPL];
+    double col[4] = {0.0, 0.0, 0.0, 0.0};
+    launder_rows(ph);
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) col[c] = 0.0;
-    if constexpr (INPLACE) launder_rows(ph);
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const double z = zs[r];
-#pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        const float4 x = INPLACE ? ph[r][h] : pin4(ph[r][h]);
-        col[4 * h + 0] = fma((double)x.x, z, col[4 * h + 0]);
-        col[4 * h + 1] = fma((double)x.y, z, col[4 * h + 1]);
-        col[4 * h + 2] = fma((double)x.z, z, col[4 * h + 2]);
-        col[4 * h + 3] = fma((double)x.w, z, col[4 * h + 3]);
-      }
+    for (int r = 0; r < RW; ++r) {
+      const double z = zw[pw * RW + r];
+      col[0] = fma((double)ph[r].x, z, col[0]);
+      col[1] = fma((double)ph[r].y, z, col[1]);
+      col[2] = fma((double)ph[r].z, z, col[2]);
+      col[3] = fma((double)ph[r].w, z, col[3]);
     }
     // column c of block b at ((c / CB) nb + b) CB + c % CB: the partials a block
-    // reduces are contiguous (CB = m / nb, a multiple of 4)
-    const int CB = m / nb;
+    // reduces are contiguous
+    if constexpr (P == 1) {
+      double* dst = Spart + ((((int64_t)(cb >> cbl) * nb + b) << cbl) + (cb & (CB - 1)));
+      st_tag2(dst, col[0], col[1], e);
+      st_tag2(dst + 2, col[2], col[3], e);
+    } else {
+      // the row subsets' sums meet in LDS, in order; thread = CPT columns
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const int c = cb + 256 * h;
-      double* dst = Spart + ((int64_t)(c / CB) * nb + b) * CB + c % CB;
+      for (int q = 0; q < 4; ++q) cr[pw][cb + q] = col[q];
+      __syncthreads();
+      const int c = tid * CPT;
+      if (P <= 4 || c < m) {
+        double v[CPT];
 #pragma unroll
-      for (int q = 0; q < 4; q += 2) st_tag2(dst + q, col[4 * h + q], col[4 * h + q + 1], e);
+        for (int q = 0; q < CPT; ++q) {
+          v[q] = cr[0][c + q];
+#pragma unroll
+          for (int p = 1; p < P; ++p) v[q] += cr[p][c + q];
+        }
+        double* dst = Spart + ((((int64_t)(c >> cbl) * nb + b) << cbl) + (c & (CB - 1)));
+        if constexpr (CPT == 2) st_tag2(dst, v[0], v[1], e);
+        else st_tag(dst, v[0], e);
+      }
     }
   };
-  // t over the block's columns from the partials of step e (scaled by 1 / |z1|
-  // when norm, |z1|^2 summed here from its partials first) into every copy,
-  // tagged with step e; with kh >= 0 first the h2 entry kh.  Thread = (column
-  // cl < CB, partial lane pl < NT / CB).  false when a wait failed.
-  auto col_reduce = [&](bool norm, double& z2v, int e, int kh) -> bool {
-    const int CB = m / nb;
-    const int64_t base = (int64_t)b * nb * CB + tid;
-    stores_done_barrier();
-    double v[CPL], zv[1], hv[1];
-    bool ok = ld_wait<CPL>([&](int u) { return Spart + base + u * NT; }, (1u << CPL) - 1u, e, bar, spin, v);
-    if (norm)
-      ok = ld_wait<1>([&](int) { return Hpart + (int64_t)tid * hs + ldq; }, tid < nb ? 1u : 0u, e,
-                      bar, spin, zv) && ok;
-    ok = ld_wait<1>([&](int) { return Hpart + (int64_t)tid * hs + kh; }, (kh >= 0 && tid < nb) ? 1u : 0u,
-                    e, bar, spin, hv) && ok;
-    if (!block_ok(ok)) return false;
-    if (norm || kh >= 0) {
-      double d2 = 0.0;
-      if (!norm) zv[0] = 0.0;
-      block_sum3(zv[0], hv[0], d2, red);
-      if (norm) z2v = zv[0];
-      if (kh >= 0 && tid == 0) st_tag(H2 + kh, hv[0], e);
-    }
-    double sm = 0.0;
+  // The values of step e reduced across the blocks: t over the block's CB
+  // columns into every copy (cols), and its entries k = b, b + nb, ... <= last
+  // of h2 (k = last: |z1|^2, slot ldq; none for last < 0).  Thread = (column
+  // tid % CB, partial lane tid / CB); for h2 (from the last thread down) LP
+  // threads over the nb partials of an entry.  The loads of both go out
+  // together, so that an entry of h2 costs no round trip of its own.
+  auto reduce = [&](int e, bool cols, int last) -> bool {
+    // an opaque copy of the thread's index: the addresses below are formed here
+    // in every step instead of being held in registers across it
+    unsigned td = threadIdx.x;
+    asm volatile("" : "+v"(td));
+    const unsigned ln = td & 63, wq = td >> 6, th = NT - 1 - td;
+    const bool own = cols && (b << cbl) < m;
+    const unsigned tot = own ? nb << cbl : 0, endc = (nb << cbl) - 1;
+    const int LP = 1 << lpl;
+    const unsigned pl = th & (LP - 1);
+    double* const src = Spart + (own ? ((int64_t)b * nb) << cbl : 0);
+    int k = (int)(th >> lpl) < NT >> lpl ? b + nb * (int)(th >> lpl) : last + 1;
+    int slot = k >= last ? ldq : k;
+    unsigned act = (k <= last && (int)pl < nb) ? 1u << UL : 0u;
 #pragma unroll
-    for (int u = 0; u < CPL; ++u) sm += v[u];
-    // a column's partial lanes within a wave lie CB lanes apart: an xor
-    // butterfly over them (both lanes of a pair get the same sum), then the
-    // waves' sums (for CB >= 64, the column's lanes) in order
-    for (int o = CB; o < 64; o <<= 1) sm += __shfl_xor(sm, o);
-    const int SD = CB < 64 ? 64 : CB;
-    if (lane < CB) cpart[tid] = sm;
+    for (int u = 0; u < UL; ++u) act |= (td + u * NT < tot) ? 1u << u : 0u;
+    stores_done_barrier();
+    double v[UL + 1];
+    bool ok = ld_wait<UL + 1>(
+        [&](int u) {
+          return u < UL ? src + min(td + u * NT, endc) : Hpart + (min(pl, nb - 1u) * (unsigned)hs + slot);
+        },
+        act, e, bar, spin, v);
+    double sm = v[0];
+#pragma unroll
+    for (int u = 1; u < UL; ++u) sm += v[u];
+    // a column's partial lanes within a wave lie CB lanes apart, then the waves'
+    // sums (for CB >= 64, the column's lanes) in order
+    sm = strided_sum(sm, CB);
+    double hv = group_sum(v[UL], LP);
+    if ((int)ln < CB) cpart[td] = sm;
+    if (LP > 64 && ln == 0) hw[wq] = hv;
+    if (!ok) bad = 1;
     __syncthreads();
+    if (bad) return false;
     // thread (copy r, column cl) sums the column (the same sum in every copy)
-    for (int q = tid; q < CB * ntc; q += NT) {
-      const int cl = q % CB, r = q / CB;
-      double S = 0.0;
-      for (int p = 0; p < NT / SD; ++p) S += cpart[p * SD + cl];
-      const double t = norm ? (z2v > 0.0 ? S / sqrt(z2v) : 0.0) : S;
-      st_tag(Tv + (int64_t)r * m + b * CB + cl, t, e);
+    if (own) {
+      const int SD = CB < 64 ? 64 : CB;
+      for (int q = td; q < ntc << cbl; q += NT) {
+        const int cl = q & (CB - 1), r = q >> cbl;
+        double S = cpart[cl];
+        for (int p = SD; p < NT; p += SD) S += cpart[p + cl];
+        st_tag(Tv + (int64_t)r * m + (b << cbl) + cl, S, e);
+      }
+    }
+    if (pl == 0 && k <= last) {
+      for (int q = 1; q < LP >> 6; ++q) hv += hw[wq - q];
+      st_tag(H2 + slot, hv, e);
+    }
+    // entries past the threads' (NT / nb of them were taken above): one per wave
+    for (int q = (NT >> lpl) + (int)wq; b + nb * q <= last; q += NW) {
+      k = b + nb * q;
+      slot = k >= last ? ldq : k;
+      hv = 0.0;
+      for (unsigned p0 = 0; p0 < (unsigned)nb; p0 += 64) {
+        double hx[1];
+        if (!ld_wait<1>([&](int) { return Hpart + (min(p0 + ln, nb - 1u) * (unsigned)hs + slot); },
+                        p0 + ln < (unsigned)nb ? 1u : 0u, e, bar, spin, hx))
+          bad = 1;
+        hv += hx[0];
+      }
+      hv = wave_sum_f64(hv);
+      if (ln == 0) st_tag(H2 + slot, hv, e);
     }
     stores_done_barrier();
-    return true;
+    return bad == 0;
   };
-  // sum over the blocks of the h2 partial k (or |z1|^2 for k = ldq) of step e
-  auto hpart_sum = [&](int k, int e, double& out) -> bool {
-    stores_done_barrier();
-    double hv[1];
-    const bool ok = ld_wait<1>([&](int) { return Hpart + (int64_t)tid * hs + k; }, tid < nb ? 1u : 0u,
-                               e, bar, spin, hv);
-    if (!block_ok(ok)) return false;
-    double d1 = 0.0, d2 = 0.0;
-    block_sum3(hv[0], d1, d2, red);
-    out = hv[0];
-    return true;
-  };
-
-  // t_0 = Phi^T q_0 and its |t_0|^2 partials: step 0 of the tags
-  col_partials(0);
-  double z2 = 0.0;
-  if (!col_reduce(false, z2, 0, -1)) return;
 
   double amax = 0.0;
   const int idx = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-  for (int j = 0; j < n_it; ++j) {
+  // j = -1: t_0 = Phi^T q_0 only (step 0 of the tags)
+  for (int j = -1; j < n_it; ++j) {
+    if (j >= 0) {
     // ---- rows: the reduced values of the previous step (tags of step j),
     // those of this step tagged j + 1.  A wave takes its row dots as soon as its
-    // own entries of t~ have arrived (the scalars of the step wait for values
+    // own entries of t have arrived (the scalars of the step wait for values
     // of every block).
-    double tv[CPL], h1[1];
-    bool ok = ld_wait<CPL>([&](int u) { return Tr + cb + 256 * (u >> 2) + (u & 3); }, (1u << CPL) - 1u,
-                           j, bar, spin, tv);
-    // Phi t~ of the block's rows: 4 CPL products per lane and row, summed over
-    // the wave 8 rows at a time (into prw), then over the NW waves
-    if constexpr (INPLACE) launder_rows(ph);
+    double tv[4];
+    bool ok = ld_wait<4>([&](int u) { return Tr + cb + u; }, 15u, j, bar, spin, tv);
+    // Phi t of the block's rows: 4 products per lane and row, summed over the
+    // wave 8 rows at a time (into prw), then over the NS slices
+    launder_rows(ph);
 #pragma unroll
-    for (int r8 = 0; r8 < RB; r8 += 8) {
+    for (int r8 = 0; r8 < RW; r8 += 8) {
       double d[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        double x = 0.0;
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-          const float4 y = INPLACE ? ph[r8 + e][h] : pin4(ph[r8 + e][h]);
-          x = fma((double)y.x, tv[4 * h + 0], x);
-          x = fma((double)y.y, tv[4 * h + 1], x);
-          x = fma((double)y.z, tv[4 * h + 2], x);
-          x = fma((double)y.w, tv[4 * h + 3], x);
-        }
-        d[e] = x;
+        const float4 y = ph[r8 + e];
+        double x = (double)y.x * tv[0];
+        x = fma((double)y.y, tv[1], x);
+        x = fma((double)y.z, tv[2], x);
+        d[e] = fma((double)y.w, tv[3], x);
       }
       const double tot = wave_sum8_f64(d);
-      if ((lane & 7) == 0) prw[wv][r8 + idx] = tot;
+      if ((lane & 7) == 0) prw[sl][pw * RW + r8 + idx] = tot;
     }
-    ok = ld_wait<1>([&](int) { return H2 + tid; }, tid < j ? 1u : 0u, j, bar, spin, h1) && ok;
-    if (!block_ok(ok)) return;
-    const double h2v = h1[0];
-    // this thread's share of alpha~ = |t~|^2: every block holds all of t~ and
-    // sums it in the same order, so every block gets the same value
-    double apv = 0.0;
-#pragma unroll
-    for (int u = 0; u < CPL; ++u) apv = fma(tv[u], tv[u], apv);
+    // h2 (threads < j) with the neighbours that the wave's edge lanes need for
+    // g, and |z1|^2 (thread j); T_{j-1}'s entries are read while they arrive
+    const int tj = min(tid, max(j - 1, 0));
+    const double alv = als[tj], bev = bes[tj], bep = bes[max(tj - 1, 0)];
+    double h1[2];
+    {
+      const int nbr = lane == 0 ? tid - 1 : tid + 1;
+      const unsigned act = (j > 0 && tid <= j ? 1u : 0u) |
+                           (tid < j && (lane == 0 || lane == 63) && nbr >= 0 && nbr < j ? 2u : 0u);
+      ok = ld_wait<2>([&](int u) { return H2 + (u == 0 ? (tid < j ? tid : ldq) : max(0, min(nbr, ldq))); },
+                      act, j, bar, spin, h1) && ok;
+    }
+    const double h2v = tid < j ? h1[0] : 0.0;
     if (tid < j) h2s[tid] = h2v;
-    __syncthreads();
+    if (tid == j) z2s = h1[0];
+    if (!ok) bad = 1;
     // g = T_{j-1} h2 (alpha_k on the diagonal, beta_k beside it; beta_{j-1} is
-    // not part of T_{j-1}); alpha~ = |t~|^2, |h2|^2 and h2^T g
-    double gi = 0.0;
-    if (tid < j) {
-      gi = als[tid] * h2v;
-      if (tid > 0) gi = fma(bes[tid - 1], h2s[tid - 1], gi);
-      if (tid + 1 < j) gi = fma(bes[tid], h2s[tid + 1], gi);
-      gs[tid] = gi;
-    }
-    double alpha_t = apv, hh = h2v * h2v, hth = h2v * gi;
-    block_sum3(alpha_t, hh, hth, red);
-    double alpha = alpha_t, beta = 0.0, h2last = 0.0, ibeta = 0.0;
-    if (j > 0) {
-      const double b2 = z2 - hh;
-      beta = b2 > 0.0 ? sqrt(b2) : 0.0;
-      if (!(beta > w.tol * amax)) {             // breakdown: n_eff stays j
-        if (b == 0 && tid == 0) {
-          w.beta[j - 1] = beta;
-          w.stop[0] = 1;
-        }
-        return;
-      }
-      h2last = h2s[j - 1];
-      alpha = (z2 * alpha_t - hth) / (beta * beta) - 2.0 * h2last;
-      // (the 256-thread kernel multiplies by 1 / beta below: one division per
-      // step rather than two per row on the block's dependent path; at 512
-      // threads the extra value held costs more than the divisions)
-      if constexpr (NT <= 256) ibeta = 1.0 / beta;
-    }
-    amax = fmax(amax, fabs(alpha));
-    if (tid == 0) {
-      als[j] = alpha;
-      if (j > 0) bes[j - 1] = beta;
-      if (b == 0) {
-        if (j > 0) w.beta[j - 1] = beta;
-        w.alpha[j] = alpha;
-        w.neff[0] = j + 1;
+    // not part of T_{j-1}); |h2|^2 and h2^T g; |t|^2 (each column once: the
+    // first row subset's waves): every block holds all of t and sums it in the
+    // same order, so every block gets the same value
+    double hp = dpp_f64<DPP_WAVE_SHR1>(h2v), hn = dpp_f64<DPP_WAVE_SHL1>(h2v);
+    if (lane == 0) hp = h1[1];
+    if (lane == 63) hn = h1[1];
+    double gi = alv * h2v;
+    gi = fma(tid > 0 ? bep : 0.0, hp, gi);
+    gi = fma(tid + 1 < j ? bev : 0.0, hn, gi);
+    if (tid < j) gs[tid] = gi;
+    else gi = 0.0;
+    {
+      double apv = 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) apv = fma(tv[u], tv[u], apv);
+      // (three sums in one stretch of code, so that their steps overlap)
+      const double sa = wave_sum_f64(apv), sh = wave_sum_f64(h2v * h2v), sg = wave_sum_f64(h2v * gi);
+      if (lane == 0) {
+        red[0][wv] = sa;
+        red[1][wv] = sh;
+        red[2][wv] = sg;
       }
     }
+    __syncthreads();
+    if (bad) return;
     // Q_{j-1} h2 and Q_{j-1} g of each row: thread = (row i, k-group kg)
     {
       const int i = tid % RB, kg = tid / RB;
       double aq = 0.0, ag = 0.0;
+#pragma unroll 4
       for (int k = kg; k < j; k += KG) {
         const double qk = Qs[k * QS + i];
         aq = fma(qk, h2s[k], aq);
         ag = fma(qk, gs[k], ag);
       }
-      rq[kg][i] = aq;
-      rg[kg][i] = ag;
+      // the wave's k-groups of a row lie RB lanes apart
+      if constexpr (RB <= 32) {
+        aq = strided_sum(aq, RB);
+        ag = strided_sum(ag, RB);
+      }
+      if (lane < RB) {
+        rq[wv][i] = aq;
+        rg[wv][i] = ag;
+      }
+    }
+    double alpha = red[0][0];
+#pragma unroll
+    for (int q = 1; q < NS; ++q) alpha += red[0][q];
+    double beta = 0.0, h2last = 0.0, ibeta = 0.0;
+    if (j > 0) {
+      double hh = red[1][0], hth = red[2][0];
+      for (int q = 1; 64 * q < j; ++q) {
+        hh += red[1][q];
+        hth += red[2][q];
+      }
+      const double b2 = z2s - hh;
+      if (b2 > 0.0) sqrt_rsqrt(b2, beta, ibeta);
+      if (!(beta > w.tol * amax)) {             // breakdown: n_eff stays j
+        if (b == 0 && tid == 0) {
+          beta_o[j - 1] = beta;
+          w.stop[a] = 1;
+        }
+        return;
+      }
+      h2last = h2s[j - 1];
+      alpha = (alpha - hth) * (ibeta * ibeta) - 2.0 * h2last;
+    }
+    amax = fmax(amax, fabs(alpha));
+    if (tid == 64) {
+      als[j] = alpha;
+      if (j > 0) bes[j - 1] = beta;
+      if (b == 0) {
+        if (j > 0) beta_o[j - 1] = beta;
+        alpha_o[j] = alpha;
+        w.neff[a] = j + 1;
+      }
     }
     __syncthreads();
-    if (tid < RB) {
-      const int i = tid, row = r0 + i;
-      double sub = 0.0, sg = 0.0;
-      for (int q = 0; q < KG; ++q) {
-        sub += rq[q][i];
-        sg += rg[q][i];
+    // q_j and z1 of the block's rows: wave 0, RP lanes a row over the waves' sums
+    if (tid < 64) {
+      const int i = tid % RB, part = tid / RB, row = r0 + i;
+      double sub = 0.0, sg = 0.0, u = 0.0;
+#pragma unroll
+      for (int q = 0; q < NW; q += RP) {
+        if (NW % RP == 0 || q + part < NW) {
+          sub += rq[q + part][i];
+          sg += rg[q + part][i];
+        }
       }
+#pragma unroll
+      for (int q = 0; q < NS; q += RP) {
+        if (NS % RP == 0 || q + part < NS) u += prw[q + part][i];
+      }
+      if constexpr (RB <= 32) {
+        sub = strided_sum(sub, RB);
+        sg = strided_sum(sg, RB);
+        u = strided_sum(u, RB);
+      }
+      const double wr = ws[i];
+      u *= wr;
       double q = Qs[i], qm = 0.0;                 // j = 0: q_0
       if (j > 0) {
-        if constexpr (NT <= 256) q = (row < L) ? (zs[i] - sub) * ibeta : 0.0;
-        else q = (row < L) ? (zs[i] - sub) / beta : 0.0;
+        q = (row < L) ? (zs[i] - sub) * ibeta : 0.0;
         qm = Qs[(j - 1) * QS + i];
-        Qs[j * QS + i] = q;
-        if (row < L) w.Q[(int64_t)j * L + row] = q;
-      }
-      qr[i] = q;
-      qmr[i] = qm;
-      sgr[i] = sg;
-    }
-    __syncthreads();
-    // z1 of the block's rows, and their partial of |z1|^2 (wave 0 holds the RB rows)
-    if (tid < 64) {
-      double z = 0.0;
-      if (tid < RB) {
-        const int i = tid;
-        double u = prw[0][i];
-#pragma unroll
-        for (int q = 1; q < NW; ++q) u += prw[q][i];
-        const double q = qr[i];
-        if constexpr (NT <= 256) {
-          if (j > 0) u = (fma(sqrt(z2), u, -sgr[i]) - beta * h2last * q) * ibeta;
-        } else {
-          if (j > 0) u = (fma(sqrt(z2), u, -sgr[i]) - beta * h2last * q) / beta;
+        if (part == 0) {
+          Qs[j * QS + i] = q;
+          if (row < L) Qa[(int64_t)j * L + row] = q;
         }
-        z = (u - alpha * q) - beta * qmr[i];
-        z = (r0 + i < L) ? z : 0.0;
-        zs[i] = z;
+        u = ((u - sg) - beta * h2last * q) * ibeta;
       }
-      const double zz = wave_sum_f64(z * z);
-      if (tid == 0) st_tag(Hpart + (int64_t)b * hs + ldq, zz, j + 1);
+      double z = (u - alpha * q) - beta * qm;
+      z = (row < L) ? z : 0.0;
+      if (part == 0) {
+        zs[i] = z;
+        zw[i] = wr * z;
+      }
     }
     __syncthreads();
+    }
     // partials of Phi^T z1, then of h2 = Q_j^T z1 (k <= j): the h2 partials are
-    // read only after the column partials have been reduced, so they are formed
-    // while those travel
+    // formed while the column partials travel
     col_partials(j + 1);
-    if constexpr (NT <= 256) {
-      // four threads per entry k (four lanes of a wave), RB / 4 rows each
-      for (int t = tid; t < 4 * (j + 1); t += NT) {
-        const int k = t >> 2, p4 = t & 3;
-        const double* qk = Qs + k * QS + p4 * (RB / 4);
-        const double* zq = zs + p4 * (RB / 4);
-        double a2[2] = {0.0, 0.0};
+    // four threads per entry k (four lanes of a wave), RB / 4 rows each; the
+    // entry after the last is |z1|^2
+    for (int t = tid; t < 4 * (j + 2) && j >= 0; t += NT) {
+      const int k = t >> 2, p4 = t & 3;
+      const double* qk = (k <= j ? Qs + k * QS : zs) + p4 * (RB / 4);
+      const double* zq = zs + p4 * (RB / 4);
+      double a2[2] = {0.0, 0.0};
 #pragma unroll
-        for (int i = 0; i < RB / 4; ++i) a2[i & 1] = fma(qk[i], zq[i], a2[i & 1]);
-        double v = a2[0] + a2[1];
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        if (p4 == 0) st_tag(Hpart + (int64_t)b * hs + k, v, j + 1);
-      }
-    } else {
-      for (int k = tid; k <= j; k += NT) {
-        double a4[4] = {0.0, 0.0, 0.0, 0.0};
-        const double* qk = Qs + k * QS;
-#pragma unroll
-        for (int i = 0; i < RB; ++i) a4[i & 3] = fma(qk[i], zs[i], a4[i & 3]);
-        st_tag(Hpart + (int64_t)b * hs + k, (a4[0] + a4[1]) + (a4[2] + a4[3]), j + 1);
-      }
+      for (int i = 0; i < RB / 4; ++i) a2[i & 1] = fma(qk[i], zq[i], a2[i & 1]);
+      double v = a2[0] + a2[1];
+      v += dpp_f64<DPP_XOR1>(v);
+      v += dpp_f64<DPP_XOR2>(v);
+      if (p4 == 0) st_tag(Hpart + (int64_t)b * hs + (k <= j ? k : ldq), v, j + 1);
     }
-    // ---- columns: |z1|^2 (every block), t~_{j+1}, h2
-    int k0 = b;                                   // h2 entries of this block: b, b + nb, ...
-    if (j + 1 < n_it) {
-      if (!col_reduce(true, z2, j + 1, b <= j ? b : -1)) return;
-      k0 = b + nb;
-    } else {
-      if (!hpart_sum(ldq, j + 1, z2)) return;
-    }
-    for (int k = k0; k <= j; k += nb) {
-      double v = 0.0;
-      if (!hpart_sum(k, j + 1, v)) return;
-      if (tid == 0) st_tag(H2 + k, v, j + 1);
-    }
+    // ---- t_{j+1}, h2 and |z1|^2 (entry j + 1)
+    if (!reduce(j + 1, j + 1 < n_it, j < 0 ? -1 : j + 1)) return;
   }
   // beta of the last step (reported; T does not use it)
   if (b == 0) {
     double hv[1];
-    const bool ok = ld_wait<1>([&](int) { return H2 + tid; }, tid < n_it ? 1u : 0u, n_it, bar, spin, hv);
-    if (!block_ok(ok)) return;
-    double hh2 = hv[0] * hv[0], d1 = 0.0, d2 = 0.0;
-    block_sum3(hh2, d1, d2, red);
+    const bool ok = ld_wait<1>([&](int) { return H2 + min(tid, ldq); }, tid < n_it ? 1u : 0u, n_it, bar,
+                               spin, hv);
+    const double sh = wave_sum_f64(hv[0] * hv[0]);
+    if (lane == 0) red[0][wv] = sh;
+    if (!ok) bad = 1;
+    __syncthreads();
+    if (bad) return;
     if (tid == 0) {
-      const double b2 = z2 - hh2;
-      w.beta[n_it - 1] = b2 > 0.0 ? sqrt(b2) : 0.0;
+      double hh = red[0][0];
+      for (int q = 1; q < NW; ++q) hh += red[0][q];
+      if (!ld_wait<1>([&](int) { return H2 + ldq; }, 1u, n_it, bar, spin, hv)) return;
+      const double b2 = hv[0] - hh;
+      beta_o[n_it - 1] = b2 > 0.0 ? sqrt(b2) : 0.0;
     }
   }
 }
 
 // Everything the kernel expects before it starts, in one launch: q_0 into
-// Q[0], alpha, beta, n_eff, the breakdown flag and max |alpha| cleared (the
+// Q[a][0], alpha, beta, n_eff, the breakdown flag and max |alpha| cleared (the
 // streaming path's k_lz_start), and the status word and every buffer of tagged
 // values zeroed (tag 0: not yet written).
 struct ResClear {
-  double* p[6];
-  int64_t n[6];   // doubles
+  double* p[5];
+  int64_t n[5];   // doubles
 };
 __global__ void k_lz_res_prep(LanczosWS w, const double* __restrict__ q1, ResClear z) {
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t st = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = t0; i < w.L; i += st) w.Q[i] = q1[i];
-  for (int64_t i = t0; i < w.n_it; i += st) {
+  for (int64_t i = t0; i < (int64_t)w.n_act * w.L; i += st) {
+    const int64_t a = i / w.L;
+    w.Q[a * w.ldq * w.L + i - a * w.L] = q1[i];
+  }
+  for (int64_t i = t0; i < (int64_t)w.n_act * w.n_it; i += st) {
     w.alpha[i] = 0.0;
     w.beta[i] = 0.0;
   }
-  if (t0 == 0) {
-    w.stop[0] = 0;
-    w.neff[0] = 0;
-    w.amax[0] = 0.0;
-    w.amax[1] = 0.0;
+  for (int64_t a = t0; a < w.n_act; a += st) {
+    w.stop[a] = 0;
+    w.neff[a] = 0;
+    w.amax[2 * a] = 0.0;
+    w.amax[2 * a + 1] = 0.0;
   }
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
+  for (int q = 0; q < 5; ++q)
     for (int64_t i = t0; i < z.n[q]; i += st) z.p[q][i] = 0.0;
 }
 
 namespace {
 struct ResShape {
-  int rb, nb, nt;   // rows per block, blocks, threads per block
+  int p, rw, nb, cbl;   // row subsets, rows per wave, blocks per window, log2 of the columns per owner
 };
-// The resident kernel's shape, or rb = 0 when it does not qualify: one window,
-// m of 1024 (256 threads, 4 columns a lane) or 2048 (512 threads, 4 columns a
-// lane), rb of 32 or 16 rows a block, nb = ceil(L / rb) rounded up to a power of
-// two, dividing m, at most one block per compute unit and per row group of the
-// workspace, n_it <= 256
-ResShape res_shape(const LanczosWS& w, int n_cu) {
-  ResShape s{0, 0, 0};
-  if (w.n_act != 1 || (w.m != 1024 && w.m != 2048) || w.n_it > 256 || w.n_it < 1) return s;
-  const int nt = w.m == 2048 ? 512 : LR_T;
-  for (int rb : {32, 16}) {
-    int nb = 1;                                // ceil(L / rb) rounded up to a power of two
-    while (nb * rb < w.L) nb *= 2;             // (blocks past the last row hold zeros)
-    if (nb > n_cu || nb > w.G3 || (nb & (nb - 1)) != 0 || w.m % nb != 0 || w.m / nb > nt ||
-        w.m / nb < 4)
-      continue;   // (G3 row groups: the rows of Spart and H2part)
-    s.rb = rb;
-    s.nb = nb;
-    s.nt = nt;
-    return s;
+// The resident kernel's shapes for w in order of preference; returns their number
+// (0: it does not qualify).  nb = ceil(L / RB) rounded up to a power of two
+// (blocks past the last row hold zeros), at least m / (the most columns a block
+// can own), at most 256, all windows' blocks at most two per compute unit.
+// Preferred: the fewest rows a block (less work per step in each) while the
+// exchanged partials, nb m doubles a step and window, stay few: nb <= 128, or
+// nb m <= 2^17.  Measured, us a step (rows a block): 5003 x 512 6.5 (32) 6.8
+// (64); 1216 x 256 5.3 (32) 5.6 (64); 1367 x 1024 8.4 (8) 6.6 (16) 6.9 (32);
+// 4096 x 1024 8.7 (16) 7.5 (32); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
+// (16) 8.1 (32); 3001 x 768 7.2 (16) 7.0 (32) 8.5 (64).
+int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
+  if (w.n_act < 1 || w.m % 256 != 0 || w.m < 256 || w.m > 2048 || w.n_it > 256 || w.n_it < 1) return 0;
+  const int ns = w.m / 256, p = ns == 1 ? 4 : ns <= 3 ? 2 : 1, nt = 64 * ns * p;
+  const int cbmax = std::min(nt & -nt, 256);     // a power of two dividing the threads
+  ResShape c[3];
+  int n = 0, pref = -1;
+  for (int rw : {8, 16, 32}) {
+    if (p * rw > 64) continue;
+    int64_t nb = 1;
+    while (nb * p * rw < w.L || nb * cbmax < w.m) nb *= 2;
+    if (nb > 256 || nb * w.n_act > 2LL * n_cu) continue;
+    int cbl = 2;
+    while ((nb << cbl) < w.m) ++cbl;
+    if (pref < 0 && nb * w.n_act <= n_cu && (nb <= 128 || nb * w.m <= 131072)) pref = n;
+    c[n++] = ResShape{p, rw, (int)nb, cbl};
   }
-  return s;
+  // the preferred one, then the others from the most rows a block down
+  int k = 0;
+  if (pref >= 0) out[k++] = c[pref];
+  for (int q = n - 1; q >= 0; --q)
+    if (q != pref) out[k++] = c[q];
+  return k;
 }
-template <int RB, int CPL, int NT, bool SPIN>
+template <int NS, int P, int RW, bool SPIN>
 hipError_t launch_res_t(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                        bool check, hipStream_t s) {
-  auto k = k_lz_resident<RB, CPL, NT, SPIN>;
-  const size_t lds = (size_t)(w.n_it + 1) * (RB + 1) * sizeof(double);
+                        int check_cu, hipStream_t s) {
+  auto k = k_lz_resident<NS, P, RW, SPIN>;
+  constexpr int NT = 64 * NS * P;
+  const size_t lds = (size_t)(w.n_it + 1) * (P * RW + 1) * sizeof(double);
   if (lds > 65536) {
     const hipError_t e =
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (check) {
+  if (check_cu > 0) {
+    // every block resident at once
     int per_cu = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k, NT, lds);
     if (e != hipSuccess) return e;
-    return per_cu >= 1 ? hipSuccess : hipErrorInvalidConfiguration;
+    return (int64_t)per_cu * check_cu >= (int64_t)w.n_act * sh.nb ? hipSuccess
+                                                                  : hipErrorInvalidConfiguration;
   }
-  hipLaunchKernelGGL(k, dim3(sh.nb), dim3(NT), lds, s, w, bar, q1);
+  hipLaunchKernelGGL(k, dim3(sh.nb * w.n_act), dim3(NT), lds, s, w, bar, q1, sh.nb, sh.cbl);
   return hipGetLastError();
+}
+template <int NS, bool SPIN>
+hipError_t launch_res_n(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
+                        int check_cu, hipStream_t s) {
+  // P: the row subsets that fill 4 or 8 waves
+  constexpr int P = NS == 1 ? 4 : NS <= 3 ? 2 : 1;
+  if (sh.rw == 8) return launch_res_t<NS, P, 8, SPIN>(w, sh, bar, q1, check_cu, s);
+  if (sh.rw == 16) return launch_res_t<NS, P, 16, SPIN>(w, sh, bar, q1, check_cu, s);
+  if constexpr (P <= 2) return launch_res_t<NS, P, 32, SPIN>(w, sh, bar, q1, check_cu, s);
+  return hipErrorInvalidValue;
 }
 template <bool SPIN>
 hipError_t launch_res_s(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                        bool check, hipStream_t s) {
-  if (w.m == 2048) return sh.rb == 32 ? launch_res_t<32, 4, 512, SPIN>(w, sh, bar, q1, check, s)
-                                      : launch_res_t<16, 4, 512, SPIN>(w, sh, bar, q1, check, s);
-  return sh.rb == 32 ? launch_res_t<32, 4, LR_T, SPIN>(w, sh, bar, q1, check, s)
-                     : launch_res_t<16, 4, LR_T, SPIN>(w, sh, bar, q1, check, s);
+                        int check_cu, hipStream_t s) {
+  switch (w.m / 256) {
+    case 1: return launch_res_n<1, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 2: return launch_res_n<2, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 3: return launch_res_n<3, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 4: return launch_res_n<4, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 5: return launch_res_n<5, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 6: return launch_res_n<6, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 7: return launch_res_n<7, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 8: return launch_res_n<8, SPIN>(w, sh, bar, q1, check_cu, s);
+  }
+  return hipErrorInvalidValue;
 }
 // a wait limit other than the built-in one (SLH_OPT_WAIT_POLLS) takes an
 // instantiation of its own, so that the limit stays a constant in the other
 hipError_t launch_res(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                      bool check, hipStream_t s) {
-  return w.spin > 0 ? launch_res_s<true>(w, sh, bar, q1, check, s)
-                    : launch_res_s<false>(w, sh, bar, q1, check, s);
+                      int check_cu, hipStream_t s) {
+  return w.spin > 0 ? launch_res_s<true>(w, sh, bar, q1, check_cu, s)
+                    : launch_res_s<false>(w, sh, bar, q1, check_cu, s);
 }
 }  // namespace
 
-bool lanczos_resident_ok(const LanczosWS& w, int n_cu) {
-  const ResShape sh = res_shape(w, n_cu);
-  if (sh.rb == 0) return false;
+namespace {
+// the first shape whose blocks are all resident at once (p = 0: none)
+ResShape res_shape(const LanczosWS& w, int n_cu) {
+  ResShape sh[3];
+  const int n = res_shapes(w, n_cu, sh);
   (void)hipGetLastError();
-  return launch_res(w, sh, nullptr, nullptr, true, nullptr) == hipSuccess;
+  for (int q = 0; q < n; ++q)
+    if (launch_res(w, sh[q], nullptr, nullptr, n_cu, nullptr) == hipSuccess) return sh[q];
+  (void)hipGetLastError();
+  return ResShape{0, 0, 0, 0};
 }
+}  // namespace
 
-size_t lanczos_resident_bar_words(int n_cu) {
-  (void)n_cu;
+int lanczos_resident_blocks(const LanczosWS& w, int n_cu) { return res_shape(w, n_cu).nb; }
+
+size_t lanczos_resident_bar_words() {
   return (size_t)LR_ERR + 32;   // the error word on a line of its own
 }
 
@@ -621,14 +724,16 @@ hipError_t launch_lanczos_resident(const LanczosWS& w, const double* q1_act, uns
                                    int n_cu, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   (void)hipGetLastError();
   const ResShape sh = res_shape(w, n_cu);
-  if (sh.rb == 0) return hipErrorInvalidValue;
-  const int64_t hs = w.ldq + 1;
+  if (sh.p == 0) return hipErrorInvalidValue;
+  const int64_t hs = w.ldq + 1, na = w.n_act;
   ResClear z;
-  const double* const bufs[6] = {(const double*)bar, w.Spart, w.H2part, w.T, w.Apart, w.H2};
-  const int64_t lens[6] = {(int64_t)lanczos_resident_bar_words(n_cu) / 2, (int64_t)sh.nb * w.m,
-                           (int64_t)sh.nb * hs, (int64_t)res_copies(w.ldq) * w.m, 0, hs};
-  for (int q = 0; q < 6; ++q) {
-    z.p[q] = const_cast<double*>(bufs[q]);
+  double* const bufs[5] = {(double*)bar, w.Spart, w.H2part, w.T, w.H2};
+  // T: the copies in use lie at the front of each window's ldq m doubles
+  const int64_t lens[5] = {(int64_t)lanczos_resident_bar_words() / 2, na * sh.nb * w.m,
+                           na * sh.nb * hs,
+                           ((na - 1) * w.ldq + res_copies(w.ldq, sh.nb)) * w.m, na * hs};
+  for (int q = 0; q < 5; ++q) {
+    z.p[q] = bufs[q];
     z.n[q] = lens[q];
   }
   hipLaunchKernelGGL(k_lz_res_prep, dim3(256), dim3(256), 0, s, w, q1_act, z);
@@ -638,7 +743,7 @@ hipError_t launch_lanczos_resident(const LanczosWS& w, const double* q1_act, uns
     e = hipEventRecord(e0, s);
     if (e != hipSuccess) return e;
   }
-  e = launch_res(w, sh, bar, q1_act, false, s);
+  e = launch_res(w, sh, bar, q1_act, 0, s);
   if (e != hipSuccess) return e;
   if (e1) e = hipEventRecord(e1, s);
   return e;

@@ -826,15 +826,18 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
         w.NCH = chunks <= 2 * ncu ? 1 : (int)((chunks + ncu - 1) / ncu);
         w.G3 = (int)((L + 16 * w.NCH - 1) / (16 * w.NCH));
       }
+      // the resident kernel where every window's Phi fits in the register files
+      const int res_nb = c->resident ? lanczos_resident_blocks(w, c->n_cu) : 0;
+      const bool res = res_nb > 0;
+      const size_t grp = std::max(w.G3, res_nb);   // row groups of the partials
       const size_t hs = (size_t)w.ldq + 1;
       ENSURE(c, c->Q, (size_t)na * w.ldq * L * 8);
       ENSURE(c, c->T, (size_t)na * w.ldq * c->m * 8);
-      // |t|^2 partials: m / 16 per window, or one per block of the resident kernel
-      ENSURE(c, c->Apart, (size_t)na * std::max<int64_t>(c->m / 16, c->n_cu) * 8);
+      ENSURE(c, c->Apart, (size_t)na * (c->m / 16) * 8);   // |t|^2 partials
       ENSURE(c, c->Z1, (size_t)na * L * 8);
-      ENSURE(c, c->Spart, (size_t)na * w.G3 * c->m * 8);
+      ENSURE(c, c->Spart, na * grp * c->m * 8);
       ENSURE(c, c->Zs, (size_t)na * 2 * L * 8);
-      ENSURE(c, c->H2part, (size_t)na * w.G3 * hs * 8);
+      ENSURE(c, c->H2part, na * grp * hs * 8);
       ENSURE(c, c->H2, (size_t)na * hs * 8);
       ENSURE(c, c->alpha, (size_t)na * n_it * 8);
       ENSURE(c, c->beta, (size_t)na * n_it * 8);
@@ -858,10 +861,7 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       w.neff = P<int>(c->neff);
       w.stop = P<int>(c->stop);
       w.amax = P<double>(c->amax);
-      // one window whose Phi fits in the register files: the resident kernel
-      const bool res = c->resident && lanczos_resident_ok(w, c->n_cu);
-      (void)hipGetLastError();
-      if (res) ENSURE(c, c->lz_bar, lanczos_resident_bar_words(c->n_cu) * sizeof(unsigned));
+      if (res) ENSURE(c, c->lz_bar, lanczos_resident_bar_words() * sizeof(unsigned));
       if (c->timing) {
         // timing: launch the step sequence directly so that every pass over Phi
         // can be bracketed by events (events inside a captured graph cannot be timed)

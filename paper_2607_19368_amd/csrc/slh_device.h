@@ -74,9 +74,11 @@ __device__ __forceinline__ double f64_of(uint32_t lo, uint32_t hi) {
 
 // DPP controls used here: quad_perm [1, 0, 3, 2] (lane ^ 1), quad_perm
 // [2, 3, 0, 1] (lane ^ 2), row_half_mirror (7 - i within 8 lanes), row_mirror
-// (15 - i within 16), row_ror:8 (lane ^ 8 within 16).
+// (15 - i within 16), row_ror:8 (lane ^ 8 within 16), row_ror:4, and the whole
+// wave shifted by one lane (lane l of wave_shr:1 gets lane l - 1, of wave_shl:1
+// lane l + 1; the lane past the end keeps 0).
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140,
-              DPP_ROR8 = 0x128;
+              DPP_ROR8 = 0x128, DPP_ROR4 = 0x124, DPP_WAVE_SHR1 = 0x138, DPP_WAVE_SHL1 = 0x130;
 
 // The value of lane dpp(l) in lane l (every lane active).
 template <int CTRL>

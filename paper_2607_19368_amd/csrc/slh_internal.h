@@ -41,6 +41,8 @@ hipError_t launch_featmap(const FeatmapArgs& a, int n_cu, hipStream_t s, hipEven
 struct LanczosWS {
   int n_act, L, m, n_it, ldq;   // ldq = n_it + 1 vectors per window
   const float* Phi;             // [n_act][L][m]
+  const double* wt;             // [n_act][L] row weights: the operator is that of diag(wt) Phi
+                                //   (NULL: all 1)
   double* Q;                    // [n_act][ldq][L]  Lanczos basis, vector-major
   double* T;                    // [n_act][ldq][m]  t_j = Phi^T z1 / |z1| of step j-1 in slot j & 1
   double* Apart;                // [n_act][m/16]    partials of |t_j|^2 (= alpha_j) per 16 columns
@@ -75,16 +77,17 @@ hipError_t launch_lanczos_passes(const LanczosWS& w, int j, int reps, hipStream_
 // per-window state (n_eff, stop) cleared (k_lz_start)
 hipError_t launch_lanczos_start(const LanczosWS& w, const double* q1_act, hipStream_t s);
 
-// ---- resident Lanczos (k_lzres.hip): one window whose Phi fits in the register
-// files, the whole run as one persistent kernel (rows of Phi held in registers;
+// ---- resident Lanczos (k_lzres.hip): windows whose Phi fit in the register
+// files together, the whole run as one persistent kernel (rows of Phi held in registers;
 // the blocks exchange step-tagged values instead of meeting at barriers) ----
-// true when the shape qualifies (n_act 1, m 1024 or 2048, at most 32 rows per
-// compute unit, n_it <= 256) and every block of the kernel can be resident
-bool lanczos_resident_ok(const LanczosWS& w, int n_cu);
+// blocks per window when the shape qualifies (every window's rows fit, n_it <=
+// 256) and every block of the kernel can be resident at once, else 0; Spart and
+// H2part hold that many row groups per window
+int lanczos_resident_blocks(const LanczosWS& w, int n_cu);
 // 32-bit words of the kernel's status buffer; its error word, at index
 // LZ_BAR_ERR, is nonzero after a wait between blocks timed out (the run's
 // results are then invalid)
-size_t lanczos_resident_bar_words(int n_cu);
+size_t lanczos_resident_bar_words();
 constexpr int LZ_BAR_ERR = 32;
 // one preparation kernel (q_0 into Q[0] and the state cleared as k_lz_start
 // does; the status and exchange buffers zeroed), then the persistent kernel

@@ -385,6 +385,53 @@ def test_resident_lanczos_on_oracle_phi(case):
     assert da <= 1e-10 and db <= 1e-10 and dr <= 1e-10 and ang <= 1e-8
 
 
+@pytest.mark.parametrize("N,m,n_it,window", [
+    (100, 256, 20, 0),        # four waves a slice, four blocks, most of the last one past the end
+    (8190, 256, 256, 0),      # 256 blocks, as many threads as blocks, 257 entries of h2
+    (513, 512, 40, 0),        # one row in the last block that holds any
+    (1000, 768, 33, 0),       # columns not a power of two
+    (700, 1280, 256, 0),      # five waves
+    (2500, 1536, 24, 0), (300, 1792, 24, 0),
+    (4097, 2048, 24, 0),      # past 128 blocks of 32 rows
+    (64 * 40, 512, 24, 64), (5 * 161, 1024, 24, 161), (3 * 37, 2048, 12, 37)])
+def test_resident_shapes_match_streaming(N, m, n_it, window):
+    """Each shape of the resident kernel (column slices, rows per wave, blocks per
+    window) against the streaming path on the same Phi: the same recurrence with
+    partial sums grouped differently.  Basis orthonormal to 1e-12; alpha, beta to
+    1e-8 relative (rounding of 1e-16 per sum amplified by |A| / beta along the
+    steps, as between the streaming path and the oracle) where n_it is far below
+    the rank min(N, m) (near it the extreme Ritz values have converged and the
+    later entries of T are sensitive to every rounding; the Ritz values are not),
+    and the Ritz values to 1e-10 of the largest."""
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    g = torch.Generator().manual_seed(N + m)
+    Phi = torch.randn((N, m), generator=g) * torch.exp(-3.0 * torch.arange(m) / m)
+    Phi = Phi.cuda()
+    got = []
+    for resident in (1, 0):
+        ctx = P.slh_create(N, 64, m, 4, 4, 0)
+        if window:
+            P.slh_set_option(ctx, B.SLH_OPT_WINDOW_LEN, window)
+        P.slh_set_option(ctx, B.SLH_OPT_TIMING, 1)
+        P.slh_set_option(ctx, B.SLH_OPT_RESIDENT, resident)
+        P.slh_load(ctx, B.SLH_OUT_PHI, Phi)
+        ritz, iters = P.slh_lanczos(ctx, n_it)
+        assert P.slh_stage_times(ctx)["lanczos_resident"] == float(resident)
+        assert (iters == n_it).all()
+        got.append((ritz, P.slh_copy_out(ctx, B.SLH_OUT_ALPHA), P.slh_copy_out(ctx, B.SLH_OUT_BETA),
+                    P.slh_copy_out(ctx, B.SLH_OUT_Q)))
+    (ritz, al, be, Q), (ritz0, al0, be0, _) = got
+    worst = max(np.abs(q[:n_it] @ q[:n_it].T - np.eye(n_it)).max() for q in Q)
+    da, db = np.abs(al / al0 - 1).max(), np.abs(be / be0 - 1).max()
+    dr = np.abs(ritz - ritz0).max() / ritz0.max()
+    _say(f"[resident shapes] {N}x{m} window {window}: |Q^T Q - I| {worst:.1e} alpha {da:.1e} beta {db:.1e} ritz {dr:.1e}")
+    assert worst <= 1e-12 and dr <= 1e-10
+    if 4 * n_it <= min(window or N, m):
+        assert da <= 1e-8 and db <= 1e-8
+
+
 @pytest.mark.timeout(900)
 def test_end_to_end_qwen14b_long():
     inp = make_inputs("qwen14b_long")
