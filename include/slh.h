@@ -112,10 +112,8 @@ typedef struct slh_ctx slh_ctx;
                                     explicit L x L operator Phi_w Phi_w^T (the same
                                     operator and recurrence; section 3.5 local
                                     backend); 0: the general path for every L          */
-#define SLH_OPT_RESIDENT      11 /* 1 (default): a single window whose Phi fits in the
-                                    register files (m of 1024 or 2048, at most 32
-                                    rows per compute unit, n_it <= 256) runs the
-                                    whole Lanczos loop of Algorithm 2 as one
+#define SLH_OPT_RESIDENT      11 /* 1 (default): windows whose Phi fit in the register
+                                    files together (n_it <= 256) run the whole Lanczos loop of Algorithm 2 as one
                                     persistent kernel that holds its rows of Phi in
                                     registers (the same recurrence; partial sums in
                                     a different grouping); 0: one pass over Phi per
@@ -127,6 +125,16 @@ typedef struct slh_ctx slh_ctx;
                                     (default): 2^20, far beyond any wait of a
                                     healthy run (about a second).  Small values
                                     exercise that error path                       */
+
+#define SLH_OPT_DISTINCT      13 /* 1 (default): slh_feature_map looks for equal rows of
+                                    a bf16 X within each spectral window (of 33 to
+                                    131072 tokens) and, where they are many, Phi and
+                                    Lanczos take each distinct row once, weighted by
+                                    its count (the same operator on the span that
+                                    the start vector reaches: the same T, Ritz
+                                    values, Z and codes up to rounding; the call
+                                    then waits for the stream, except under stream
+                                    capture, where every row is taken); 0: every row */
 
 /*
  * Random parameters of the method, drawn from `seed` with Philox4x32-10
@@ -422,6 +430,10 @@ int slh_merge_noalloc(const void *X, int32_t x_dtype, int64_t ldx, int64_t N, in
 /* Number of windows and of spectral windows of the current routing. */
 int64_t slh_num_windows(const slh_ctx *ctx);
 int64_t slh_num_spectral(const slh_ctx *ctx);
+/* Rows per spectral window that the last slh_feature_map computed: the window
+ * length, or, where SLH_OPT_DISTINCT grouped equal rows, the most distinct rows
+ * of a window plus one. */
+int64_t slh_operator_rows(const slh_ctx *ctx);
 
 #ifdef __cplusplus
 }

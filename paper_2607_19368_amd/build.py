@@ -19,6 +19,7 @@ OBJ = os.path.join(PKG, "_build")
 SOURCES = [
     "slh_api.cpp",
     "k_prep.hip",
+    "k_group.hip",
     "k_featmap.hip",
     "k_lanczos.hip",
     "k_lzres.hip",

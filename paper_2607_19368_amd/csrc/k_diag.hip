@@ -10,8 +10,9 @@ namespace slh {
 
 // rowsq[a][i] = ||phi_i||^2: one wave per row, lane = 4 columns of every
 // 256-column slice, then a butterfly.
-__global__ __launch_bounds__(256) void k_dg_rowsq(const float* __restrict__ Phi, int L, int m,
-                                                  double* __restrict__ rowsq) {
+__global__ __launch_bounds__(256) void k_dg_rowsq(const float* __restrict__ Phi,
+                                                  const double* __restrict__ wt, int64_t ldr, int L,
+                                                  int m, double* __restrict__ rowsq) {
   const int a = blockIdx.y, lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= L) return;                          // whole waves
@@ -31,6 +32,10 @@ __global__ __launch_bounds__(256) void k_dg_rowsq(const float* __restrict__ Phi,
     }
   }
   d = wave_sum_f64(d);
+  if (wt) {                                      // a row that stands for wt^2 equal ones
+    const double w = wt[a * ldr + row];
+    d *= w * w;
+  }
   if (lane == 0) rowsq[(int64_t)a * L + row] = d;
 }
 
@@ -161,12 +166,13 @@ hipError_t launch_purity(const void* X, int dtype, int64_t ldx, int D, const int
   return hipGetLastError();
 }
 
-hipError_t launch_energy(const float* Phi, const double* theta, int n_act, int L, int m, int r,
-                         double* rowsq, double* energy, hipStream_t s) {
+hipError_t launch_energy(const float* Phi, const double* wt, int64_t ldr, const double* theta,
+                         int n_act, int L, int m, int r, double* rowsq, double* energy,
+                         hipStream_t s) {
   (void)hipGetLastError();
   if (n_act <= 0) return hipSuccess;
   if (m % 256 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_dg_rowsq, dim3((L + 3) / 4, n_act), dim3(256), 0, s, Phi, L, m, rowsq);
+  hipLaunchKernelGGL(k_dg_rowsq, dim3((L + 3) / 4, n_act), dim3(256), 0, s, Phi, wt, ldr, L, m, rowsq);
   hipLaunchKernelGGL(k_dg_energy, dim3(n_act), dim3(256), 0, s, rowsq, theta, L, r, energy);
   return hipGetLastError();
 }

@@ -77,10 +77,16 @@ __device__ __forceinline__ float fm_cos(float x) {
   return ((q + 1) & 2) ? -v : v;
 }
 
-__device__ __forceinline__ int fm_global_row(int ar, const int* winlist, int L) {
-  if (!winlist) return ar;
+// token of row ar; negative (~token) for a row of zeros
+__device__ __forceinline__ int fm_global_row(int ar, const FeatmapArgs& a) {
+  const int L = (int)a.L;
+  if (a.rowsrc) {
+    const int w = ar / L;
+    return a.rowsrc[w * a.ldr + (ar - w * L)];
+  }
+  if (!a.winlist) return ar;
   const int w = ar / L;
-  return winlist[w] * L + (ar - w * L);
+  return a.winlist[w] * L + (ar - w * L);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2); give
@@ -133,7 +139,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
   for (int q = 0; q < LA; ++q) {
     const int r = FM_RPL * (q * NW + wave) + lrow;
     const int ar = min(m0 + r, n_rows - 1);
-    arow[q] = a.X + (int64_t)fm_global_row(ar, a.winlist, (int)a.L) * a.ldx;
+    const int tok = fm_global_row(ar, a);
+    arow[q] = a.X + (int64_t)(tok < 0 ? ~tok : tok) * a.ldx;
     achk[q] = 8 * (lchk ^ fm_swz(r));
   }
   const uint16_t* bsrc[LB];
@@ -277,7 +284,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
 #pragma unroll
   for (int q = 0; q < WM / 64; ++q) {
     const int row = min(m0 + wm * WM + 64 * q + lane, n_rows - 1);
-    rsc[q] = a.rowscale[fm_global_row(row, a.winlist, (int)a.L)];
+    const int tok = fm_global_row(row, a);
+    rsc[q] = tok < 0 ? 0.0f : a.rowscale[tok];
   }
 #pragma unroll
   for (int h = 0; h < TM; ++h) {

@@ -9,7 +9,10 @@
 
 namespace slh {
 
-__global__ __launch_bounds__(256) void k_simhash(const double* __restrict__ Z,
+// GRP: Z holds the rows of the window's groups, and the token's row is formed
+// from its group's and the orthogonal part's (ldz rows per window).
+template <bool GRP>
+__global__ __launch_bounds__(256) void k_simhash(const double* __restrict__ Z, int ldz, GroupWS grp,
                                                  const double* __restrict__ R,
                                                  const int* __restrict__ winlist, int L, int r,
                                                  int bits, uint32_t* __restrict__ codes,
@@ -25,8 +28,17 @@ __global__ __launch_bounds__(256) void k_simhash(const double* __restrict__ Z,
   const int i = (blockIdx.x * 4 + wave) * 4 + q;   // token within the window
   double p = 0.0;
   if (i < L) {
-    const double* z = Z + ((int64_t)a * L + i) * r;
-    for (int c = 0; c < r; ++c) p = fma(z[c], sR[c * 16 + l], p);
+    if constexpr (GRP) {
+      const int64_t o = (int64_t)a * L;
+      const int g = grp.gid[o + i], n = grp.n_dev[a];
+      const double sg = grp.isq[o + g], sx = grp.isq[o + n] * grp.xc[o + i];
+      const double* z = Z + ((int64_t)a * ldz + g) * r;
+      const double* zx = Z + ((int64_t)a * ldz + n) * r;
+      for (int c = 0; c < r; ++c) p = fma(fma(sg, z[c], sx * zx[c]), sR[c * 16 + l], p);
+    } else {
+      const double* z = Z + ((int64_t)a * L + i) * r;
+      for (int c = 0; c < r; ++c) p = fma(z[c], sR[c * 16 + l], p);
+    }
   }
   const unsigned long long m = __ballot(i < L && l < bits && p > 0.0);
   if (i < L) {
@@ -43,13 +55,17 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
     p[i] = v;
 }
 
-hipError_t launch_simhash(const double* Z, const double* R, const int* winlist, int n_act,
-                          int L, int r, int bits, uint32_t* codes, double* proj,
-                          hipStream_t s) {
+hipError_t launch_simhash(const double* Z, int ldz, const GroupWS* grp, const double* R,
+                          const int* winlist, int n_act, int L, int r, int bits, uint32_t* codes,
+                          double* proj, hipStream_t s) {
   (void)hipGetLastError();
   const int blocks = (L + 15) / 16;
-  hipLaunchKernelGGL(k_simhash, dim3(blocks, n_act), dim3(256), 0, s, Z, R, winlist, L, r, bits,
-                     codes, proj);
+  if (grp)
+    hipLaunchKernelGGL(k_simhash<true>, dim3(blocks, n_act), dim3(256), 0, s, Z, ldz, *grp, R, winlist,
+                       L, r, bits, codes, proj);
+  else
+    hipLaunchKernelGGL(k_simhash<false>, dim3(blocks, n_act), dim3(256), 0, s, Z, ldz, GroupWS{}, R,
+                       winlist, L, r, bits, codes, proj);
   return hipGetLastError();
 }
 

@@ -223,7 +223,7 @@ __device__ __forceinline__ void lz_store_colsums(const LanczosWS& w, int a, int 
 
 // Initial pass: partials of Phi^T q_0 (t_0 before reduction), over the same row
 // groups as the step's pass.
-template <int RPW>
+template <int RPW, bool WT>
 __global__ __launch_bounds__(512) void k_lz_init(LanczosWS w) {
   constexpr int WPS = LZ_RC / RPW;
   const int a = blockIdx.y, g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
@@ -238,7 +238,9 @@ __global__ __launch_bounds__(512) void k_lz_init(LanczosWS w) {
   double col[4] = {0.0, 0.0, 0.0, 0.0};
   for (int c = 0; c < nch; ++c) {
     const int rc0 = r0 + LZ_RC * c;
-    const double z = q0[min(rc0 + (tid & (LZ_RC - 1)), L - 1)];
+    const int irc = min(rc0 + (tid & (LZ_RC - 1)), L - 1);
+    double z = q0[irc];
+    if constexpr (WT) z *= w.wt[a * w.ldr + irc];
     float4 v[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) v[i] = *(const float4*)(pbase + (int64_t)min(rc0 + prow + i, L - 1) * m);
@@ -284,11 +286,11 @@ __global__ __launch_bounds__(512) void k_lz_init(LanczosWS w) {
 // dry = 1 (timing replays): q_j and z1 go to Zs, no bookkeeping, no breakdown exit.
 // Dynamic LDS: 16 m floats (the staged chunk) when NCH > 1, else none.
 // ---------------------------------------------------------------------------
-// STAGED: blocks of NCH > 1 chunks (else NCH = 1, no LDS staging and a smaller
+// WT: rows weighted by w.wt.  STAGED: blocks of NCH > 1 chunks (else NCH = 1, no LDS staging and a smaller
 // register footprint, two blocks per CU).
 // Unstaged: at most 128 VGPRs (four waves per SIMD), so that two blocks share a
 // CU and all of the pass's blocks are resident at once.
-template <int RPW, int MAXT, bool STAGED>
+template <int RPW, int MAXT, bool STAGED, bool WT>
 __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, int j, int dry) {
   constexpr int RC = LZ_RC, WPS = RC / RPW, KG = 512 / RC;
   extern __shared__ float4 phis[];             // [RC][m / 4] staged chunk
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
   __builtin_amdgcn_sched_barrier(0);
   // a chunk's loads: Q[k][row] for k = kg + KG t < j, z1 and q_{j-1} of the
   // thread's row, the wave's Phi rows
-  double qv[MAXT], zp, qp;
+  double qv[MAXT], zp, qp, wr = 1.0;
   float4 v[RPW];
   auto load_chunk = [&](int c) {
     const int rc0 = r0 + RC * c;
@@ -339,6 +341,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
 #pragma unroll
     for (int t = 0; t < MAXT; ++t) qv[t] = Qa[(int64_t)min(kg + KG * t, jm) * L + irc];
     zp = w.Z1[(int64_t)a * L + irc];
+    if constexpr (WT) wr = w.wt[a * w.ldr + irc];
     qp = Qa[(int64_t)jm * L + irc];            // q_{j-1}, or q_0 when j = 0
 #pragma unroll
     for (int i = 0; i < RPW; ++i) v[i] = *(const float4*)(pbase + (int64_t)min(rc0 + prow + i, L - 1) * m);
@@ -348,7 +351,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
   __shared__ double h2s[264], gs[264];
   __shared__ double rq[KG][RC + 1], rg[KG][RC + 1];
   __shared__ double pr[RC][9];
-  __shared__ double zs[RC];
+  __shared__ double zs[RC], zws[WT ? RC : 1];
   __shared__ double cr[WPS > 1 ? 7 : 1][256];
   // g = T_{j-1} h2 (alpha_i on the diagonal, beta_i beside it; beta_{j-1} is
   // not part of T_{j-1}) from the loaded neighbours; |t~|^2 (alpha~), |h2|^2 and
@@ -464,16 +467,18 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
     }
   };
   // z1 of the thread's row (threads < RC), stored, into zs
-  auto row_z = [&](int ir, double sub_g, double q, double qm) {
+  auto row_z = [&](int ir, double sub_g, double q, double qm, double wrc) {
     double z = 0.0;
     if (ir < L) {
       double u = 0.0;
       for (int s2 = 0; s2 < (m >> 8); ++s2) u += pr[rl][s2];
+      if constexpr (WT) u *= wrc;
       if (j > 0) u = (fma(zn, u, -sub_g) - beta * h2last * q) / beta;
       z = (u - alpha * q) - beta * qm;
       zdst[ir] = z;
     }
     zs[rl] = z;
+    if constexpr (WT) zws[rl] = wrc * z;
     qz = fma(q, z, qz);
     zz = fma(z, z, zz);
   };
@@ -482,7 +487,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
     if (gm.rows) {
 #pragma unroll
       for (int i = i0; i < i1; ++i) {
-        const double zr = zs[gm.p * RPW + i];
+        const double zr = WT ? zws[gm.p * RPW + i] : zs[gm.p * RPW + i];
         const float4 x = from_lds ? phis[(gm.p * RPW + i) * m4 + gm.sl * 64 + lane] : pin_row(v[i]);
         col[0] = fma((double)x.x, zr, col[0]);
         col[1] = fma((double)x.y, zr, col[1]);
@@ -510,7 +515,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
     double qvc[MAXT];
 #pragma unroll
     for (int t = 0; t < MAXT; ++t) qvc[t] = qv[t];
-    const double zpc = zp, qpc = qp;
+    const double zpc = zp, qpc = qp, wrc = wr;
     // Staged: q_j and the k-group sums before the row dots (they need only the
     // prologue, so this barrier falls while the chunk's Phi rows are in flight).
     // Unstaged they follow the dots (taken before, they cost the 128-VGPR
@@ -528,7 +533,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
       }
       load_chunk(c + 1);
       __syncthreads();
-      if (tid < RC) row_z(ir, sub_g, q, qm);
+      if (tid < RC) row_z(ir, sub_g, q, qm, wrc);
       __syncthreads();
       colsums(0, RPW, true);
     } else {
@@ -536,7 +541,7 @@ __global__ __launch_bounds__(512, STAGED ? 2 : 4) void k_lz_step(LanczosWS w, in
       // the second half arrives, measured slower: 19.7 against 18.5 us at qwen7b)
       dots(0, RPW);
       __syncthreads();
-      if (tid < RC) row_z(ir, sub_g, q, qm);
+      if (tid < RC) row_z(ir, sub_g, q, qm, wrc);
       __syncthreads();
       colsums(0, RPW, false);
     }
@@ -675,7 +680,7 @@ __global__ __launch_bounds__(256) void k_lz_last_beta(LanczosWS w) {
 __global__ void k_lz_start(LanczosWS w, const double* __restrict__ q1) {
   const int a = blockIdx.y;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < w.L; i += gridDim.x * 256)
-    w.Q[(int64_t)a * w.ldq * w.L + i] = q1[(int64_t)a * w.L + i];
+    w.Q[(int64_t)a * w.ldq * w.L + i] = q1[a * w.ldr + i];
   if (blockIdx.x == 0 && threadIdx.x < w.n_it) {
     w.alpha[(int64_t)a * w.n_it + threadIdx.x] = 0.0;
     w.beta[(int64_t)a * w.n_it + threadIdx.x] = 0.0;
@@ -694,7 +699,8 @@ static int step_rpw(int m) { return LZ_RC / (8 / (m >> 8)); }
 
 template <int RPW>
 static void launch_init_t(const LanczosWS& w, hipStream_t s) {
-  hipLaunchKernelGGL(k_lz_init<RPW>, dim3(w.G3, w.n_act), dim3(512), 0, s, w);
+  if (w.wt) hipLaunchKernelGGL((k_lz_init<RPW, true>), dim3(w.G3, w.n_act), dim3(512), 0, s, w);
+  else hipLaunchKernelGGL((k_lz_init<RPW, false>), dim3(w.G3, w.n_act), dim3(512), 0, s, w);
 }
 static void launch_init(const LanczosWS& w, hipStream_t s) {
   switch (step_rpw(w.m)) {
@@ -705,11 +711,11 @@ static void launch_init(const LanczosWS& w, hipStream_t s) {
   }
 }
 
-template <int RPW, int MAXT, bool STAGED>
+template <int RPW, int MAXT, bool STAGED, bool WT>
 static hipError_t launch_step_s(const LanczosWS& w, int j, int dry, hipStream_t s, hipEvent_t e0,
                                 hipEvent_t e1) {
   const dim3 g(w.G3, w.n_act), b(512);
-  auto k = k_lz_step<RPW, MAXT, STAGED>;
+  auto k = k_lz_step<RPW, MAXT, STAGED, WT>;
   const size_t lds = STAGED ? (size_t)LZ_RC * w.m * sizeof(float) : 0;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -723,8 +729,11 @@ static hipError_t launch_step_s(const LanczosWS& w, int j, int dry, hipStream_t 
 template <int RPW, int MAXT>
 static hipError_t launch_step_t(const LanczosWS& w, int j, int dry, hipStream_t s, hipEvent_t e0,
                                 hipEvent_t e1) {
-  if (w.NCH > 1) return launch_step_s<RPW, MAXT, true>(w, j, dry, s, e0, e1);
-  return launch_step_s<RPW, MAXT, false>(w, j, dry, s, e0, e1);
+  if (w.wt)
+    return w.NCH > 1 ? launch_step_s<RPW, MAXT, true, true>(w, j, dry, s, e0, e1)
+                     : launch_step_s<RPW, MAXT, false, true>(w, j, dry, s, e0, e1);
+  return w.NCH > 1 ? launch_step_s<RPW, MAXT, true, false>(w, j, dry, s, e0, e1)
+                   : launch_step_s<RPW, MAXT, false, false>(w, j, dry, s, e0, e1);
 }
 // MAXT: the smallest slot count with 32 MAXT >= n_it
 template <int RPW>

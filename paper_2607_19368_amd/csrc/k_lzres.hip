@@ -253,8 +253,8 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
   }
   if (tid == 0) bad = 0;
   if (tid < RB) {
-    const double q = (r0 + tid < L) ? q1[(int64_t)a * L + r0 + tid] : 0.0;
-    const double wr = (w.wt && r0 + tid < L) ? w.wt[(int64_t)a * L + r0 + tid] : 1.0;
+    const double q = (r0 + tid < L) ? q1[a * w.ldr + r0 + tid] : 0.0;
+    const double wr = (w.wt && r0 + tid < L) ? w.wt[a * w.ldr + r0 + tid] : 1.0;
     Qs[tid] = q;
     zs[tid] = q;
     zw[tid] = wr * q;
@@ -591,7 +591,7 @@ __global__ void k_lz_res_prep(LanczosWS w, const double* __restrict__ q1, ResCle
   const int64_t st = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = t0; i < (int64_t)w.n_act * w.L; i += st) {
     const int64_t a = i / w.L;
-    w.Q[a * w.ldq * w.L + i - a * w.L] = q1[i];
+    w.Q[a * w.ldq * w.L + i - a * w.L] = q1[a * w.ldr + i - a * w.L];
   }
   for (int64_t i = t0; i < (int64_t)w.n_act * w.n_it; i += st) {
     w.alpha[i] = 0.0;

@@ -18,8 +18,11 @@
 namespace slh {
 
 // part[a][g][col] = sum of Phi[a][r][col] over rows r of group g (NR rows).
-__global__ __launch_bounds__(256) void k_nm_colsum(const float* __restrict__ Phi, int L, int m,
-                                                   int NR, double* __restrict__ part) {
+// Row r counts wt[r]^2 times when wt is given (a group of equal rows).
+template <bool WT>
+__global__ __launch_bounds__(256) void k_nm_colsum(const float* __restrict__ Phi,
+                                                   const double* __restrict__ wt, int64_t ldr, int L,
+                                                   int m, int NR, double* __restrict__ part) {
   const int sl = blockIdx.x, g = blockIdx.y, a = blockIdx.z, tid = threadIdx.x;
   const int G = gridDim.y;
   const int col = sl * 256 + tid;
@@ -32,7 +35,14 @@ __global__ __launch_bounds__(256) void k_nm_colsum(const float* __restrict__ Phi
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = P[(int64_t)min(r + e, r1 - 1) * m];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += (r + e < r1) ? (double)v[e] : 0.0;
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (WT) {
+        const double w = wt[a * ldr + min(r + e, r1 - 1)];
+        acc[e] += (r + e < r1) ? w * w * (double)v[e] : 0.0;
+      } else {
+        acc[e] += (r + e < r1) ? (double)v[e] : 0.0;
+      }
+    }
   }
   part[((int64_t)a * G + g) * m + col] =
       ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
@@ -101,13 +111,14 @@ int normalise_groups(int n_act, int L, int m, int n_cu) {
   return std::max(1, std::min(G, (L + 7) / 8));
 }
 
-hipError_t launch_normalise(float* Phi, int n_act, int L, int m, int G, double* part, double* csum,
-                            double* s_out, hipStream_t s) {
+hipError_t launch_normalise(float* Phi, const double* wt, int64_t ldr, int n_act, int L, int m, int G,
+                            double* part, double* csum, double* s_out, hipStream_t s) {
   (void)hipGetLastError();
   if (n_act <= 0 || m % 256 != 0 || G < 1) return n_act <= 0 ? hipSuccess : hipErrorInvalidValue;
   const int NR = (((L + G - 1) / G) + 7) / 8 * 8;
   const int Gr = (L + NR - 1) / NR;              // groups that hold rows
-  hipLaunchKernelGGL(k_nm_colsum, dim3(m / 256, Gr, n_act), dim3(256), 0, s, Phi, L, m, NR, part);
+  if (wt) hipLaunchKernelGGL(k_nm_colsum<true>, dim3(m / 256, Gr, n_act), dim3(256), 0, s, Phi, wt, ldr, L, m, NR, part);
+  else hipLaunchKernelGGL(k_nm_colsum<false>, dim3(m / 256, Gr, n_act), dim3(256), 0, s, Phi, wt, ldr, L, m, NR, part);
   hipLaunchKernelGGL(k_nm_colreduce, dim3(m / 256, n_act), dim3(256), 0, s, part, Gr, m, csum);
   hipLaunchKernelGGL(k_nm_rowscale, dim3((L + 3) / 4, n_act), dim3(256), 0, s, Phi, csum, L, m,
                      s_out);

@@ -163,6 +163,16 @@ struct slh_ctx {
   DevBuf dg_tiles, dg_counts;
   DevBuf posv, mg_pre;
   DevBuf nm_part, nm_csum, rowsum;
+  // Distinct rows (k_group.hip): two sets, so that the groups behind Q and Z stay
+  // while the next prompt's feature map makes its own.
+  int distinct = 1;                 // SLH_OPT_DISTINCT
+  DevBuf grpA, grpB, xpand;
+  GroupWS grp[2] = {};
+  int* grp_pin = nullptr;           // pinned: group counts, then the differ word
+  int grp_pin_n = 0;
+  int phi_g = -1, q_g = -1, row_g = -1;   // set behind Phi, behind Q and Z, behind rowsum (-1: every row)
+  int64_t Lphi = 0, Lq = 0;         // rows per window of Phi, of Q and Z
+  const double* lz_q1 = nullptr;    // start vectors of the last Lanczos run
   DevBuf dg_rowsq, dg_energy;
 
   // timing (SLH_OPT_TIMING)
@@ -353,6 +363,87 @@ void route_all_spectral(slh_ctx* c) {
   c->routing_on_device = false;
 }
 
+// start vectors of every window (Philox stream 3), drawn once per window length
+int ensure_q1(slh_ctx* c) {
+  const int64_t L = window_len(c);
+  if (c->q1_L == L) return SLH_OK;
+  ENSURE(c, c->q1all, (size_t)c->N * sizeof(double));
+  std::vector<double> q((size_t)c->N);
+  for (int64_t w = 0; w < c->n_win; ++w) slh_gen_start(c->seed, w, L, q.data() + w * L);
+  HIP_TRY(c, hipMemcpy(c->q1all.p, q.data(), q.size() * sizeof(double), hipMemcpyHostToDevice));
+  c->q1_L = L;
+  return SLH_OK;
+}
+
+// Below this many entries of Phi (8 MB) the spectral step is bound by latency,
+// whatever the rows (3001 x 256: 218 us a prompt, of which equal rows could save
+// 25, and finding them takes 35).
+constexpr int64_t GROUP_MIN_PHI = (int64_t)1 << 21;
+
+// Groups the equal rows of each active window of a bf16 X (fp32 X holds hidden
+// states, where no two rows agree).  Sets phi_g and Lphi: the groups are taken
+// where they leave at most 7/8 of the rows.  Waits for the stream (the host sizes
+// the feature map and Lanczos by the count), so not under stream capture.
+int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
+  const int64_t L = window_len(c);
+  const int na = c->n_act;
+  c->phi_g = -1;
+  c->Lphi = L;
+  if (!c->distinct || dtype != SLH_BF16 || na < 1 || L <= 32 || L > GROUP_L_MAX ||
+      na * L * c->m < GROUP_MIN_PHI || c->N > 0x7FFFFFFF)
+    return SLH_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return SLH_OK;
+  }
+  int rc = ensure_q1(c);
+  if (rc) return rc;
+  if (c->grp_pin_n < na + 1) {
+    if (c->grp_pin) (void)hipHostFree(c->grp_pin);
+    c->grp_pin = nullptr;
+    c->grp_pin_n = 0;
+    if (hipHostMalloc((void**)&c->grp_pin, (size_t)(na + 1) * sizeof(int), hipHostMallocDefault) !=
+        hipSuccess) {
+      c->grp_pin = nullptr;
+      return fail(c, SLH_ENOMEM, "hipHostMalloc(%zu)", (size_t)(na + 1) * sizeof(int));
+    }
+    c->grp_pin_n = na + 1;
+  }
+  const int set = c->q_g == 0 ? 1 : 0;
+  DevBuf& buf = set ? c->grpB : c->grpA;
+  const size_t n = (size_t)na * L;
+  ENSURE(c, buf, n * 48 + (size_t)na * 4);
+  GroupWS& w = c->grp[set];
+  w.n_act = na;
+  w.L = (int)L;
+  w.winlist = na == c->n_win ? nullptr : P<int>(c->winlist);
+  w.q1 = P<double>(c->q1all);
+  char* p = (char*)buf.p;
+  w.hash = (unsigned long long*)p;
+  w.wt = (double*)(p + 8 * n);
+  w.isq = (double*)(p + 16 * n);
+  w.q = (double*)(p + 24 * n);
+  w.xc = (double*)(p + 32 * n);
+  w.gid = (int*)(p + 40 * n);
+  w.rowsrc = (int*)(p + 44 * n);
+  w.n_dev = (int*)(p + 48 * n);
+  w.n_out = c->grp_pin;
+  w.differ = c->grp_pin + na;
+  *w.differ = 0;                    // the last prompt's kernels are done: this call waited for them
+  HIP_TRY(c, launch_group(w, (const uint16_t*)X, ldx, (int)c->D, c->stream));
+  if ((rc = wait_stream(c))) return rc;
+  int most = 0;
+  for (int a = 0; a < na; ++a) {
+    if (w.n_out[a] < 0) return SLH_OK;
+    most = std::max(most, w.n_out[a]);
+  }
+  if (*w.differ || 8 * (int64_t)(most + 1) > 7 * L) return SLH_OK;
+  c->phi_g = set;
+  c->Lphi = most + 1;
+  return SLH_OK;
+}
+
 // Exact target length: the spectral windows share B = target - (chunk-window
 // macro-tokens) - (preserved tokens), floor(B / n) each and one more for the
 // first B mod n (window order).  Returns false if some budget would leave [1, L].
@@ -526,7 +617,7 @@ void slh_destroy(slh_ctx* c) {
                     &c->Mtot, &c->part, &c->part_seg, &c->part_cnt, &c->part_nsum,
                     &c->part_end, &c->rpart, &c->scores, &c->rsu, &c->lz_bar, &c->nm_part, &c->nm_csum, &c->rowsum, &c->dg_counts,
                     &c->dg_energy, &c->dg_rowsq, &c->dg_tiles, &c->mg_pre, &c->posv, &c->tg_scr,
-                    &c->tg_tw};
+                    &c->tg_tw, &c->grpA, &c->grpB, &c->xpand};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -535,6 +626,7 @@ void slh_destroy(slh_ctx* c) {
   for (auto& e : c->mq_ev)
     if (e) (void)hipEventDestroy(e);
   if (c->mq_pin) (void)hipHostFree(c->mq_pin);
+  if (c->grp_pin) (void)hipHostFree(c->grp_pin);
 
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
@@ -619,6 +711,10 @@ int slh_set_option(slh_ctx* c, int32_t key, double v) {
       if (v != 0.0 && v != 1.0) return fail(c, SLH_EINVAL, "RESIDENT must be 0 or 1");
       c->resident = (int)v;
       break;
+    case SLH_OPT_DISTINCT:
+      if (v != 0.0 && v != 1.0) return fail(c, SLH_EINVAL, "DISTINCT must be 0 or 1");
+      c->distinct = (int)v;
+      break;
     case SLH_OPT_WAIT_POLLS:
       if (!(v >= 0.0 && v <= 2147483647.0) || v != (double)(int)v)
         return fail(c, SLH_EINVAL, "WAIT_POLLS must be an integer in [0, 2^31)");
@@ -640,6 +736,7 @@ int slh_set_stream(slh_ctx* c, void* s) {
 
 int64_t slh_num_windows(const slh_ctx* c) { return c ? c->n_win : 0; }
 int64_t slh_num_spectral(const slh_ctx* c) { return c ? c->n_act : 0; }
+int64_t slh_operator_rows(const slh_ctx* c) { return c ? c->Lphi : 0; }
 int64_t slh_merge_capacity(const slh_ctx* c) { return c ? capacity(c) : 0; }
 
 int slh_route(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, double rho, double tau,
@@ -725,10 +822,14 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   if (!(c->norms_fresh && norms_match(c, X, dtype, ldx)))
     if ((rc = prep_norms(c, X, dtype, ldx))) return rc;
   c->norms_fresh = false;
-  const int64_t L = window_len(c);
+  if ((rc = group_rows(c, X, dtype, ldx))) return rc;
+  const GroupWS* grp = c->phi_g >= 0 ? &c->grp[c->phi_g] : nullptr;
+  const int64_t L = c->Lphi;        // rows per window
   const int64_t rows = (int64_t)c->n_act * L;
   ENSURE(c, c->Phi, (size_t)std::max<int64_t>(rows, 1) * c->m * sizeof(float));
   FeatmapArgs a;
+  a.rowsrc = grp ? grp->rowsrc : nullptr;
+  a.ldr = window_len(c);
   a.X = dtype == SLH_F32 ? P<uint16_t>(c->Xb) : (const uint16_t*)X;
   a.ldx = dtype == SLH_F32 ? c->D : ldx;
   a.Wt = P<uint16_t>(c->Wt);
@@ -749,7 +850,8 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
     ENSURE(c, c->nm_csum, (size_t)c->n_act * c->m * 8);
     ENSURE(c, c->rowsum, (size_t)rows * 8);
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[9], c->stream));
-    HIP_TRY(c, launch_normalise(P<float>(c->Phi), c->n_act, (int)L, (int)c->m, G,
+    c->row_g = c->phi_g;
+    HIP_TRY(c, launch_normalise(P<float>(c->Phi), grp ? grp->wt : nullptr, window_len(c), c->n_act, (int)L, (int)c->m, G,
                                 P<double>(c->nm_part), P<double>(c->nm_csum),
                                 P<double>(c->rowsum), c->stream));
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[10], c->stream));
@@ -770,21 +872,24 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
   const int na = c->n_act;
   c->n_it = n_it;
   if (na > 0) {
-    // start vectors of the spectral windows
-    if (c->q1_L != L) {
-      ENSURE(c, c->q1all, (size_t)c->N * sizeof(double));
-      std::vector<double> q((size_t)c->N);
-      for (int64_t w = 0; w < c->n_win; ++w) slh_gen_start(c->seed, w, L, q.data() + w * L);
-      HIP_TRY(c, hipMemcpy(c->q1all.p, q.data(), q.size() * sizeof(double), hipMemcpyHostToDevice));
-      c->q1_L = L;
-    }
-    const double* q1act = P<double>(c->q1all);
-    if (na != c->n_win) {
+    // start vectors of the spectral windows (of their groups where rows are grouped)
+    int rc = ensure_q1(c);
+    if (rc) return rc;
+    const GroupWS* grp = c->phi_g >= 0 ? &c->grp[c->phi_g] : nullptr;
+    const double* q1act = grp ? grp->q : P<double>(c->q1all);
+    if (!grp && na != c->n_win) {
       ENSURE(c, c->q1act, (size_t)na * L * sizeof(double));
       HIP_TRY(c, launch_gather_windows(P<double>(c->q1act), P<double>(c->q1all), P<int>(c->winlist),
                                        L, na, c->stream));
       q1act = P<double>(c->q1act);
     }
+    if (!c->Phi.p || (int64_t)c->Phi.bytes < na * c->Lphi * c->m * 4 ||
+        (grp ? grp->L != L || grp->n_act != na : c->Lphi != L))
+      return fail(c, SLH_ESTATE, "slh_lanczos before slh_feature_map");
+    c->q_g = c->phi_g;
+    c->Lq = c->Lphi;
+    c->lz_q1 = q1act;
+    const int64_t Lr = c->Lq;       // rows per window of the operator
     if (c->short_win && local_supported((int)L, n_it, c->r)) {
       // short windows: Lanczos, Eigh and Ritz of each window in one wavefront
       ENSURE(c, c->Q, (size_t)na * (n_it + 1) * L * 8);
@@ -809,7 +914,9 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       LanczosWS w;
       memset(&w, 0, sizeof w);      // the graph key compares the bytes
       w.n_act = na;
-      w.L = (int)L;
+      w.L = (int)Lr;
+      w.wt = grp ? grp->wt : nullptr;
+      w.ldr = L;
       w.m = (int)c->m;
       w.n_it = n_it;
       w.ldq = n_it + 1;
@@ -821,22 +928,22 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       // current one staged in LDS, 16 m floats, so such a block runs alone on
       // its CU)
       {
-        const int64_t chunks = (int64_t)na * ((L + 15) / 16);
+        const int64_t chunks = (int64_t)na * ((Lr + 15) / 16);
         const int64_t ncu = std::max(1, c->n_cu);
         w.NCH = chunks <= 2 * ncu ? 1 : (int)((chunks + ncu - 1) / ncu);
-        w.G3 = (int)((L + 16 * w.NCH - 1) / (16 * w.NCH));
+        w.G3 = (int)((Lr + 16 * w.NCH - 1) / (16 * w.NCH));
       }
       // the resident kernel where every window's Phi fits in the register files
       const int res_nb = c->resident ? lanczos_resident_blocks(w, c->n_cu) : 0;
       const bool res = res_nb > 0;
       const size_t grp = std::max(w.G3, res_nb);   // row groups of the partials
       const size_t hs = (size_t)w.ldq + 1;
-      ENSURE(c, c->Q, (size_t)na * w.ldq * L * 8);
+      ENSURE(c, c->Q, (size_t)na * w.ldq * Lr * 8);
       ENSURE(c, c->T, (size_t)na * w.ldq * c->m * 8);
       ENSURE(c, c->Apart, (size_t)na * (c->m / 16) * 8);   // |t|^2 partials
-      ENSURE(c, c->Z1, (size_t)na * L * 8);
+      ENSURE(c, c->Z1, (size_t)na * Lr * 8);
       ENSURE(c, c->Spart, na * grp * c->m * 8);
-      ENSURE(c, c->Zs, (size_t)na * 2 * L * 8);
+      ENSURE(c, c->Zs, (size_t)na * 2 * Lr * 8);
       ENSURE(c, c->H2part, na * grp * hs * 8);
       ENSURE(c, c->H2, (size_t)na * hs * 8);
       ENSURE(c, c->alpha, (size_t)na * n_it * 8);
@@ -846,7 +953,7 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       ENSURE(c, c->amax, (size_t)na * 2 * 8);
       ENSURE(c, c->theta, (size_t)na * c->r * 8);
       ENSURE(c, c->Seig, (size_t)na * n_it * c->r * 8);
-      ENSURE(c, c->Z, (size_t)na * L * c->r * 8);
+      ENSURE(c, c->Z, (size_t)na * Lr * c->r * 8);
       w.Phi = P<float>(c->Phi);
       w.Q = P<double>(c->Q);
       w.T = P<double>(c->T);
@@ -875,16 +982,20 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
           HIP_TRY(c, launch_lanczos(w, q1act, c->stream, c->ev_fb.data(), c->ev_fa.data()));
         HIP_TRY(c, hipEventRecord(c->ev[3], c->stream));
         HIP_TRY(c, launch_eigh_ritz(w.alpha, w.beta, w.neff, na, n_it, c->r, P<double>(c->theta),
-                                    P<double>(c->Seig), w.Q, (int)L, w.ldq, P<double>(c->Z),
+                                    P<double>(c->Seig), w.Q, w.L, w.ldq, P<double>(c->Z),
                                     c->n_cu, c->stream));
         HIP_TRY(c, hipEventRecord(c->ev[4], c->stream));
-      } else if (res) {
+      } else if (res || grp) {
         // the resident path is four kernels, launched directly: the end of a
-        // graph costs a gap before the stream's next kernel
-        HIP_TRY(c, launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
-                                           nullptr, nullptr));
+        // graph costs a gap before the stream's next kernel.  Grouped rows: their
+        // number is the prompt's own, so a graph would be captured for every one.
+        if (res)
+          HIP_TRY(c, launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
+                                             nullptr, nullptr));
+        else
+          HIP_TRY(c, launch_lanczos(w, q1act, c->stream));
         HIP_TRY(c, launch_eigh_ritz(w.alpha, w.beta, w.neff, na, n_it, c->r, P<double>(c->theta),
-                                    P<double>(c->Seig), w.Q, (int)L, w.ldq, P<double>(c->Z),
+                                    P<double>(c->Seig), w.Q, w.L, w.ldq, P<double>(c->Z),
                                     c->n_cu, c->stream));
       } else {
         // The step sequence, Eigh(T) and the Ritz coordinates are captured once
@@ -949,7 +1060,7 @@ int slh_eigh_ritz(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out
     return fail(c, SLH_ESTATE, "slh_eigh_ritz needs slh_lanczos or slh_load of alpha, beta and Q");
   if (n_it != c->n_it)
     return fail(c, SLH_EINVAL, "n_it %d differs from the tridiagonal's order %d", n_it, c->n_it);
-  const int64_t L = window_len(c);
+  const int64_t L = c->Lq;          // rows per window of Q
   const int na = c->n_act;
   if (na > 0) {
     ENSURE(c, c->theta, (size_t)na * c->r * 8);
@@ -984,7 +1095,8 @@ int slh_simhash(slh_ctx* c, uint32_t* codes_out) {
   if (na != c->n_win || c->keep_last)
     HIP_TRY(c, launch_fill_u32(P<uint32_t>(c->codes), c->Ntot, 0xFFFFFFFFu, c->stream));
   if (na > 0)
-    HIP_TRY(c, launch_simhash(P<double>(c->Z), P<double>(c->R),
+    HIP_TRY(c, launch_simhash(P<double>(c->Z), (int)c->Lq, c->q_g >= 0 ? &c->grp[c->q_g] : nullptr,
+                              P<double>(c->R),
                               na == c->n_win ? nullptr : P<int>(c->winlist), na, (int)L, c->r,
                               c->bits, P<uint32_t>(c->codes), P<double>(c->proj), c->stream));
   if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[6], c->stream));
@@ -1143,9 +1255,10 @@ int slh_spectral_energy(slh_ctx* c, double* out) {
   const int64_t L = window_len(c);
   const int na = c->n_act;
   if (na == 0) return SLH_OK;
-  ENSURE(c, c->dg_rowsq, (size_t)na * L * 8);
+  ENSURE(c, c->dg_rowsq, (size_t)na * c->Lphi * 8);
   ENSURE(c, c->dg_energy, (size_t)na * 8);
-  HIP_TRY(c, launch_energy(P<float>(c->Phi), P<double>(c->theta), na, (int)L, (int)c->m, c->r,
+  HIP_TRY(c, launch_energy(P<float>(c->Phi), c->phi_g >= 0 ? c->grp[c->phi_g].wt : nullptr, L,
+                           P<double>(c->theta), na, (int)c->Lphi, (int)c->m, c->r,
                            P<double>(c->dg_rowsq), P<double>(c->dg_energy), c->stream));
   HIP_TRY(c, hipMemcpyAsync(out, c->dg_energy.p, (size_t)na * 8, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1245,7 +1358,7 @@ int slh_time_passes(slh_ctx* c, int32_t reps, double* us_out) {
   if (c->lz_res) {
     // the resident kernel: reps whole runs, each kernel between two events
     // (its preparation kernel outside them); us per Lanczos step
-    const double* q1act = (c->n_act != c->n_win) ? P<double>(c->q1act) : P<double>(c->q1all);
+    const double* q1act = c->lz_q1;
     hipEvent_t r0 = nullptr, r1 = nullptr;
     hipError_t e = hipEventCreate(&r0);
     if (e == hipSuccess) e = hipEventCreate(&r1);
@@ -1305,6 +1418,8 @@ int slh_load(slh_ctx* c, int32_t which, const void* src, int64_t bytes) {
     if (bytes != want) return fail(c, SLH_EINVAL, "bytes must be %lld", (long long)want);
     ENSURE(c, c->Phi, (size_t)std::max<int64_t>(want, 4));
     if (want) HIP_TRY(c, hipMemcpyAsync(c->Phi.p, src, (size_t)want, hipMemcpyDeviceToDevice, c->stream));
+    c->phi_g = -1;
+    c->Lphi = L;
     c->stage = 1;
     c->merged = 0;
     return SLH_OK;
@@ -1336,6 +1451,8 @@ int slh_load(slh_ctx* c, int32_t which, const void* src, int64_t bytes) {
     HIP_TRY(c, hipMemcpyAsync(c->neff.p, ne.data(), ne.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));     // ne leaves scope
     c->n_it = (int)n_it;
+    c->q_g = -1;
+    c->Lq = L;
     c->t_loaded = 1;
     c->lz_w_valid = false;
     c->lz_res = false;
@@ -1379,6 +1496,28 @@ int slh_copy_out(slh_ctx* c, int32_t which, void* dst, int64_t bytes) {
   }
   if (bytes != want) return fail(c, SLH_EINVAL, "bytes must be %lld", (long long)want);
   if (want == 0) return SLH_OK;
+  const int g = which == SLH_OUT_PHI ? c->phi_g
+                : which == SLH_OUT_ROWSUM ? c->row_g
+                : which == SLH_OUT_Q || which == SLH_OUT_Z ? c->q_g : -1;
+  if (g >= 0) {
+    // held for the groups of equal rows: formed for every row here
+    const GroupWS& w = c->grp[g];
+    const bool q = which == SLH_OUT_Q || which == SLH_OUT_Z;
+    const int64_t Lg = q ? c->Lq : c->Lphi, per = want / (na * L * 4);   // words a row
+    if (w.L != L || w.n_act != na || (which == SLH_OUT_ROWSUM && c->row_g != c->phi_g) || !b->p ||
+        (int64_t)b->bytes < na * Lg * per * 4)
+      return fail(c, SLH_ESTATE, "output %d not computed", which);
+    ENSURE(c, c->xpand, (size_t)want);
+    if (which == SLH_OUT_Z)
+      HIP_TRY(c, launch_group_expand(w, P<double>(c->Z), Lg * c->r, c->r, 1, c->r,
+                                     P<double>(c->xpand), L * c->r, c->r, 1, c->stream));
+    else if (which == SLH_OUT_Q)
+      HIP_TRY(c, launch_group_expand(w, P<double>(c->Q), Lg * (c->n_it + 1), 1, Lg, c->n_it + 1,
+                                     P<double>(c->xpand), L * (c->n_it + 1), 1, L, c->stream));
+    else
+      HIP_TRY(c, launch_group_copy(w, b->p, Lg * per, (int)per, c->xpand.p, c->stream));
+    b = &c->xpand;
+  }
   if (!b->p || (int64_t)b->bytes < want) return fail(c, SLH_ESTATE, "output %d not computed", which);
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   HIP_TRY(c, hipMemcpy(dst, b->p, (size_t)want, hipMemcpyDeviceToHost));

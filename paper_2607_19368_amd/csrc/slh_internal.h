@@ -18,6 +18,36 @@ hipError_t launch_rownorm(const void* X, int dtype, int64_t ldx, int64_t N, int 
 hipError_t launch_gather_windows(double* dst, const double* src, const int* winlist, int64_t L,
                                  int n_act, hipStream_t s);
 
+// ---- distinct rows (k_group.hip) ----
+// Per active window a of L rows: gid[a][i] = the group of row i, n_dev[a] groups
+// (-1: not grouped, nothing else is set), rowsrc[a][g] = the token that group g's
+// rows equal (~token for rows past the groups), wt = sqrt(count) (0 past the
+// groups), isq = 1 / wt (row n: 1 / norm of xc), q the start vector's
+// coordinates, xc each row's part of q_0 orthogonal to the groups.
+constexpr int GROUP_MAX = 12288;         // groups of a window, at most
+constexpr int GROUP_L_MAX = 131072;      // rows of a window, at most
+struct GroupWS {
+  int n_act, L;
+  const int* winlist;                    // active window -> window index (NULL: all)
+  const double* q1;                      // start vectors of all windows [n_win][L]
+  unsigned long long* hash;              // [n_act][L]
+  int* gid;                              // [n_act][L]
+  int* rowsrc;                           // [n_act][L]
+  double *wt, *isq, *q, *xc;             // [n_act][L]
+  int* n_dev;                            // [n_act]
+  int* n_out;                            // [n_act] host (pinned)
+  int* differ;                           // host (pinned): 1 when a row differs from its group
+};
+hipError_t launch_group(const GroupWS& w, const uint16_t* X, int64_t ldx, int D, hipStream_t s);
+// out[a][i * ors + e * oes] = isq_g src[a][g * rs + e * es] + xc_i / |xc| src[a][n * rs + e * es],
+// e < per, g = gid[a][i], n = n_dev[a]; windows of src and out ld_src, ld_out doubles apart
+hipError_t launch_group_expand(const GroupWS& w, const double* src, int64_t ld_src, int64_t rs,
+                               int64_t es, int per, double* out, int64_t ld_out, int64_t ors,
+                               int64_t oes, hipStream_t s);
+// out[a][i] = src[a][gid[a][i]], per 32-bit words a row
+hipError_t launch_group_copy(const GroupWS& w, const void* src, int64_t ld_src, int per, void* out,
+                             hipStream_t s);
+
 // ---- feature map (k_featmap.hip) ----
 struct FeatmapArgs {
   const uint16_t* X;      // bf16 rows, global token index, row stride ldx
@@ -29,6 +59,9 @@ struct FeatmapArgs {
   const int* winlist;     // active window -> window index (n_rows / L entries)
   int64_t n_rows;         // n_act * L
   int64_t L;
+  const int* rowsrc;      // distinct rows: row g of window a is token rowsrc[a ldr + g]
+                          //   (~token: a row of zeros); NULL: row i of winlist's window
+  int64_t ldr;
   int D, m;
   int ldw;                // D rounded up to a multiple of 64
 };
@@ -41,8 +74,9 @@ hipError_t launch_featmap(const FeatmapArgs& a, int n_cu, hipStream_t s, hipEven
 struct LanczosWS {
   int n_act, L, m, n_it, ldq;   // ldq = n_it + 1 vectors per window
   const float* Phi;             // [n_act][L][m]
-  const double* wt;             // [n_act][L] row weights: the operator is that of diag(wt) Phi
+  const double* wt;             // [n_act][ldr] row weights: the operator is that of diag(wt) Phi
                                 //   (NULL: all 1)
+  int64_t ldr;                  // rows from one window's start vector (and wt) to the next's
   double* Q;                    // [n_act][ldq][L]  Lanczos basis, vector-major
   double* T;                    // [n_act][ldq][m]  t_j = Phi^T z1 / |z1| of step j-1 in slot j & 1
   double* Apart;                // [n_act][m/16]    partials of |t_j|^2 (= alpha_j) per 16 columns
@@ -102,9 +136,10 @@ hipError_t launch_lanczos_resident(const LanczosWS& w, const double* q1_act, uns
 hipError_t launch_eigh_ritz(const double* alpha, const double* beta, const int* neff, int n_act,
                             int n_it, int r, double* theta, double* Seig, const double* Q, int L,
                             int ldq, double* Z, int n_cu, hipStream_t s);
-hipError_t launch_simhash(const double* Z, const double* R, const int* winlist, int n_act,
-                          int L, int r, int bits, uint32_t* codes, double* proj,
-                          hipStream_t s);
+// grp: Z holds ldz rows per window, of the groups (else NULL, and ldz = L)
+hipError_t launch_simhash(const double* Z, int ldz, const GroupWS* grp, const double* R,
+                          const int* winlist, int n_act, int L, int r, int bits, uint32_t* codes,
+                          double* proj, hipStream_t s);
 
 // ---- short windows (k_local.hip): Lanczos + Eigh + Ritz of each window in one
 // wavefront, on the window's explicit L x L operator (L <= 32, n_it <= L) ----
@@ -116,12 +151,15 @@ hipError_t launch_local(const float* Phi, int n_act, int m, int L, int n_it, int
 // ---- normalised operator (k_norm.hip): per window s = Phi (Phi^T 1), rows of
 // Phi scaled in place by s_i^-1/2 (0 where s_i <= 0); s kept in s_out ----
 int normalise_groups(int n_act, int L, int m, int n_cu);   // row groups G of the column sums
-hipError_t launch_normalise(float* Phi, int n_act, int L, int m, int G, double* part, double* csum,
-                            double* s_out, hipStream_t s);   // part: [n_act][G][m], csum: [n_act][m]
+// wt (may be NULL): row i stands for wt[a ldr + i]^2 equal rows
+hipError_t launch_normalise(float* Phi, const double* wt, int64_t ldr, int n_act, int L, int m, int G,
+                            double* part, double* csum, double* s_out,
+                            hipStream_t s);   // part: [n_act][G][m], csum: [n_act][m]
 
 // ---- diagnostics (k_diag.hip): per window sum(theta) / ||Phi_w||_F^2 ----
-hipError_t launch_energy(const float* Phi, const double* theta, int n_act, int L, int m, int r,
-                         double* rowsq, double* energy, hipStream_t s);   // rowsq: [n_act][L]
+hipError_t launch_energy(const float* Phi, const double* wt, int64_t ldr, const double* theta,
+                         int n_act, int L, int m, int r, double* rowsq, double* energy,
+                         hipStream_t s);   // rowsq: [n_act][L]; wt as in launch_normalise
 
 // bucket purity: tiles = ntiles (A, B) pairs of 64-position blocks of the sorted
 // member order; counts[0] += pairs with cos > thresh, counts[1] += pairs

@@ -18,7 +18,7 @@ SLH_OK, SLH_EINVAL, SLH_ENOMEM, SLH_EHIP, SLH_ESTATE = 0, -1, -2, -3, -4
 SLH_BF16, SLH_F32 = 0, 1
 SLH_OPT_KERNEL, SLH_OPT_WINDOW_LEN, SLH_OPT_POS_MODE, SLH_OPT_BREAKDOWN_TOL, SLH_OPT_TIMING = 1, 2, 3, 4, 5
 SLH_OPT_SHORT_WINDOWS, SLH_OPT_NORMALIZE, SLH_OPT_POS_SCHEME, SLH_OPT_KEEP_LAST = 6, 7, 8, 9
-SLH_OPT_TARGET_LEN, SLH_OPT_RESIDENT, SLH_OPT_WAIT_POLLS = 10, 11, 12
+SLH_OPT_TARGET_LEN, SLH_OPT_RESIDENT, SLH_OPT_WAIT_POLLS, SLH_OPT_DISTINCT = 10, 11, 12, 13
 SLH_OUT_PHI, SLH_OUT_ALPHA, SLH_OUT_BETA, SLH_OUT_Z = 1, 2, 3, 4
 SLH_OUT_PROJ, SLH_OUT_CODES, SLH_OUT_THETA, SLH_OUT_Q, SLH_OUT_WINDOWS = 5, 6, 7, 8, 9
 SLH_OUT_ROWSUM = 10
@@ -30,7 +30,7 @@ EXPORTS = [
     "slh_simhash", "slh_merge", "slh_merge_capacity", "slh_copy_out", "slh_num_windows",
     "slh_num_spectral", "slh_load", "slh_stage_times", "slh_time_passes", "slh_spectral_energy",
     "slh_bucket_purity", "slh_eigh_ritz", "slh_peak_read", "slh_peak_mfma", "slh_merge_noalloc",
-    "slh_merge_async", "slh_merge_wait",
+    "slh_merge_async", "slh_merge_wait", "slh_operator_rows",
 ]
 
 _lib = None
@@ -72,6 +72,7 @@ def load():
         "slh_copy_out": (i32, [vp, i32, vp, i64]),
         "slh_num_windows": (i64, [vp]),
         "slh_num_spectral": (i64, [vp]),
+        "slh_operator_rows": (i64, [vp]),
         "slh_load": (i32, [vp, i32, vp, i64]),
         "slh_spectral_energy": (i32, [vp, vp]),
         "slh_bucket_purity": (i32, [vp, vp, i32, i64, ctypes.c_double, vp]),
@@ -129,6 +130,11 @@ class Ctx:
     @property
     def n_windows(self):
         return int(load().slh_num_windows(self.handle))
+
+    @property
+    def operator_rows(self):
+        """Rows per spectral window that the last feature map computed."""
+        return int(load().slh_operator_rows(self.handle))
 
     @property
     def n_spectral(self):

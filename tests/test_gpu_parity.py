@@ -432,6 +432,120 @@ def test_resident_shapes_match_streaming(N, m, n_it, window):
         assert da <= 1e-8 and db <= 1e-8
 
 
+# ------------------------------------------------------------------ distinct rows
+def _repeating_rows(N, D, distinct, seed):
+    """N bf16 rows that hold `distinct` different ones, a few of them very often."""
+    import torch
+    g = torch.Generator().manual_seed(seed)
+    table = (0.02 * torch.randn((distinct, D), generator=g)).bfloat16()
+    ids = (distinct * torch.rand(N, generator=g) ** 3).long().clamp_(max=distinct - 1)
+    ids[:distinct] = torch.randperm(distinct, generator=g)[:N]
+    return table[ids[torch.randperm(N, generator=g)]].cuda()
+
+
+def _spectral_run(X, m, n_it, r, bits, distinct, window=0, resident=1, normalise=0):
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    ctx = P.slh_create(X.shape[0], X.shape[1], m, r, bits, 0)
+    if window:
+        P.slh_set_option(ctx, B.SLH_OPT_WINDOW_LEN, window)
+    P.slh_set_option(ctx, B.SLH_OPT_DISTINCT, distinct)
+    P.slh_set_option(ctx, B.SLH_OPT_RESIDENT, resident)
+    P.slh_set_option(ctx, B.SLH_OPT_NORMALIZE, normalise)
+    P.slh_feature_map(ctx, X)
+    out = dict(rows=ctx.operator_rows, Phi=P.slh_copy_out(ctx, B.SLH_OUT_PHI))
+    if normalise:
+        out["rowsum"] = P.slh_copy_out(ctx, B.SLH_OUT_ROWSUM)
+    out["ritz"], out["iters"] = P.slh_lanczos(ctx, n_it)
+    out["energy"] = P.slh_spectral_energy(ctx)
+    P.slh_simhash(ctx)
+    for k in ("ALPHA", "Z", "PROJ", "Q", "CODES"):
+        out[k] = P.slh_copy_out(ctx, getattr(B, "SLH_OUT_" + k))
+    return out
+
+
+@pytest.mark.parametrize("case", ["one", "one_streaming", "windows", "normalised", "ragged", "wide"])
+def test_distinct_rows_match_every_row(case):
+    """The operator on the distinct rows against the operator on every row
+    (SLH_OPT_DISTINCT 0), the same in exact arithmetic: Phi bit for bit, the basis
+    and Ritz coordinates of every token, row sums and energy.  Both sides run the
+    same recurrence in fp64 with sums grouped differently, so alpha agrees to 1e-9
+    (1e-12 measured between the streaming and resident paths, n_it far below the
+    distinct rows) and Z, whose rows are of size 1, to 1e-8; a code bit may differ
+    only where its projection is within 1e-7 of zero."""
+    N, D, m, distinct, window, n_it, kw = {
+        "one": (4096, 512, 1024, 700, 0, 24, {}),
+        "one_streaming": (4096, 512, 1024, 700, 0, 24, dict(resident=0)),
+        "windows": (8 * 1111, 256, 512, 300, 1111, 24, {}),
+        "normalised": (4096, 256, 512, 900, 0, 16, dict(normalise=1)),
+        "ragged": (8191, 264, 512, 1001, 0, 24, {}),      # the last word of the bit map part full
+        "wide": (2051, 2056, 2048, 1500, 0, 24, {}),      # D past one 2048-value stretch
+    }[case]
+    X = _repeating_rows(N, D, distinct, 3)
+    if window:                                 # a different number of rows in each window
+        X[:window // 2] = X[window // 2 - 1]
+    a = _spectral_run(X, m, n_it, 12, 8, 1, window, **kw)
+    b = _spectral_run(X, m, n_it, 12, 8, 0, window, **kw)
+    L = window or N
+    assert b["rows"] == L and a["rows"] <= distinct + 1 < L
+    if not kw.get("normalise"):
+        assert np.array_equal(a["Phi"], b["Phi"])
+    else:
+        assert np.abs(a["Phi"] - b["Phi"]).max() <= 2e-7 * np.abs(b["Phi"]).max()
+        assert np.abs(a["rowsum"] / b["rowsum"] - 1).max() <= 1e-12
+    assert np.array_equal(a["iters"], b["iters"])
+    da = np.abs(a["ALPHA"] / b["ALPHA"] - 1).max()
+    dr = np.abs(a["ritz"] / b["ritz"] - 1).max()
+    dz, dq = np.abs(a["Z"] - b["Z"]).max(), np.abs(a["Q"][:, :n_it] - b["Q"][:, :n_it]).max()
+    de = np.abs(a["energy"] / b["energy"] - 1).max()
+    _say(f"[distinct rows] {case}: rows {a['rows']} of {L}, alpha {da:.1e} ritz {dr:.1e} Z {dz:.1e} Q {dq:.1e} energy {de:.1e}")
+    lim = 1e-6 if kw.get("normalise") else 1e-8    # row weights rounded to fp32 differ by an ulp
+    assert da <= lim and dr <= lim and dz <= 10 * lim and dq <= 10 * lim and de <= lim
+    flip = (a["PROJ"] > 0) != (b["PROJ"] > 0)
+    assert not flip.any() or np.abs(b["PROJ"][flip]).max() <= 100 * lim
+    if not flip.any():
+        assert np.array_equal(a["CODES"], b["CODES"])
+
+
+@pytest.mark.parametrize("case", ["all_different", "alike_where_hashed", "fp32", "few", "other_stream"])
+def test_distinct_rows_only_where_equal(case):
+    """What is grouped: rows equal in every value.  Rows that agree only in the
+    hashed stretches (the first 64 values and 64 from the middle), rows that all
+    differ and fp32 rows are taken one by one; with fewer distinct rows than steps
+    the run breaks down as it does on every row."""
+    import torch
+    N, D, m = 4096, 512, 1024
+    X = _repeating_rows(N, D, 500, 4)
+    n_it = 20
+    if case == "all_different":
+        X = (0.02 * torch.randn((N, D), generator=torch.Generator().manual_seed(1))).bfloat16().cuda()
+    elif case == "alike_where_hashed":
+        X[7, 200] += 1.0
+    elif case == "fp32":
+        X = X.float()
+    elif case == "few":
+        X = X[:3].repeat(N // 3 + 1, 1)[:N].contiguous()
+    if case == "other_stream":
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            a = _spectral_run(X, m, n_it, 4, 8, 1)
+        s.synchronize()
+    else:
+        a = _spectral_run(X, m, n_it, 4, 8, 1)
+    b = _spectral_run(X, m, n_it, 4, 8, 0)
+    if case in ("few", "other_stream"):
+        assert a["rows"] == (4 if case == "few" else 501)
+    else:
+        assert a["rows"] == N
+        assert all(np.array_equal(a[k], b[k]) for k in ("Phi", "Z", "CODES"))
+    if case == "few":
+        assert a["iters"][0] <= 6 and b["iters"][0] <= 6     # rank 3, and rounding past it
+        assert abs(a["ritz"][0, -1] / b["ritz"][0, -1] - 1) <= 1e-9
+    if case == "other_stream":
+        assert np.abs(a["Z"] - b["Z"]).max() <= 1e-7
+
+
 @pytest.mark.timeout(900)
 def test_end_to_end_qwen14b_long():
     inp = make_inputs("qwen14b_long")
