@@ -611,20 +611,25 @@ __global__ void k_lz_res_prep(LanczosWS w, const double* __restrict__ q1, ResCle
 namespace {
 struct ResShape {
   int p, rw, nb, cbl;   // row subsets, rows per wave, blocks per window, log2 of the columns per owner
+  int nw;               // windows of a launch
 };
+// Row subsets: those that fill 4 to 8 waves.  m = 1024 takes 8 waves rather than 4
+// (us a step, 4 / 8 waves: 1367 rows 6.4 / 6.2, 4096 rows 7.2 / 7.1, a launch of
+// 16 windows of 850 rows 10.6 / 8.7, where the blocks are half as many).
+constexpr int res_subsets(int ns) { return ns == 1 ? 4 : ns <= 4 ? 2 : 1; }
 // The resident kernel's shapes for w in order of preference; returns their number
 // (0: it does not qualify).  nb = ceil(L / RB) rounded up to a power of two
 // (blocks past the last row hold zeros), at least m / (the most columns a block
-// can own), at most 256, all windows' blocks at most two per compute unit.
+// can own), at most 256.
 // Preferred: the fewest rows a block (less work per step in each) while the
 // exchanged partials, nb m doubles a step and window, stay few: nb <= 128, or
 // nb m <= 2^17.  Measured, us a step (rows a block): 5003 x 512 6.5 (32) 6.8
-// (64); 1216 x 256 5.3 (32) 5.6 (64); 1367 x 1024 8.4 (8) 6.6 (16) 6.9 (32);
-// 4096 x 1024 8.7 (16) 7.5 (32); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
+// (64); 1216 x 256 5.3 (32) 5.6 (64); 1367 x 1024 6.2 (16) 6.9 (32) 8.4 (64);
+// 4096 x 1024 7.4 (16) 7.1 (32) 8.6 (64); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
 // (16) 8.1 (32); 3001 x 768 7.2 (16) 7.0 (32) 8.5 (64).
 int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
   if (w.n_act < 1 || w.m % 256 != 0 || w.m < 256 || w.m > 2048 || w.n_it > 256 || w.n_it < 1) return 0;
-  const int ns = w.m / 256, p = ns == 1 ? 4 : ns <= 3 ? 2 : 1, nt = 64 * ns * p;
+  const int ns = w.m / 256, p = res_subsets(ns), nt = 64 * ns * p;
   const int cbmax = std::min(nt & -nt, 256);     // a power of two dividing the threads
   ResShape c[3];
   int n = 0, pref = -1;
@@ -632,11 +637,11 @@ int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
     if (p * rw > 64) continue;
     int64_t nb = 1;
     while (nb * p * rw < w.L || nb * cbmax < w.m) nb *= 2;
-    if (nb > 256 || nb * w.n_act > 2LL * n_cu) continue;
+    if (nb > 256) continue;
     int cbl = 2;
     while ((nb << cbl) < w.m) ++cbl;
     if (pref < 0 && nb * w.n_act <= n_cu && (nb <= 128 || nb * w.m <= 131072)) pref = n;
-    c[n++] = ResShape{p, rw, (int)nb, cbl};
+    c[n++] = ResShape{p, rw, (int)nb, cbl, 0};
   }
   // the preferred one, then the others from the most rows a block down
   int k = 0;
@@ -645,9 +650,10 @@ int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
     if (q != pref) out[k++] = c[q];
   return k;
 }
+// per_cu != NULL: only the blocks that one compute unit holds
 template <int NS, int P, int RW, bool SPIN>
 hipError_t launch_res_t(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                        int check_cu, hipStream_t s) {
+                        int* per_cu, hipStream_t s) {
   auto k = k_lz_resident<NS, P, RW, SPIN>;
   constexpr int NT = 64 * NS * P;
   const size_t lds = (size_t)(w.n_it + 1) * (P * RW + 1) * sizeof(double);
@@ -656,61 +662,71 @@ hipError_t launch_res_t(const LanczosWS& w, const ResShape& sh, unsigned* bar, c
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (check_cu > 0) {
-    // every block resident at once
-    int per_cu = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k, NT, lds);
-    if (e != hipSuccess) return e;
-    return (int64_t)per_cu * check_cu >= (int64_t)w.n_act * sh.nb ? hipSuccess
-                                                                  : hipErrorInvalidConfiguration;
-  }
+  if (per_cu) return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void*)k, NT, lds);
   hipLaunchKernelGGL(k, dim3(sh.nb * w.n_act), dim3(NT), lds, s, w, bar, q1, sh.nb, sh.cbl);
   return hipGetLastError();
 }
 template <int NS, bool SPIN>
 hipError_t launch_res_n(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                        int check_cu, hipStream_t s) {
-  // P: the row subsets that fill 4 or 8 waves
-  constexpr int P = NS == 1 ? 4 : NS <= 3 ? 2 : 1;
-  if (sh.rw == 8) return launch_res_t<NS, P, 8, SPIN>(w, sh, bar, q1, check_cu, s);
-  if (sh.rw == 16) return launch_res_t<NS, P, 16, SPIN>(w, sh, bar, q1, check_cu, s);
-  if constexpr (P <= 2) return launch_res_t<NS, P, 32, SPIN>(w, sh, bar, q1, check_cu, s);
+                        int* per_cu, hipStream_t s) {
+  constexpr int P = res_subsets(NS);
+  if (sh.rw == 8) return launch_res_t<NS, P, 8, SPIN>(w, sh, bar, q1, per_cu, s);
+  if (sh.rw == 16) return launch_res_t<NS, P, 16, SPIN>(w, sh, bar, q1, per_cu, s);
+  if constexpr (P <= 2) return launch_res_t<NS, P, 32, SPIN>(w, sh, bar, q1, per_cu, s);
   return hipErrorInvalidValue;
 }
 template <bool SPIN>
 hipError_t launch_res_s(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                        int check_cu, hipStream_t s) {
+                        int* per_cu, hipStream_t s) {
   switch (w.m / 256) {
-    case 1: return launch_res_n<1, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 2: return launch_res_n<2, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 3: return launch_res_n<3, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 4: return launch_res_n<4, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 5: return launch_res_n<5, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 6: return launch_res_n<6, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 7: return launch_res_n<7, SPIN>(w, sh, bar, q1, check_cu, s);
-    case 8: return launch_res_n<8, SPIN>(w, sh, bar, q1, check_cu, s);
+    case 1: return launch_res_n<1, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 2: return launch_res_n<2, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 3: return launch_res_n<3, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 4: return launch_res_n<4, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 5: return launch_res_n<5, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 6: return launch_res_n<6, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 7: return launch_res_n<7, SPIN>(w, sh, bar, q1, per_cu, s);
+    case 8: return launch_res_n<8, SPIN>(w, sh, bar, q1, per_cu, s);
   }
   return hipErrorInvalidValue;
 }
 // a wait limit other than the built-in one (SLH_OPT_WAIT_POLLS) takes an
 // instantiation of its own, so that the limit stays a constant in the other
 hipError_t launch_res(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
-                      int check_cu, hipStream_t s) {
-  return w.spin > 0 ? launch_res_s<true>(w, sh, bar, q1, check_cu, s)
-                    : launch_res_s<false>(w, sh, bar, q1, check_cu, s);
+                      int* per_cu, hipStream_t s) {
+  return w.spin > 0 ? launch_res_s<true>(w, sh, bar, q1, per_cu, s)
+                    : launch_res_s<false>(w, sh, bar, q1, per_cu, s);
 }
 }  // namespace
 
 namespace {
-// the first shape whose blocks are all resident at once (p = 0: none)
+// The first shape whose blocks, of all windows, are resident at once (at most two
+// per compute unit), else the one that takes the fewest launches of as many
+// windows as are (p = 0: none).  A step of a launch that fills the chip takes
+// up to 10 us, one of the streaming path 9 us + its read of Phi at 5.5 TB/s (32
+// windows of 850 x 1024: two launches 17.3 us a step against 29).
 ResShape res_shape(const LanczosWS& w, int n_cu) {
-  ResShape sh[3];
+  ResShape sh[3], best{0, 0, 0, 0, 0};
   const int n = res_shapes(w, n_cu, sh);
+  int fewest = 0;
   (void)hipGetLastError();
-  for (int q = 0; q < n; ++q)
-    if (launch_res(w, sh[q], nullptr, nullptr, n_cu, nullptr) == hipSuccess) return sh[q];
+  for (int q = 0; q < n; ++q) {
+    int per_cu = 0;
+    if (launch_res(w, sh[q], nullptr, nullptr, &per_cu, nullptr) != hipSuccess) continue;
+    sh[q].nw = std::min(w.n_act, std::min(per_cu, 2) * n_cu / sh[q].nb);
+    if (sh[q].nw == w.n_act) return sh[q];
+    if (sh[q].nw < 1) continue;
+    const int launches = (w.n_act + sh[q].nw - 1) / sh[q].nw;
+    if (best.p == 0 || launches < fewest) {
+      best = sh[q];
+      fewest = launches;
+    }
+  }
   (void)hipGetLastError();
-  return ResShape{0, 0, 0, 0};
+  const double phi = 4.0 * w.n_act * w.L * w.m;
+  if (best.p && 10.0 * fewest >= 9.0 + phi / 5.5e6) best.p = best.nb = 0;
+  if (best.p) best.nw = (w.n_act + fewest - 1) / fewest;   // launches of equal size
+  return best;
 }
 }  // namespace
 
@@ -725,27 +741,39 @@ hipError_t launch_lanczos_resident(const LanczosWS& w, const double* q1_act, uns
   (void)hipGetLastError();
   const ResShape sh = res_shape(w, n_cu);
   if (sh.p == 0) return hipErrorInvalidValue;
-  const int64_t hs = w.ldq + 1, na = w.n_act;
-  ResClear z;
-  double* const bufs[5] = {(double*)bar, w.Spart, w.H2part, w.T, w.H2};
-  // T: the copies in use lie at the front of each window's ldq m doubles
-  const int64_t lens[5] = {(int64_t)lanczos_resident_bar_words() / 2, na * sh.nb * w.m,
-                           na * sh.nb * hs,
-                           ((na - 1) * w.ldq + res_copies(w.ldq, sh.nb)) * w.m, na * hs};
-  for (int q = 0; q < 5; ++q) {
-    z.p[q] = bufs[q];
-    z.n[q] = lens[q];
+  const int64_t hs = w.ldq + 1;
+  hipError_t e = hipSuccess;
+  for (int a0 = 0; a0 < w.n_act && e == hipSuccess; a0 += sh.nw) {
+    // windows a0 .. a0 + na - 1 (Spart, H2part, H2 and T serve every launch)
+    const int64_t na = std::min(sh.nw, w.n_act - a0);
+    LanczosWS b = w;
+    b.n_act = (int)na;
+    b.Phi += (int64_t)a0 * w.L * w.m;
+    if (b.wt) b.wt += a0 * w.ldr;
+    b.Q += (int64_t)a0 * w.ldq * w.L;
+    b.alpha += (int64_t)a0 * w.n_it;
+    b.beta += (int64_t)a0 * w.n_it;
+    b.neff += a0;
+    b.stop += a0;
+    b.amax += 2 * a0;
+    const double* q1 = q1_act + a0 * w.ldr;
+    ResClear z;
+    double* const bufs[5] = {(double*)bar, b.Spart, b.H2part, b.T, b.H2};
+    // the error word is cleared once a run.  T: the copies in use lie at the front
+    // of each window's ldq m doubles.
+    const int64_t lens[5] = {a0 ? 0 : (int64_t)lanczos_resident_bar_words() / 2, na * sh.nb * w.m,
+                             na * sh.nb * hs,
+                             ((na - 1) * w.ldq + res_copies(w.ldq, sh.nb)) * w.m, na * hs};
+    for (int q = 0; q < 5; ++q) {
+      z.p[q] = bufs[q];
+      z.n[q] = lens[q];
+    }
+    hipLaunchKernelGGL(k_lz_res_prep, dim3(256), dim3(256), 0, s, b, q1, z);
+    e = hipGetLastError();
+    if (e == hipSuccess && e0 && a0 == 0) e = hipEventRecord(e0, s);
+    if (e == hipSuccess) e = launch_res(b, sh, bar, q1, nullptr, s);
   }
-  hipLaunchKernelGGL(k_lz_res_prep, dim3(256), dim3(256), 0, s, w, q1_act, z);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (e0) {
-    e = hipEventRecord(e0, s);
-    if (e != hipSuccess) return e;
-  }
-  e = launch_res(w, sh, bar, q1_act, 0, s);
-  if (e != hipSuccess) return e;
-  if (e1) e = hipEventRecord(e1, s);
+  if (e == hipSuccess && e1) e = hipEventRecord(e1, s);
   return e;
 }
 
