@@ -193,19 +193,24 @@ __device__ __forceinline__ void launder_rows(float4 (&ph)[RW]) {
 // bytes.  A step is two exchanges between blocks (a store and the poll that
 // sees it, about 2000 cycles each) and six block barriers with the dots, sums
 // and scalars between them.
-template <int NS, int P, int RW, bool SPIN>
+// RL: that many more rows a block, in LDS (their float4s are read back once for
+// the row dots and once for the column partials), for windows a little past what
+// the registers hold.
+template <int NS, int P, int RW, int RL, bool SPIN>
 __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, unsigned* bar,
                                                                 const double* __restrict__ q1,
                                                                 int nb, int cbl) {
-  constexpr int NW = NS * P, NT = 64 * NW, RB = P * RW, KG = NT / RB, QS = RB + 1;   // QS: row stride of Qs (bank spread)
+  constexpr int NW = NS * P, NT = 64 * NW, RB = P * RW + RL, QS = RB + 1;   // QS: row stride of Qs (bank spread)
   constexpr int CPT = P <= 4 ? 4 / P : 1;        // columns whose partials a thread stores
   // column partials a thread reads: CB nb is m rounded up to a power of two, or
   // 4 nb <= 4 * 256 at the smallest CB
   constexpr int M2 = NS <= 4 ? 1024 : 2048;
   constexpr int UL = (M2 + NT - 1) / NT;
-  constexpr int RP = 64 / RB;                    // lanes of wave 0 per row
+  constexpr int RS = RB <= 8 ? 8 : RB <= 16 ? 16 : RB <= 32 ? 32 : 64;   // row slots of the row-space sums
+  constexpr int KG = NT / RS;
+  constexpr int RP = 64 / RS;                    // lanes of wave 0 per row
   constexpr int m = 256 * NS;
-  static_assert(RW % 8 == 0 && NT % RB == 0 && RB <= 64 && RB >= 8 && NT >= 256, "shape");
+  static_assert(RW % 8 == 0 && RL % 8 == 0 && RB <= 64 && NT >= 256 && (RL == 0 || P == 1), "shape");
   const int CB = 1 << cbl;
   // window a, block b of its nb (consecutive blocks on one XCD where n_act is a
   // multiple of 8: the dispatch deals blocks to the XCDs in turn)
@@ -217,11 +222,13 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
   const int spin = SPIN ? (w.spin > 0 ? w.spin : LR_SPIN) : LR_SPIN;
   const int r0 = b * RB;
   const int cb = 256 * sl + 4 * lane;
-  extern __shared__ double Qs[];                 // [n_it + 1][QS]
+  extern __shared__ float4 res_dyn[];
+  float4* const lrow = res_dyn;                  // [RL][m / 4]
+  double* const Qs = (double*)(res_dyn + RL * (m / 4));   // [n_it + 1][QS]
   __shared__ double h2s[256], gs[256], als[256], bes[256];
-  __shared__ double prw[NS][RB];
-  __shared__ double zs[RB], zw[RB], ws[RB];
-  __shared__ double rq[NW][RB + 1], rg[NW][RB + 1];
+  __shared__ double prw[NS][RS];
+  __shared__ double zs[RS], zw[RS], ws[RS];
+  __shared__ double rq[NW][RS + 1], rg[NW][RS + 1];
   __shared__ double red[3][NW], z2s;
   __shared__ double cpart[NT], hw[NW];
   __shared__ double cr[P > 1 ? P : 1][P > 1 ? m : 1];
@@ -250,8 +257,14 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
       for (int r = 0; r < RW; ++r)
         if (r0 + pw * RW + r >= L) ph[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const float4 x = *(const float4*)(src + (int64_t)min(r0 + RW + r, L - 1) * m);
+      lrow[r * (m / 4) + cb / 4] = r0 + RW + r < L ? x : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
   }
   if (tid == 0) bad = 0;
+  if (RS != RB && tid < RS) zs[tid] = zw[tid] = ws[tid] = 0.0;   // (slots past the rows)
   if (tid < RB) {
     const double q = (r0 + tid < L) ? q1[a * w.ldr + r0 + tid] : 0.0;
     const double wr = (w.wt && r0 + tid < L) ? w.wt[a * w.ldr + r0 + tid] : 1.0;
@@ -273,6 +286,15 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
       col[1] = fma((double)ph[r].y, z, col[1]);
       col[2] = fma((double)ph[r].z, z, col[2]);
       col[3] = fma((double)ph[r].w, z, col[3]);
+    }
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+      const double z = zw[RW + r];
+      const float4 x = lrow[r * (m / 4) + cb / 4];
+      col[0] = fma((double)x.x, z, col[0]);
+      col[1] = fma((double)x.y, z, col[1]);
+      col[2] = fma((double)x.z, z, col[2]);
+      col[3] = fma((double)x.w, z, col[3]);
     }
     // column c of block b at ((c / CB) nb + b) CB + c % CB: the partials a block
     // reduces are contiguous
@@ -402,6 +424,20 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
       const double tot = wave_sum8_f64(d);
       if ((lane & 7) == 0) prw[sl][pw * RW + r8 + idx] = tot;
     }
+#pragma unroll
+    for (int r8 = 0; r8 < RL; r8 += 8) {
+      double d[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float4 y = lrow[(r8 + e) * (m / 4) + cb / 4];
+        double x = (double)y.x * tv[0];
+        x = fma((double)y.y, tv[1], x);
+        x = fma((double)y.z, tv[2], x);
+        d[e] = fma((double)y.w, tv[3], x);
+      }
+      const double tot = wave_sum8_f64(d);
+      if ((lane & 7) == 0) prw[sl][RW + r8 + idx] = tot;
+    }
     // h2 (threads < j) with the neighbours that the wave's edge lanes need for
     // g, and |z1|^2 (thread j); T_{j-1}'s entries are read while they arrive
     const int tj = min(tid, max(j - 1, 0));
@@ -446,20 +482,20 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
     if (bad) return;
     // Q_{j-1} h2 and Q_{j-1} g of each row: thread = (row i, k-group kg)
     {
-      const int i = tid % RB, kg = tid / RB;
+      const int i = tid % RS, kg = tid / RS;
       double aq = 0.0, ag = 0.0;
 #pragma unroll 4
-      for (int k = kg; k < j; k += KG) {
+      for (int k = (RS == RB || i < RB) ? kg : j; k < j; k += KG) {
         const double qk = Qs[k * QS + i];
         aq = fma(qk, h2s[k], aq);
         ag = fma(qk, gs[k], ag);
       }
-      // the wave's k-groups of a row lie RB lanes apart
-      if constexpr (RB <= 32) {
-        aq = strided_sum(aq, RB);
-        ag = strided_sum(ag, RB);
+      // the wave's k-groups of a row lie RS lanes apart
+      if constexpr (RS <= 32) {
+        aq = strided_sum(aq, RS);
+        ag = strided_sum(ag, RS);
       }
-      if (lane < RB) {
+      if (lane < RS) {
         rq[wv][i] = aq;
         rg[wv][i] = ag;
       }
@@ -499,7 +535,7 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
     __syncthreads();
     // q_j and z1 of the block's rows: wave 0, RP lanes a row over the waves' sums
     if (tid < 64) {
-      const int i = tid % RB, part = tid / RB, row = r0 + i;
+      const int i = tid % RS, part = tid / RS, row = i < RB ? r0 + i : L;
       double sub = 0.0, sg = 0.0, u = 0.0;
 #pragma unroll
       for (int q = 0; q < NW; q += RP) {
@@ -512,18 +548,18 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
       for (int q = 0; q < NS; q += RP) {
         if (NS % RP == 0 || q + part < NS) u += prw[q + part][i];
       }
-      if constexpr (RB <= 32) {
-        sub = strided_sum(sub, RB);
-        sg = strided_sum(sg, RB);
-        u = strided_sum(u, RB);
+      if constexpr (RS <= 32) {
+        sub = strided_sum(sub, RS);
+        sg = strided_sum(sg, RS);
+        u = strided_sum(u, RS);
       }
       const double wr = ws[i];
       u *= wr;
-      double q = Qs[i], qm = 0.0;                 // j = 0: q_0
+      double q = Qs[min(i, RB - 1)], qm = 0.0;    // j = 0: q_0
       if (j > 0) {
         q = (row < L) ? (zs[i] - sub) * ibeta : 0.0;
-        qm = Qs[(j - 1) * QS + i];
-        if (part == 0) {
+        qm = Qs[(j - 1) * QS + min(i, RB - 1)];
+        if (part == 0 && (RS == RB || i < RB)) {
           Qs[j * QS + i] = q;
           if (row < L) Qa[(int64_t)j * L + row] = q;
         }
@@ -610,7 +646,7 @@ __global__ void k_lz_res_prep(LanczosWS w, const double* __restrict__ q1, ResCle
 
 namespace {
 struct ResShape {
-  int p, rw, nb, cbl;   // row subsets, rows per wave, blocks per window, log2 of the columns per owner
+  int p, rw, rl, nb, cbl;   // row subsets, rows per wave, rows in LDS, blocks per window, log2 of the columns per owner
   int nw;               // windows of a launch
 };
 // Row subsets: those that fill 4 to 8 waves.  m = 1024 takes 8 waves rather than 4
@@ -627,21 +663,23 @@ constexpr int res_subsets(int ns) { return ns == 1 ? 4 : ns <= 4 ? 2 : 1; }
 // (64); 1216 x 256 5.3 (32) 5.6 (64); 1367 x 1024 6.2 (16) 6.9 (32) 8.4 (64);
 // 4096 x 1024 7.4 (16) 7.1 (32) 8.6 (64); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
 // (16) 8.1 (32); 3001 x 768 7.2 (16) 7.0 (32) 8.5 (64).
-int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
+int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[4]) {
   if (w.n_act < 1 || w.m % 256 != 0 || w.m < 256 || w.m > 2048 || w.n_it > 256 || w.n_it < 1) return 0;
   const int ns = w.m / 256, p = res_subsets(ns), nt = 64 * ns * p;
   const int cbmax = std::min(nt & -nt, 256);     // a power of two dividing the threads
-  ResShape c[3];
+  ResShape c[4];
   int n = 0, pref = -1;
-  for (int rw : {8, 16, 32}) {
-    if (p * rw > 64) continue;
+  for (int q = 0; q < 4; ++q) {
+    const int rw = q < 3 ? 8 << q : 32, rl = q < 3 ? 0 : 8, rb = p * rw + rl;
+    if (rb > 64 || (rl && ns < 5)) continue;
     int64_t nb = 1;
-    while (nb * p * rw < w.L || nb * cbmax < w.m) nb *= 2;
+    while (nb * rb < w.L || nb * cbmax < w.m) nb *= 2;
+    if (rl && n > 0 && nb == c[n - 1].nb) continue;      // registers hold as many
     if (nb > 256) continue;
     int cbl = 2;
     while ((nb << cbl) < w.m) ++cbl;
     if (pref < 0 && nb * w.n_act <= n_cu && (nb <= 128 || nb * w.m <= 131072)) pref = n;
-    c[n++] = ResShape{p, rw, (int)nb, cbl, 0};
+    c[n++] = ResShape{p, rw, rl, (int)nb, cbl, 0};
   }
   // the preferred one, then the others from the most rows a block down
   int k = 0;
@@ -651,12 +689,12 @@ int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[3]) {
   return k;
 }
 // per_cu != NULL: only the blocks that one compute unit holds
-template <int NS, int P, int RW, bool SPIN>
+template <int NS, int P, int RW, int RL, bool SPIN>
 hipError_t launch_res_t(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
                         int* per_cu, hipStream_t s) {
-  auto k = k_lz_resident<NS, P, RW, SPIN>;
+  auto k = k_lz_resident<NS, P, RW, RL, SPIN>;
   constexpr int NT = 64 * NS * P;
-  const size_t lds = (size_t)(w.n_it + 1) * (P * RW + 1) * sizeof(double);
+  const size_t lds = (size_t)(w.n_it + 1) * (P * RW + RL + 1) * sizeof(double) + (size_t)RL * 1024 * NS;
   if (lds > 65536) {
     const hipError_t e =
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -670,9 +708,11 @@ template <int NS, bool SPIN>
 hipError_t launch_res_n(const LanczosWS& w, const ResShape& sh, unsigned* bar, const double* q1,
                         int* per_cu, hipStream_t s) {
   constexpr int P = res_subsets(NS);
-  if (sh.rw == 8) return launch_res_t<NS, P, 8, SPIN>(w, sh, bar, q1, per_cu, s);
-  if (sh.rw == 16) return launch_res_t<NS, P, 16, SPIN>(w, sh, bar, q1, per_cu, s);
-  if constexpr (P <= 2) return launch_res_t<NS, P, 32, SPIN>(w, sh, bar, q1, per_cu, s);
+  if (sh.rw == 8) return launch_res_t<NS, P, 8, 0, SPIN>(w, sh, bar, q1, per_cu, s);
+  if (sh.rw == 16) return launch_res_t<NS, P, 16, 0, SPIN>(w, sh, bar, q1, per_cu, s);
+  if constexpr (NS >= 5)
+    if (sh.rl == 8) return launch_res_t<NS, P, 32, 8, SPIN>(w, sh, bar, q1, per_cu, s);
+  if constexpr (P <= 2) return launch_res_t<NS, P, 32, 0, SPIN>(w, sh, bar, q1, per_cu, s);
   return hipErrorInvalidValue;
 }
 template <bool SPIN>
@@ -706,7 +746,7 @@ namespace {
 // up to 10 us, one of the streaming path 9 us + its read of Phi at 5.5 TB/s (32
 // windows of 850 x 1024: two launches 17.3 us a step against 29).
 ResShape res_shape(const LanczosWS& w, int n_cu) {
-  ResShape sh[3], best{0, 0, 0, 0, 0};
+  ResShape sh[4], best{};
   const int n = res_shapes(w, n_cu, sh);
   int fewest = 0;
   (void)hipGetLastError();

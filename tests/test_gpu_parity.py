@@ -393,6 +393,8 @@ def test_resident_lanczos_on_oracle_phi(case):
     (700, 1280, 256, 0),      # five waves
     (2500, 1536, 24, 0), (300, 1792, 24, 0),
     (4097, 2048, 24, 0),      # past 128 blocks of 32 rows
+    (8193, 2048, 24, 0),      # past the registers: rows in LDS too
+    (10240, 1280, 24, 0),     # ... in every slot
     (64 * 40, 512, 24, 64), (5 * 161, 1024, 24, 161), (3 * 37, 2048, 12, 37),
     (21 * 900, 1024, 24, 900)])   # two launches, of 11 and 10 windows
 def test_resident_shapes_match_streaming(N, m, n_it, window):
