@@ -183,6 +183,18 @@ __global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
   if (tid == 0) w.mw[win] = nseg;
 }
 
+// the count M of a single window where the later steps and the host look for it
+__device__ __forceinline__ void mg_totals(const MergeWS& w, int M, const MergeOut& o) {
+  w.mw[0] = M;
+  w.wbase[0] = 0;
+  w.wbase[1] = M;
+  *w.Mtot = M;
+  if (o.report) {
+    o.report[0] = (unsigned)M;
+    o.report[1] = o.err ? *o.err : 0u;
+  }
+}
+
 // Book-keeping of a window of L <= 16384 tokens in one 1024-thread block: sort
 // the keys (code << tb) | local token (tb = log2 P, P = L rounded up to a power
 // of two) by code, stably, so each bucket's members stay in token order; flag
@@ -203,8 +215,12 @@ __global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
 // position's code (a neighbour shuffle), and each position's bucket end by a
 // reverse scan over the block.  Dynamic LDS: two buffers of L keys (the second
 // reused for the token ranks).
-template <int E>
-__global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int P, int tb) {
+//
+// FIN (one window, max positions): the macro indices are the window's own, so
+// what k_mg_wbase, k_mg_finalize and k_mg_report do is done here too (three
+// launches of 4 to 5 us each on one prompt).
+template <int E, bool FIN>
+__global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int tb, MergeOut o) {
   extern __shared__ uint32_t mg_dyn[];
   const int L = w.L;
   uint32_t* bufA = mg_dyn;                            // [L]
@@ -219,12 +235,21 @@ __global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int P, int tb) 
     const int k = w.chunk_k;
     for (int s = tid; s < L; s += 1024) {
       w.sval[base + s] = (int)(base + s);
-      w.sloc[base + s] = s / k;
+      if constexpr (FIN) {
+        const int g = s / k;
+        w.sseg[s] = g;
+        if (o.tok2macro) o.tok2macro[s] = g;
+        if (s == L - 1 || (s + 1) % k == 0) o.P[g] = w.compact ? g : s;
+      } else {
+        w.sloc[base + s] = s / k;
+      }
     }
-    if (tid == 0) w.mw[win] = (L + k - 1) / k;
+    if (tid == 0) {
+      if constexpr (FIN) mg_totals(w, (L + k - 1) / k, o);
+      else w.mw[win] = (L + k - 1) / k;
+    }
     return;
   }
-  (void)P;
   const uint32_t tmask = (1u << tb) - 1u;
   for (int i = tid; i < L; i += 1024) bufA[i] = (w.codes[base + i] << tb) | (uint32_t)i;
 
@@ -354,11 +379,21 @@ __global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int P, int tb) 
     const int s = tid * E + e;
     if (fl[e]) cur = (int)(v[e] & tmask);
     if (s < L) {
-      w.sval[base + s] = (int)(base + (v[e] & tmask));
-      w.sloc[base + s] = R[cur];
+      const int tok = (int)(base + (v[e] & tmask)), g = R[cur];
+      w.sval[base + s] = tok;
+      if constexpr (FIN) {
+        w.sseg[s] = g;
+        if (o.tok2macro) o.tok2macro[tok] = g;
+        if (fl[e]) o.P[g] = w.compact ? g : tok;
+      } else {
+        w.sloc[base + s] = g;
+      }
     }
   }
-  if (tid == 0) w.mw[win] = tot;
+  if (tid == 0) {
+    if constexpr (FIN) mg_totals(w, tot, o);
+    else w.mw[win] = tot;
+  }
 }
 
 // inclusive max-scan of one int per thread over a 1024-thread block
@@ -785,6 +820,19 @@ __device__ __forceinline__ void mg_add(float* acc, const MgRaw<DT>& r) {
   }
 }
 
+// sum of the squares of 8 values
+template <int DT>
+__device__ __forceinline__ double mg_sq(const MgRaw<DT>& r) {
+  float f[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f[e] = 0.0f;
+  mg_add<DT>(f, r);
+  double s = 0.0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s = fma((double)f[e], (double)f[e], s);
+  return s;
+}
+
 __device__ __forceinline__ void mg_store8(float* dst, const float* v, float scale) {
   ((float4*)dst)[0] = make_float4(v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale);
   ((float4*)dst)[1] = make_float4(v[4] * scale, v[5] * scale, v[6] * scale, v[7] * scale);
@@ -802,7 +850,10 @@ __device__ __forceinline__ float mg_block_sum(float v, float* red) {
 // One workgroup per chunk of CH sorted positions; member rows stream DEPTH at
 // a time with the next DEPTH in flight (DEPTH sized to keep the row buffers at
 // 64 registers).
-template <int DT, int PPT>
+// NRM: the rows' norms are taken here from the values loaded for the sums (fp64,
+// two barriers a batch) rather than read from w.nrm_x; the merge alone then reads
+// X once instead of twice.
+template <int DT, int PPT, bool NRM>
 __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
                                                    int64_t ldx, float* __restrict__ E) {
   const int c = blockIdx.x, tid = threadIdx.x;
@@ -813,11 +864,12 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
   __shared__ double snrm[MG_CHMAX];
   __shared__ int prev_g, next_g;
   __shared__ float red[2][8];
+  __shared__ double wsq[NRM ? 8 : 1][8];
   if (tid < n) {
     const int tok = w.sval[s0 + tid];
     ssv[tid] = tok;
     ssg[tid] = w.sseg[s0 + tid];
-    snrm[tid] = w.nrm_x[tok];
+    if constexpr (!NRM) snrm[tid] = w.nrm_x[tok];
   }
   if (tid == 0) {
     prev_g = (s0 > 0) ? w.sseg[s0 - 1] : -1;
@@ -854,6 +906,28 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
   load_batch(rc, 0);
   for (int b = 0; b < nbat; ++b) {
     if (b + 1 < nbat) load_batch(rn, b + 1);
+    if constexpr (NRM) {
+      double sq8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sq8[e] = 0.0;
+        if (e < DEPTH) {
+#pragma unroll
+          for (int q = 0; q < PPT; ++q) sq8[e] += cin[q] ? mg_sq<DT>(rc[e < DEPTH ? e : 0][q]) : 0.0;
+        }
+      }
+      const double tot = wave_sum8_f64(sq8);
+      const int lane = tid & 63;
+      if ((lane & 7) == 0)
+        wsq[((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1)][tid >> 6] = tot;
+      __syncthreads();
+      if (tid < DEPTH && DEPTH * b + tid < n) {
+        const double* q = wsq[tid];
+        snrm[DEPTH * b + tid] =
+            sqrt(((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int e = 0; e < DEPTH; ++e) {
       const int s = DEPTH * b + e;
@@ -1027,7 +1101,8 @@ __global__ __launch_bounds__(512) void k_mg_combine(MergeWS w, float* __restrict
 template <int DT, int PPT>
 static void launch_reduce_combine(const MergeWS& w, const void* X, int64_t ldx, float* E,
                                   int nchunks, hipStream_t s) {
-  hipLaunchKernelGGL((k_mg_reduce<DT, PPT>), dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
+  if (w.nrm_x) hipLaunchKernelGGL((k_mg_reduce<DT, PPT, false>), dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
+  else hipLaunchKernelGGL((k_mg_reduce<DT, PPT, true>), dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
   hipLaunchKernelGGL((k_mg_combine<PPT>), dim3(nchunks), dim3(512), 0, s, w, E, nchunks);
 }
 
@@ -1073,12 +1148,6 @@ __global__ void k_mg_report(const int* __restrict__ Mtot, const unsigned* __rest
   out[1] = err ? *err : 0u;
 }
 
-hipError_t launch_merge_report(const int* Mtot, const unsigned* err, unsigned* out, hipStream_t s) {
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(k_mg_report, dim3(1), dim3(1), 0, s, Mtot, err, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64_t N, int K,
                              const int* Mtot, int compact, float* E, int* P, int* tok2macro,
                              hipStream_t s) {
@@ -1093,36 +1162,47 @@ hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64
   return hipGetLastError();
 }
 
+// Longer chunks leave fewer cut buckets, whose partial rows are written and read
+// again, and a shorter chain to sum for the most common bucket; they take rows
+// enough to fill the chip.  Measured at 16 / 32 / 64: 32768 tokens 2465 / 2413 /
+// 2347 us a call, 49157 668 / 644 / 642, 8192 1144 / 1140 / 1153, 512 241 / 246 /
+// 256, 64 windows of 2048 365 / 366 / 381.
+int merge_chunk(int64_t L) { return L >= 24576 ? 64 : L >= 8192 ? 32 : 16; }
+
 int merge_nchunks(int64_t N, int CH) { return (int)((N + CH - 1) / CH); }
 
+template <int E, bool FIN>
+static hipError_t launch_book_lds(const MergeWS& w, int tb, const MergeOut& o, hipStream_t s) {
+  const size_t bytes = (size_t)2 * w.L * 4;
+  auto k = k_mg_book_lds<E, FIN>;
+  if (bytes > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3(w.n_win), dim3(1024), bytes, s, w, tb, o);
+  return hipSuccess;
+}
+template <bool FIN>
+static hipError_t launch_book(const MergeWS& w, const MergeOut& o, hipStream_t s) {
+  int tb = 0;
+  while ((1 << tb) < w.L) ++tb;
+  switch (tb) {
+    case 14: return launch_book_lds<16, FIN>(w, tb, o, s);
+    case 13: return launch_book_lds<8, FIN>(w, tb, o, s);
+    case 12: return launch_book_lds<4, FIN>(w, tb, o, s);
+    case 11: return launch_book_lds<2, FIN>(w, tb, o, s);
+    default: return launch_book_lds<1, FIN>(w, tb, o, s);
+  }
+}
+
 hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx, float* E,
-                        int* P, int* tok2macro, hipStream_t s) {
+                        const MergeOut& o, hipStream_t s) {
   (void)hipGetLastError();
+  const bool fin = w.L <= 16384 && w.n_win == 1 && w.N == w.L && !w.tw && w.scheme == 0;
   if (w.L <= 16384) {
-    int P = 1, tb = 0;
-    while (P < w.L) {
-      P <<= 1;
-      ++tb;
-    }
-    const int Pp = P > 1024 ? P : 1024;
-    const size_t bytes = (size_t)2 * w.L * 4;
-    const void* kf = (Pp == 1024)   ? (const void*)k_mg_book_lds<1>
-                     : (Pp == 2048) ? (const void*)k_mg_book_lds<2>
-                     : (Pp == 4096) ? (const void*)k_mg_book_lds<4>
-                     : (Pp == 8192) ? (const void*)k_mg_book_lds<8>
-                                    : (const void*)k_mg_book_lds<16>;
-    if (bytes > 65536) {
-      const hipError_t e = hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)bytes);
-      if (e != hipSuccess) return e;
-    }
-    switch (Pp) {
-      case 1024: hipLaunchKernelGGL(k_mg_book_lds<1>, dim3(w.n_win), dim3(1024), bytes, s, w, P, tb); break;
-      case 2048: hipLaunchKernelGGL(k_mg_book_lds<2>, dim3(w.n_win), dim3(1024), bytes, s, w, P, tb); break;
-      case 4096: hipLaunchKernelGGL(k_mg_book_lds<4>, dim3(w.n_win), dim3(1024), bytes, s, w, P, tb); break;
-      case 8192: hipLaunchKernelGGL(k_mg_book_lds<8>, dim3(w.n_win), dim3(1024), bytes, s, w, P, tb); break;
-      default: hipLaunchKernelGGL(k_mg_book_lds<16>, dim3(w.n_win), dim3(1024), bytes, s, w, P, tb); break;
-    }
+    const hipError_t e = fin ? launch_book<true>(w, o, s) : launch_book<false>(w, o, s);
+    if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(k_mg_book, dim3(w.n_win), dim3(1024), 0, s, w);
   }
@@ -1132,12 +1212,16 @@ hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx,
   if (w.scheme != 0)
     hipLaunchKernelGGL(k_mg_rerank, dim3(w.n_win), dim3(1024), 0, s, w, w.scheme, w.posv, w.valA,
                        w.pre, w.tmpi, w.segid, w.segk, w.valB);
-  hipLaunchKernelGGL(k_mg_wbase, dim3(1), dim3(1024), 0, s, w);
-  hipLaunchKernelGGL(k_mg_finalize, dim3((unsigned)((w.N + 255) / 256)), dim3(256), 0, s, w, P,
-                     tok2macro);
+  if (!fin) {
+    hipLaunchKernelGGL(k_mg_wbase, dim3(1), dim3(1024), 0, s, w);
+    hipLaunchKernelGGL(k_mg_finalize, dim3((unsigned)((w.N + 255) / 256)), dim3(256), 0, s, w, o.P,
+                       o.tok2macro);
+  }
   const int nchunks = merge_nchunks(w.N, w.CH);
   if (dtype == 0) dispatch_ppt<0>(w, X, ldx, E, nchunks, s);
   else dispatch_ppt<1>(w, X, ldx, E, nchunks, s);
+  if (!fin && o.report)
+    hipLaunchKernelGGL(k_mg_report, dim3(1), dim3(1), 0, s, w.Mtot, o.err, o.report);
   return hipGetLastError();
 }
 

@@ -1119,11 +1119,9 @@ int slh_merge_async(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, float
   if (!emb_out || !pos_out) return fail(c, SLH_EINVAL, "NULL output");
   const int64_t need = capacity(c);
   if (cap < need) return fail(c, SLH_EINVAL, "cap %lld < required %lld", (long long)cap, (long long)need);
-  if (!norms_match(c, X, dtype, ldx))
-    if ((rc = prep_norms(c, X, dtype, ldx))) return rc;
   const int64_t L = window_len(c);
   const int64_t N = c->N;
-  const int CH = 16;
+  const int CH = merge_chunk(L);
   const int nch = merge_nchunks(N, CH);
   ENSURE(c, c->keyA, N * 4);
   ENSURE(c, c->keyB, N * 4);
@@ -1155,7 +1153,7 @@ int slh_merge_async(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, float
   w.N = N;
   w.route = P<uint8_t>(c->route);
   w.codes = P<uint32_t>(c->codes);
-  w.nrm_x = P<double>(c->nrm_x);
+  w.nrm_x = norms_match(c, X, dtype, ldx) ? P<double>(c->nrm_x) : nullptr;
   w.keyA = P<uint32_t>(c->keyA);
   w.keyB = P<uint32_t>(c->keyB);
   w.valA = P<int>(c->valA);
@@ -1205,15 +1203,17 @@ int slh_merge_async(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, float
     w.pre = P<long long>(c->mg_pre);
   }
   if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[7], c->stream));
-  HIP_TRY(c, launch_merge(w, X, dtype == SLH_BF16 ? 0 : 1, ldx, emb_out, pos_out, tok2macro_out,
-                          c->stream));
+  const int sl = (int)(c->mq_head & 1);
+  MergeOut o;
+  o.P = pos_out;
+  o.tok2macro = tok2macro_out;
+  o.report = c->mq_pin + 2 * sl;
+  o.err = c->lz_res ? P<unsigned>(c->lz_bar) + LZ_BAR_ERR : nullptr;
+  HIP_TRY(c, launch_merge(w, X, dtype == SLH_BF16 ? 0 : 1, ldx, emb_out, o, c->stream));
   HIP_TRY(c, launch_merge_tail(X, dtype == SLH_BF16 ? 0 : 1, ldx, (int)c->D, N, (int)c->keep_last,
                                P<int>(c->Mtot), c->compact, emb_out, pos_out, tok2macro_out,
                                c->stream));
   if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[8], c->stream));
-  const int sl = (int)(c->mq_head & 1);
-  HIP_TRY(c, launch_merge_report(P<int>(c->Mtot), c->lz_res ? P<unsigned>(c->lz_bar) + LZ_BAR_ERR : nullptr,
-                                 c->mq_pin + 2 * sl, c->stream));
   HIP_TRY(c, hipEventRecord(c->mq_ev[sl], c->stream));
   c->mq_res[sl] = c->lz_res;
   c->mq_keep[sl] = (int)c->keep_last;

@@ -175,7 +175,7 @@ struct MergeWS {
   int64_t N;
   const uint8_t* route;         // [n_win] 1 = spectral (device)
   const uint32_t* codes;        // [N]
-  const double* nrm_x;          // [N]
+  const double* nrm_x;          // [N] (NULL: taken from X while the rows are summed)
   uint32_t* keyA; uint32_t* keyB;  // [N] radix-sort keys
   int* valA; int* valB;            // [N] radix-sort values (token index)
   int* tmpi;                    // [N] representative flags / ranks (token order)
@@ -200,13 +200,19 @@ struct MergeWS {
   int* tg;                      // [N] exact target length: scratch
 };
 int merge_nchunks(int64_t N, int CH);
+int merge_chunk(int64_t L);              // CH for windows of L tokens
 // preserved suffix: tail tokens N .. N + K - 1 become macro-tokens *Mtot .. *Mtot + K - 1
-hipError_t launch_merge_report(const int* Mtot, const unsigned* err, unsigned* out, hipStream_t s);
 hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64_t N, int K,
                              const int* Mtot, int compact, float* E, int* P, int* tok2macro,
                              hipStream_t s);
-hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx,
-                        float* E, int* P, int* tok2macro, hipStream_t s);
+struct MergeOut {
+  int* P;
+  int* tok2macro;               // may be NULL
+  unsigned* report;             // pinned: M and *err (may be NULL)
+  const unsigned* err;          // the resident Lanczos kernel's error word (may be NULL: 0)
+};
+hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx, float* E,
+                        const MergeOut& o, hipStream_t s);
 
 // ---- adaptive routing (k_route.hip) ----
 // inv_x: 1 / |x_i| per row (0 for a zero row); part: n_win * route_slices(D) * 2

@@ -22,8 +22,8 @@ constexpr int64_t NA_NCH = (NA_NMAX + NA_CH - 1) / NA_CH;
 // byte offsets of the workspaces inside the array (each 256-byte aligned)
 constexpr int64_t na_al(int64_t b) { return (b + 255) & ~(int64_t)255; }
 constexpr int64_t NA_INTS = 0;                                   // 10 int arrays of NMAX
-constexpr int64_t NA_NRM = NA_INTS + na_al(10 * NA_NMAX * 4);    // nrm2_fm, nrm_x, inv_x (double)
-constexpr int64_t NA_RSC = NA_NRM + na_al(3 * NA_NMAX * 8);      // rowscale (float)
+constexpr int64_t NA_NRM = NA_INTS + na_al(10 * NA_NMAX * 4);    // not used (row norms: formed with the sums)
+constexpr int64_t NA_RSC = NA_NRM + na_al(3 * NA_NMAX * 8);      // not used
 constexpr int64_t NA_SMALL = NA_RSC + na_al(NA_NMAX * 4);        // mw, wbase[2], Mtot, route
 constexpr int64_t NA_PSEG = NA_SMALL + 256;                      // part_seg, part_cnt, part_end
 constexpr int64_t NA_PNS = NA_PSEG + na_al(3 * 2 * NA_NCH * 4);  // part_nsum (double)
@@ -75,7 +75,6 @@ extern "C" int slh_merge_noalloc(const void* X, int32_t dtype, int64_t ldx, int6
   unsigned char* b = (unsigned char*)base;
   hipStream_t s = (hipStream_t)stream;
   int* ints = (int*)(b + NA_INTS);
-  double* nrm = (double*)(b + NA_NRM);
   int* small = (int*)(b + NA_SMALL);
   int* pseg = (int*)(b + NA_PSEG);
   MergeWS w;
@@ -88,7 +87,7 @@ extern "C" int slh_merge_noalloc(const void* X, int32_t dtype, int64_t ldx, int6
   w.N = N;
   w.route = (const uint8_t*)(small + 4);
   w.codes = codes;
-  w.nrm_x = nrm + NA_NMAX;
+  w.nrm_x = nullptr;
   w.keyA = (uint32_t*)(ints + 0 * NA_NMAX);
   w.keyB = (uint32_t*)(ints + 1 * NA_NMAX);
   w.valA = ints + 2 * NA_NMAX;
@@ -116,11 +115,12 @@ extern "C" int slh_merge_noalloc(const void* X, int32_t dtype, int64_t ldx, int6
   // the window's route flag (spectral: every byte 1) by a fill kernel, not a
   // memset, so that the call may be captured into a graph
   if (launch_fill_u32((uint32_t*)(small + 4), 1, 0x01010101u, s) != hipSuccess) return SLH_EHIP;
-  if (launch_rownorm(X, dtype == SLH_BF16 ? 0 : 1, ldx, N, (int)D, 256, 0, nrm, nrm + NA_NMAX,
-                     nrm + 2 * NA_NMAX, (float*)(b + NA_RSC), nullptr, s) != hipSuccess)
-    return SLH_EHIP;
-  if (launch_merge(w, X, dtype == SLH_BF16 ? 0 : 1, ldx, emb_out, pos_out, tok2macro_out, s) !=
-      hipSuccess)
+  MergeOut o;
+  o.P = pos_out;
+  o.tok2macro = tok2macro_out;
+  o.report = nullptr;
+  o.err = nullptr;
+  if (launch_merge(w, X, dtype == SLH_BF16 ? 0 : 1, ldx, emb_out, o, s) != hipSuccess)
     return SLH_EHIP;
   int M = 0;
   if (hipMemcpyAsync(&M, w.Mtot, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return SLH_EHIP;
