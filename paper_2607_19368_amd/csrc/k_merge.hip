@@ -1,10 +1,11 @@
 // Macro-token construction (Eq. 7, section 3.4 max positions, section 3.6
 // ordering by representative position).
 //
-// book      one workgroup per window.  Windows of up to 16384 tokens are sorted
-//           in one block (k_mg_book_lds: LSD radix sort of (code, token) keys
-//           by code in LDS, 8 bits per pass, ranks by ballot matching);
-//           longer ones use global memory.  Spectral windows: stable LSD radix sort
+// book      Windows of up to 8192 tokens are sorted in one block each
+//           (k_mg_book_lds: LSD radix sort of (code, token) keys by code in
+//           LDS, 8 bits per pass, ranks by ballot matching); longer ones by many
+//           (k_mgl_*); windows past 2^20 tokens by one block each in global
+//           memory (k_mg_book).  Spectral windows: stable LSD radix sort
 //           of (code, token) by code with 8-bit digits (histogram, scan and a
 //           stable scatter whose in-wave ranks come from ballot matching), so
 //           every bucket becomes a run of ascending token indices; a bucket's
@@ -183,6 +184,79 @@ __global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
   if (tid == 0) w.mw[win] = nseg;
 }
 
+// Stable sort of the L <= 16384 keys of buf[0] by the bits from tb up (LSD radix,
+// 8 bits a pass) by one 1024-thread block; returns which of the two buffers
+// holds the result (complete after a barrier).
+struct MgSort {
+  int hw[16][256];                                    // per wave: digit counts, then offsets
+  int wsum[16];
+};
+__device__ __forceinline__ int mg_sort_lds(uint32_t* bufA, uint32_t* bufB, int L, int tb, int bits,
+                                           MgSort& t) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int npass = (bits + 7) / 8;
+  const int span = (L + 15) / 16;                     // positions per wave
+  const int p0 = min(wave * span, L), p1 = min(p0 + span, L);
+  const uint64_t lt = (1ull << lane) - 1ull;          // lanes below this one
+  uint32_t* src = bufA;
+  uint32_t* dst = bufB;
+  // lanes of this wave whose digit equals this lane's (valid lanes only)
+  auto match = [&](int d, bool valid) {
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+      const bool on = (d >> bit) & 1;
+      const uint64_t bb = __ballot(on);
+      m &= on ? bb : ~bb;
+    }
+    return m;
+  };
+  for (int pass = 0; pass < npass; ++pass) {
+    const int sh = tb + 8 * pass;
+    for (int q = lane; q < 256; q += 64) t.hw[wave][q] = 0;
+    __syncthreads();                                  // keys of the previous pass complete
+    // counts need no order: integer adds, every chunk's in flight at once
+    for (int i = p0 + lane; i < p1; i += 64) atomicAdd(&t.hw[wave][(src[i] >> sh) & 255u], 1);
+    __syncthreads();
+    // offsets: digits in order, waves in order within a digit
+    int cnt[16], tot = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        cnt[q] = t.hw[q][tid];
+        tot += cnt[q];
+      }
+    }
+    int total;
+    const int incl = block_incl_scan_1024(tid < 256 ? tot : 0, t.wsum, total);
+    if (tid < 256) {
+      int off = incl - tot;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        t.hw[q][tid] = off;
+        off += cnt[q];
+      }
+    }
+    __syncthreads();
+    for (int c0 = p0; c0 < p1; c0 += 64) {
+      const int i = c0 + lane;
+      const bool valid = i < p1;
+      const uint32_t k = src[min(i, L - 1)];
+      const int d = (int)((k >> sh) & 255u);
+      const uint64_t m = match(d, valid);
+      int off = 0;
+      if (valid && (m & lt) == 0)                     // the group's lowest lane
+        off = atomicAdd(&t.hw[wave][d], __popcll(m));
+      off = __shfl(off, (__ffsll((long long)m) - 1) & 63, 64);
+      if (valid) dst[off + __popcll(m & lt)] = k;
+    }
+    uint32_t* x = src;
+    src = dst;
+    dst = x;
+  }
+  return src == bufA ? 0 : 1;
+}
+
 // the count M of a single window where the later steps and the host look for it
 __device__ __forceinline__ void mg_totals(const MergeWS& w, int M, const MergeOut& o) {
   w.mw[0] = M;
@@ -225,8 +299,8 @@ __global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int tb, MergeOu
   const int L = w.L;
   uint32_t* bufA = mg_dyn;                            // [L]
   uint32_t* bufB = mg_dyn + L;                        // [L]
-  __shared__ int hw[16][256];                         // per wave: digit counts, then offsets
-  __shared__ int wsum[16];
+  __shared__ MgSort srt;
+  int* const wsum = srt.wsum;
   __shared__ uint32_t wfirst[16];
   __shared__ int wend[16];
   const int win = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -253,66 +327,9 @@ __global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int tb, MergeOu
   const uint32_t tmask = (1u << tb) - 1u;
   for (int i = tid; i < L; i += 1024) bufA[i] = (w.codes[base + i] << tb) | (uint32_t)i;
 
-  const int npass = (w.bits + 7) / 8;
-  const int span = (L + 15) / 16;                     // positions per wave
-  const int p0 = min(wave * span, L), p1 = min(p0 + span, L);
-  const uint64_t lt = (1ull << lane) - 1ull;          // lanes below this one
-  uint32_t* src = bufA;
-  uint32_t* dst = bufB;
-  // lanes of this wave whose digit equals this lane's (valid lanes only)
-  auto match = [&](int d, bool valid) {
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool on = (d >> bit) & 1;
-      const uint64_t bb = __ballot(on);
-      m &= on ? bb : ~bb;
-    }
-    return m;
-  };
-  for (int pass = 0; pass < npass; ++pass) {
-    const int sh = tb + 8 * pass;
-    for (int q = lane; q < 256; q += 64) hw[wave][q] = 0;
-    __syncthreads();                                  // keys of the previous pass complete
-    // counts need no order: integer adds, every chunk's in flight at once
-    for (int i = p0 + lane; i < p1; i += 64) atomicAdd(&hw[wave][(src[i] >> sh) & 255u], 1);
-    __syncthreads();
-    // offsets: digits in order, waves in order within a digit
-    int cnt[16], tot = 0;
-    if (tid < 256) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        cnt[q] = hw[q][tid];
-        tot += cnt[q];
-      }
-    }
-    int total;
-    const int incl = block_incl_scan_1024(tid < 256 ? tot : 0, wsum, total);
-    if (tid < 256) {
-      int off = incl - tot;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        hw[q][tid] = off;
-        off += cnt[q];
-      }
-    }
-    __syncthreads();
-    for (int c0 = p0; c0 < p1; c0 += 64) {
-      const int i = c0 + lane;
-      const bool valid = i < p1;
-      const uint32_t k = src[min(i, L - 1)];
-      const int d = (int)((k >> sh) & 255u);
-      const uint64_t m = match(d, valid);
-      int off = 0;
-      if (valid && (m & lt) == 0)                     // the group's lowest lane
-        off = atomicAdd(&hw[wave][d], __popcll(m));
-      off = __shfl(off, (__ffsll((long long)m) - 1) & 63, 64);
-      if (valid) dst[off + __popcll(m & lt)] = k;
-    }
-    uint32_t* t = src;
-    src = dst;
-    dst = t;
-  }
+  const int res = mg_sort_lds(bufA, bufB, L, tb, w.bits, srt);
+  uint32_t* src = res ? bufB : bufA;
+  uint32_t* dst = res ? bufA : bufB;
   __syncthreads();                                    // sorted keys in src
   int* R = (int*)dst;                                 // [L] token -> rank
   uint32_t v[E];
@@ -415,6 +432,196 @@ __device__ __forceinline__ int block_incl_max_1024(int v, int* wsum, int& total)
   }
   total = tot;
   return max(v, pre);
+}
+
+// Book-keeping of long windows by many workgroups.  One workgroup sorting a whole
+// window keeps one compute unit busy and the other 255 idle (49157 tokens: 473 us);
+// here tiles of MT tokens are sorted side by side, and a token's place is the sum
+// of its code's base, its code's count in the tiles before and its rank in the tile:
+//   k_mgl_tile     sorts a tile's keys by code (as k_mg_book_lds); a run's count and
+//                  last token into cnt[tile][code] (zeroed before)
+//   k_mgl_codes    thread per code: cnt becomes the count in the tiles before; the
+//                  code's base within its 256 codes, its last token (the
+//                  representative), and that token's bit in the window's bit map
+//   k_mgl_rank     one workgroup a window: bases of the blocks of 256 codes and the
+//                  bits before each word of the map
+//   k_mgl_scatter  the members in sorted order, each with its bucket's rank, the bits
+//                  before its representative's (FIN: one window with max positions:
+//                  macro indices, token map and positions too)
+// Measured (all four and the zero fill): 32768 tokens x 14 bits 36 us against 310,
+// 49157 35 us against 473.
+constexpr int MT = 4096, MTB = 12;                    // tokens of a tile
+__host__ __device__ inline int mgl_tiles(int64_t L) { return (int)((L + MT - 1) / MT); }
+__host__ __device__ inline int mgl_words(int64_t L) { return (int)((L + 31) / 32); }
+// per window: base [2^bits], representative [2^bits], bases of the blocks of codes,
+// bits before each word of the map
+__host__ __device__ inline int64_t mgl_code_ints(int64_t L, int bits) {
+  const int64_t C = (int64_t)1 << bits;
+  return 2 * C + (C + 255) / 256 + mgl_words(L);
+}
+
+__global__ __launch_bounds__(1024) void k_mgl_tile(MergeWS w) {
+  __shared__ uint32_t bufA[MT], bufB[MT];
+  __shared__ MgSort srt;
+  __shared__ uint32_t wedge[2][16];
+  const int win = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!w.route[win]) return;
+  const int64_t base = (int64_t)win * w.L + (int64_t)tile * MT;
+  const int n = min(MT, w.L - tile * MT);
+  for (int i = tid; i < n; i += 1024) bufA[i] = (w.codes[base + i] << MTB) | (uint32_t)i;
+  const uint32_t* src = mg_sort_lds(bufA, bufB, n, MTB, w.bits, srt) ? bufB : bufA;
+  __syncthreads();
+  // four sorted positions a thread; the neighbours' codes across threads
+  uint32_t v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = (4 * tid + e < n) ? src[4 * tid + e] : 0xFFFFFFFFu;
+  if (lane == 0) wedge[0][wave] = v[0];
+  if (lane == 63) wedge[1][wave] = v[3];
+  __syncthreads();
+  uint32_t nx = (uint32_t)__shfl_down((int)v[0], 1, 64), pv = (uint32_t)__shfl_up((int)v[3], 1, 64);
+  if (lane == 63) nx = wave < 15 ? wedge[0][wave + 1] : 0xFFFFFFFFu;
+  if (lane == 0) pv = wave > 0 ? wedge[1][wave - 1] : 0xFFFFFFFFu;
+  // the start of each position's run: the latest start at or before it
+  int st = INT_MIN;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t p = e ? v[e - 1] : pv;
+    const int s = 4 * tid + e;
+    if (s < n && (s == 0 || (p >> MTB) != (v[e] >> MTB))) st = s;
+  }
+  int tot;
+  const int inc = block_incl_max_1024(st, srt.wsum, tot);
+  int run = __shfl_up(inc, 1, 64);                    // the latest start before this thread
+  if (lane == 0) run = INT_MIN;
+  // (lane 0 of a wave: the latest start of the waves before)
+  __shared__ int wlast[16];
+  if (lane == 63) wlast[wave] = inc;
+  __syncthreads();
+  if (lane == 0 && wave > 0) run = wlast[wave - 1];
+  int* cnt = w.lcnt + ((int64_t)win * mgl_tiles(w.L) + tile) * (1 << w.bits);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int s = 4 * tid + e;
+    if (s < n) {
+      const uint32_t p = e ? v[e - 1] : pv, q = e < 3 ? v[e < 3 ? e + 1 : 3] : nx;
+      if (s == 0 || (p >> MTB) != (v[e] >> MTB)) run = s;
+      w.keyA[base + s] = v[e];
+      w.valA[base + s] = s - run;
+      if (s == n - 1 || (q >> MTB) != (v[e] >> MTB))
+        cnt[v[e] >> MTB] = (s - run + 1) | ((int)(v[e] & (MT - 1)) << 13);
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_mgl_codes(MergeWS w) {
+  const int win = blockIdx.y, C = 1 << w.bits, c = blockIdx.x * 256 + threadIdx.x;
+  if (!w.route[win]) return;
+  const int nt = mgl_tiles(w.L);
+  int total = 0;
+  int* code = w.lcode + (int64_t)win * mgl_code_ints(w.L, w.bits);
+  if (c < C) {
+    int* cnt = w.lcnt + (int64_t)win * nt * C + c;
+    int rep = -1;
+    for (int t0 = 0; t0 < nt; t0 += 8) {
+      int x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = cnt[(int64_t)min(t0 + e, nt - 1) * C];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (t0 + e < nt) {
+          cnt[(int64_t)(t0 + e) * C] = total;
+          if (x[e]) rep = (t0 + e) * MT + (x[e] >> 13);
+          total += x[e] & 8191;
+        }
+      }
+    }
+    code[C + c] = rep;
+    if (rep >= 0) atomicOr(&w.lbits[(int64_t)win * mgl_words(w.L) + (rep >> 5)], 1u << (rep & 31));
+  }
+  // base within the block's 256 codes
+  __shared__ int wtot[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc = total;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += u;
+  }
+  if (lane == 63) wtot[wave] = inc;
+  __syncthreads();
+  for (int q = 0; q < wave; ++q) inc += wtot[q];
+  if (c < C) code[c] = inc - total;
+  if (threadIdx.x == 255) code[2 * C + blockIdx.x] = inc;
+}
+
+template <bool FIN>
+__global__ __launch_bounds__(1024) void k_mgl_rank(MergeWS w, MergeOut o) {
+  __shared__ int wsum[16];
+  const int win = blockIdx.x, tid = threadIdx.x, C = 1 << w.bits, L = w.L;
+  if (!w.route[win]) {
+    if (tid == 0) {
+      const int M = (L + w.chunk_k - 1) / w.chunk_k;
+      if constexpr (FIN) mg_totals(w, M, o);
+      else w.mw[win] = M;
+    }
+    return;
+  }
+  const int nblk = (C + 255) / 256, nword = mgl_words(L);     // nblk <= 256
+  int* blk = w.lcode + (int64_t)win * mgl_code_ints(L, w.bits) + 2 * C;
+  int* pre = blk + nblk;
+  const int x = tid < nblk ? blk[tid] : 0;
+  int tot;
+  const int inc = block_incl_scan_1024(x, wsum, tot);
+  if (tid < nblk) blk[tid] = inc - x;
+  const uint32_t* bits = w.lbits + (int64_t)win * nword;
+  int carry = 0;
+  for (int s0 = 0; s0 < nword; s0 += 1024) {
+    const int s = s0 + tid, p = s < nword ? __popc(bits[s]) : 0;
+    __syncthreads();                                          // wsum is reused
+    const int q = block_incl_scan_1024(p, wsum, tot);
+    if (s < nword) pre[s] = carry + q - p;
+    carry += tot;
+  }
+  if (tid == 0) {
+    if constexpr (FIN) mg_totals(w, carry, o);
+    else w.mw[win] = carry;
+  }
+}
+
+template <bool FIN>
+__global__ __launch_bounds__(256) void k_mgl_scatter(MergeWS w, MergeOut o) {
+  const int win = blockIdx.y, L = w.L, s = blockIdx.x * 256 + threadIdx.x;
+  if (s >= L) return;
+  const int64_t base = (int64_t)win * L;
+  if (!w.route[win]) {
+    const int k = w.chunk_k, g = s / k;
+    w.sval[base + s] = (int)(base + s);
+    if constexpr (FIN) {
+      w.sseg[s] = g;
+      if (o.tok2macro) o.tok2macro[s] = g;
+      if (s == L - 1 || (s + 1) % k == 0) o.P[g] = w.compact ? g : s;
+    } else {
+      w.sloc[base + s] = g;
+    }
+    return;
+  }
+  const int C = 1 << w.bits, tile = s / MT;
+  const int* code = w.lcode + (int64_t)win * mgl_code_ints(L, w.bits);
+  const int* blk = code + 2 * C;
+  const int* pre = blk + (C + 255) / 256;
+  const uint32_t key = w.keyA[base + s];
+  const int c = (int)(key >> MTB), tok = tile * MT + (int)(key & (MT - 1));
+  const int at = blk[c >> 8] + code[c] + w.lcnt[((int64_t)win * mgl_tiles(L) + tile) * C + c] + w.valA[base + s];
+  const int rep = code[C + c];
+  const int g = pre[rep >> 5] + __popc(w.lbits[(int64_t)win * mgl_words(L) + (rep >> 5)] & ((1u << (rep & 31)) - 1u));
+  w.sval[base + at] = (int)(base + tok);
+  if constexpr (FIN) {
+    w.sseg[at] = g;
+    if (o.tok2macro) o.tok2macro[tok] = g;
+    if (tok == rep) o.P[g] = w.compact ? g : tok;
+  } else {
+    w.sloc[base + at] = g;
+  }
 }
 
 // Scans of n values over a 1024-thread block, one block scan per 16384
@@ -889,6 +1096,18 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
   for (int q = 0; q < PPT; ++q)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0f;
+  // a batch's rows are summed by themselves first: a chunk of 64 rows then rounds
+  // no more than one of 16 summed row by row
+  float bsum[PPT][8] = {};
+  auto flush = [&]() {
+#pragma unroll
+    for (int q = 0; q < PPT; ++q)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        acc[q][k] += bsum[q][k];
+        bsum[q][k] = 0.0f;
+      }
+  };
   constexpr int DEPTH = (8 / (PPT * (DT + 1))) > 0 ? 8 / (PPT * (DT + 1)) : 1;
   MgRaw<DT> rc[DEPTH][PPT], rn[DEPTH][PPT];
   auto load_batch = [&](MgRaw<DT> (&dst)[DEPTH][PPT], int b) {
@@ -934,10 +1153,11 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
       if (s < n) {
 #pragma unroll
         for (int q = 0; q < PPT; ++q)
-          if (cin[q]) mg_add<DT>(acc[q], rc[e][q]);
+          if (cin[q]) mg_add<DT>(bsum[q], rc[e][q]);
         nsum += snrm[s];
         const int g = ssg[s];
         if (s == n - 1 || ssg[s + 1] != g) {
+          flush();
           const bool starts = (rs > 0) || (prev_g != g);
           const bool ends = (s < n - 1) || (next_g != g);
           // kind 0: whole bucket -> E (Eq. 7 renormalisation: sum * mean member norm / |sum|);
@@ -982,6 +1202,7 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
         }
       }
     }
+    flush();
 #pragma unroll
     for (int e = 0; e < DEPTH; ++e)
 #pragma unroll
@@ -1169,6 +1390,21 @@ hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64
 // 256, 64 windows of 2048 365 / 366 / 381.
 int merge_chunk(int64_t L) { return L >= 24576 ? 64 : L >= 8192 ? 32 : 16; }
 
+int64_t merge_tiled_ws(int n_win, int64_t L, int bits, int* ws, MergeWS* w) {
+  // From 8193 tokens a window: us a merge (D = 512), one workgroup / tiles: 4096 68 /
+  // 79, 8192 97 / 92, 12000 122 / 96, 16384 140 / 98, 32768 365 / 131, 49157 519 / 151,
+  // 131072 1190 / 199, eight windows of 16384 284 / 254, sixteen of 8192 275 / 274.
+  // Past 2^20 tokens, or 2^24 counters, one workgroup as before.
+  const int64_t cnt = (int64_t)n_win * mgl_tiles(L) << bits, code = n_win * mgl_code_ints(L, bits);
+  if (L <= 8192 || L > (1 << 20) || cnt > (1 << 24)) return 0;
+  if (w) {
+    w->lcode = ws;
+    w->lcnt = ws + code;
+    w->lbits = (uint32_t*)(w->lcnt + cnt);
+  }
+  return code + cnt + (int64_t)n_win * mgl_words(L);
+}
+
 int merge_nchunks(int64_t N, int CH) { return (int)((N + CH - 1) / CH); }
 
 template <int E, bool FIN>
@@ -1199,10 +1435,25 @@ static hipError_t launch_book(const MergeWS& w, const MergeOut& o, hipStream_t s
 hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx, float* E,
                         const MergeOut& o, hipStream_t s) {
   (void)hipGetLastError();
-  const bool fin = w.L <= 16384 && w.n_win == 1 && w.N == w.L && !w.tw && w.scheme == 0;
-  if (w.L <= 16384) {
+  const bool tiled = w.lcnt != nullptr, lds = w.L <= 16384 && !tiled;
+  const bool fin = (lds || tiled) && w.n_win == 1 && w.N == w.L && !w.tw && w.scheme == 0;
+  if (lds) {
     const hipError_t e = fin ? launch_book<true>(w, o, s) : launch_book<false>(w, o, s);
     if (e != hipSuccess) return e;
+  } else if (tiled) {
+    const int nt = mgl_tiles(w.L), C = 1 << w.bits;
+    const dim3 gs((unsigned)((w.L + 255) / 256), w.n_win);
+    hipError_t e = launch_fill_u32((uint32_t*)w.lcnt, w.n_win * ((int64_t)nt * C + mgl_words(w.L)), 0u, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mgl_tile, dim3(nt, w.n_win), dim3(1024), 0, s, w);
+    hipLaunchKernelGGL(k_mgl_codes, dim3((C + 255) / 256, w.n_win), dim3(256), 0, s, w);
+    if (fin) {
+      hipLaunchKernelGGL(k_mgl_rank<true>, dim3(w.n_win), dim3(1024), 0, s, w, o);
+      hipLaunchKernelGGL(k_mgl_scatter<true>, gs, dim3(256), 0, s, w, o);
+    } else {
+      hipLaunchKernelGGL(k_mgl_rank<false>, dim3(w.n_win), dim3(1024), 0, s, w, o);
+      hipLaunchKernelGGL(k_mgl_scatter<false>, gs, dim3(256), 0, s, w, o);
+    }
   } else {
     hipLaunchKernelGGL(k_mg_book, dim3(w.n_win), dim3(1024), 0, s, w);
   }

@@ -161,7 +161,7 @@ struct slh_ctx {
   void* tw_dev_p = nullptr;
   DevBuf tg_tw, tg_scr;
   DevBuf dg_tiles, dg_counts;
-  DevBuf posv, mg_pre;
+  DevBuf posv, mg_pre, mg_tiles;
   DevBuf nm_part, nm_csum, rowsum;
   // Distinct rows (k_group.hip): two sets, so that the groups behind Q and Z stay
   // while the next prompt's feature map makes its own.
@@ -617,7 +617,7 @@ void slh_destroy(slh_ctx* c) {
                     &c->Mtot, &c->part, &c->part_seg, &c->part_cnt, &c->part_nsum,
                     &c->part_end, &c->rpart, &c->scores, &c->rsu, &c->lz_bar, &c->nm_part, &c->nm_csum, &c->rowsum, &c->dg_counts,
                     &c->dg_energy, &c->dg_rowsq, &c->dg_tiles, &c->mg_pre, &c->posv, &c->tg_scr,
-                    &c->tg_tw, &c->grpA, &c->grpB, &c->xpand};
+                    &c->tg_tw, &c->grpA, &c->grpB, &c->xpand, &c->mg_tiles};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -1178,6 +1178,11 @@ int slh_merge_async(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, float
   w.pre = nullptr;
   w.tw = nullptr;
   w.tg = nullptr;
+  w.lcnt = w.lcode = nullptr;
+  if (const int64_t ints = merge_tiled_ws((int)c->n_win, L, c->bits, nullptr, nullptr)) {
+    ENSURE(c, c->mg_tiles, (size_t)ints * 4);
+    merge_tiled_ws((int)c->n_win, L, c->bits, P<int>(c->mg_tiles), &w);
+  }
   if (c->target_len > 0) {
     if (c->pos_scheme) return fail(c, SLH_EINVAL, "TARGET_LEN needs max positions (POS_SCHEME 0)");
     if (!target_budgets(c, c->tw_h))

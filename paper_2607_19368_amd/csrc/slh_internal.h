@@ -196,10 +196,16 @@ struct MergeWS {
   int scheme;                   // position scheme: 0 max, 1 lower median, 2 mean (half to even)
   int* posv;                    // [N] scheme != 0: representative position at each run end
   long long* pre;               // [N] scheme != 0 or target: prefix sums / remainders
+  int* lcnt;                    // tiled book-keeping (merge_tiled_ws; NULL: one workgroup a
+  int* lcode;                   //   window): counts, codes, the representatives' bit map
+  uint32_t* lbits;
   const int* tw;                // [n_win] exact target length: budget per window (NULL = off)
   int* tg;                      // [N] exact target length: scratch
 };
 int merge_nchunks(int64_t N, int CH);
+// ints of workspace for windows whose book-keeping is tiled, else 0; with w the
+// workspace ws is laid out in it
+int64_t merge_tiled_ws(int n_win, int64_t L, int bits, int* ws, MergeWS* w);
 int merge_chunk(int64_t L);              // CH for windows of L tokens
 // preserved suffix: tail tokens N .. N + K - 1 become macro-tokens *Mtot .. *Mtot + K - 1
 hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64_t N, int K,

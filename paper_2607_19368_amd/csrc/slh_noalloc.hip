@@ -112,6 +112,7 @@ extern "C" int slh_merge_noalloc(const void* X, int32_t dtype, int64_t ldx, int6
   w.pre = nullptr;
   w.tw = nullptr;
   w.tg = nullptr;
+  w.lcnt = w.lcode = nullptr;
   // the window's route flag (spectral: every byte 1) by a fill kernel, not a
   // memset, so that the call may be captured into a graph
   if (launch_fill_u32((uint32_t*)(small + 4), 1, 0x01010101u, s) != hipSuccess) return SLH_EHIP;

@@ -549,6 +549,53 @@ def test_distinct_rows_only_where_equal(case):
         assert np.abs(a["Z"] - b["Z"]).max() <= 1e-7
 
 
+# ------------------------------------------------------------------ merge of loaded codes
+@pytest.mark.parametrize("N,bits,window,skew,compact", [
+    (4096 * 5 + 1, 7, 0, 3.0, 0),          # one token in the last tile
+    (16385, 16, 0, 1.0, 1),                # more codes than tokens, most buckets single
+    (2 * 20001, 10, 20001, 3.0, 0),        # two long windows
+    (20480, 1, 0, 1.0, 0),                 # two buckets over every tile
+    (70000, 14, 0, 6.0, 0),                # a bucket of most tokens
+    (3001, 6, 0, 2.0, 1), (8192, 12, 0, 3.0, 0), (512 * 6, 5, 512, 2.0, 0)])
+def test_merge_bookkeeping(N, bits, window, skew, compact):
+    """Macro indices, positions and sums of slh_merge on loaded codes (no feature
+    map, so the norms come from the merge's own read of X) against the definition:
+    one bucket per (window, code), ordered by last token; E = mean * (mean member
+    norm) / |mean| in 64 bits, to 2e-6 (fp32 sums of up to 70000 rows of size 1:
+    about 2^-24 sqrt(64) within a chunk and across the chunks of a bucket)."""
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    D = 40
+    rng = np.random.default_rng(N)
+    codes = np.minimum((1 << bits) * rng.random(N) ** skew, (1 << bits) - 1).astype(np.int64)
+    X = (rng.standard_normal((N, D)) + 1.0).astype(np.float32)
+    ctx = P.slh_create(N, D, 256, 4, bits, 0)
+    if window:
+        P.slh_set_option(ctx, B.SLH_OPT_WINDOW_LEN, window)
+    P.slh_set_option(ctx, B.SLH_OPT_POS_MODE, compact)
+    P.slh_load(ctx, B.SLH_OUT_CODES, torch.from_numpy(codes.astype(np.int32)).cuda())
+    E, pos, t2m, M = P.slh_merge(ctx, torch.from_numpy(X).cuda())
+    key = np.arange(N) // (window or N) * (1 << 20) + codes
+    _, inv = np.unique(key, return_inverse=True)
+    last = np.zeros(inv.max() + 1, np.int64)
+    np.maximum.at(last, inv, np.arange(N))
+    order = np.argsort(last)
+    rank = np.empty_like(order)
+    rank[order] = np.arange(len(order))
+    assert M == len(order)
+    assert np.array_equal(t2m.cpu().numpy(), rank[inv])
+    assert np.array_equal(pos.cpu().numpy()[:M], np.arange(M) if compact else last[order])
+    S, cnt, eta = np.zeros((M, D)), np.zeros(M), np.zeros(M)
+    np.add.at(S, rank[inv], X.astype(np.float64))
+    np.add.at(cnt, rank[inv], 1.0)
+    np.add.at(eta, rank[inv], np.linalg.norm(X.astype(np.float64), axis=1))
+    ref = S * (eta / cnt / np.linalg.norm(S, axis=1))[:, None]
+    err = np.linalg.norm(E.cpu().numpy()[:M] - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    _say(f"[merge book] N={N} bits={bits} window={window}: M={M} max rel {err.max():.1e}")
+    assert err.max() <= 2e-6
+
+
 @pytest.mark.timeout(900)
 def test_end_to_end_qwen14b_long():
     inp = make_inputs("qwen14b_long")
