@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -186,6 +187,76 @@ struct slh_ctx {
 };
 
 namespace {
+
+// Resident Lanczos kernels of different streams must not run at once: each needs
+// all of its blocks on the chip, and two that each hold part of it would wait for
+// blocks that cannot start until their bounded waits gave up.  Per device, the live
+// contexts; where their streams differ, a resident launch waits for the event of
+// the one before it.  With one stream (its kernels run in order) no event is made.
+struct ResidentGate {
+  std::mutex mu;
+  std::vector<slh_ctx*> live;
+  hipEvent_t ev = nullptr;          // after the last resident launch made with several streams
+  hipStream_t last = nullptr;
+  bool recorded = false;
+  bool settle = false;              // launches without an event may be in flight
+};
+constexpr int GATE_DEVICES = 64;
+ResidentGate gates[GATE_DEVICES];
+ResidentGate* gate_of(const slh_ctx* c) {
+  return c->device >= 0 && c->device < GATE_DEVICES ? &gates[c->device] : nullptr;
+}
+void gate_enter(slh_ctx* c) {
+  if (ResidentGate* g = gate_of(c)) {
+    std::lock_guard<std::mutex> lk(g->mu);
+    g->live.push_back(c);
+    g->settle = g->settle || g->live.size() > 1;
+  }
+}
+void gate_leave(slh_ctx* c) {
+  if (ResidentGate* g = gate_of(c)) {
+    std::lock_guard<std::mutex> lk(g->mu);
+    g->live.erase(std::remove(g->live.begin(), g->live.end(), c), g->live.end());
+  }
+}
+void gate_stream(slh_ctx* c, hipStream_t s) {
+  ResidentGate* g = gate_of(c);
+  if (!g) {
+    c->stream = s;
+    return;
+  }
+  std::lock_guard<std::mutex> lk(g->mu);
+  if (c->stream != s && g->live.size() > 1) g->settle = true;
+  c->stream = s;
+}
+// launch() between the waits and records that the contexts' streams call for
+template <class F>
+hipError_t gate_resident(slh_ctx* c, F launch) {
+  ResidentGate* g = gate_of(c);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!g) return launch();
+  std::lock_guard<std::mutex> lk(g->mu);
+  bool several = false;
+  for (const slh_ctx* o : g->live) several = several || o->stream != c->stream;
+  if (!several) return launch();
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return launch();
+  }
+  hipError_t e = hipSuccess;
+  if (g->settle) {
+    e = hipDeviceSynchronize();
+    g->settle = e != hipSuccess;
+    g->recorded = false;
+  }
+  if (e == hipSuccess && !g->ev) e = hipEventCreateWithFlags(&g->ev, hipEventDisableTiming);
+  if (e == hipSuccess && g->recorded && g->last != c->stream) e = hipStreamWaitEvent(c->stream, g->ev, 0);
+  if (e == hipSuccess) e = launch();
+  if (e == hipSuccess) e = hipEventRecord(g->ev, c->stream);
+  g->recorded = e == hipSuccess;
+  g->last = c->stream;
+  return e;
+}
 
 int fail(slh_ctx* c, int code, const char* fmt, ...) {
   char buf[512];
@@ -482,10 +553,8 @@ int64_t capacity(const slh_ctx* c) {
 // synchronised across queues).  Returns the first launch error (the capture
 // is ended by the caller in every case).
 hipError_t launch_lanczos_graph_body(slh_ctx* c, const LanczosWS& w, const double* q1act, int na,
-                                 int n_it, int L, bool res) {
-  hipError_t e = res ? launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu,
-                                               c->cap_stream)
-                     : launch_lanczos(w, q1act, c->cap_stream);
+                                 int n_it, int L) {
+  hipError_t e = launch_lanczos(w, q1act, c->cap_stream);
   if (e == hipSuccess)
     e = launch_eigh_ritz(w.alpha, w.beta, w.neff, na, n_it, c->r, P<double>(c->theta),
                          P<double>(c->Seig), w.Q, L, w.ldq, P<double>(c->Z), c->n_cu, c->cap_stream);
@@ -600,12 +669,14 @@ int slh_create(slh_ctx** out, int64_t N, int64_t D, int64_t m, int32_t r, int32_
     slh_destroy(c);
     return SLH_EHIP;
   }
+  gate_enter(c);
   *out = c;
   return SLH_OK;
 }
 
 void slh_destroy(slh_ctx* c) {
   if (!c) return;
+  gate_leave(c);
   if (c->mq_head != c->mq_tail) (void)hipStreamSynchronize(c->stream);   // merges still in flight
   drop_graph(c);
   DevBuf* bufs[] = {&c->Wt, &c->psi, &c->R, &c->q1all, &c->q1act, &c->winlist, &c->route,
@@ -730,7 +801,7 @@ int slh_set_option(slh_ctx* c, int32_t key, double v) {
 
 int slh_set_stream(slh_ctx* c, void* s) {
   if (!c) return SLH_EINVAL;
-  c->stream = (hipStream_t)s;
+  gate_stream(c, (hipStream_t)s);
   return SLH_OK;
 }
 
@@ -976,8 +1047,10 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
         if (rc_ev) return rc_ev;
         HIP_TRY(c, hipEventRecord(c->ev[2], c->stream));
         if (res)
-          HIP_TRY(c, launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
-                                             c->ev_fb[0], c->ev_fa[0]));
+          HIP_TRY(c, gate_resident(c, [&] {
+            return launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
+                                           c->ev_fb[0], c->ev_fa[0]);
+          }));
         else
           HIP_TRY(c, launch_lanczos(w, q1act, c->stream, c->ev_fb.data(), c->ev_fa.data()));
         HIP_TRY(c, hipEventRecord(c->ev[3], c->stream));
@@ -990,8 +1063,10 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
         // graph costs a gap before the stream's next kernel.  Grouped rows: their
         // number is the prompt's own, so a graph would be captured for every one.
         if (res)
-          HIP_TRY(c, launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
-                                             nullptr, nullptr));
+          HIP_TRY(c, gate_resident(c, [&] {
+            return launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,
+                                           nullptr, nullptr);
+          }));
         else
           HIP_TRY(c, launch_lanczos(w, q1act, c->stream));
         HIP_TRY(c, launch_eigh_ritz(w.alpha, w.beta, w.neff, na, n_it, c->r, P<double>(c->theta),
@@ -1002,14 +1077,13 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
         // per configuration and replayed as one graph.
         std::string key((const char*)&w, sizeof w);
         key.append((const char*)&q1act, sizeof q1act);
-        key.append(res ? "r" : "s");
         const void* outs[3] = {c->theta.p, c->Seig.p, c->Z.p};   // the eigensolve's outputs
         key.append((const char*)outs, sizeof outs);
         if (!c->lz_exec || c->lz_key != key) {
           drop_graph(c);
           hipGraph_t g = nullptr;
           HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-          hipError_t le = launch_lanczos_graph_body(c, w, q1act, na, n_it, (int)L, res);
+          hipError_t le = launch_lanczos_graph_body(c, w, q1act, na, n_it, (int)L);
           hipError_t ee = hipStreamEndCapture(c->cap_stream, &g);
           if (le != hipSuccess || ee != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
@@ -1369,7 +1443,9 @@ int slh_time_passes(slh_ctx* c, int32_t reps, double* us_out) {
     if (e == hipSuccess) e = hipEventCreate(&r1);
     double tot = 0.0;
     for (int q = 0; q < reps && e == hipSuccess; ++q) {
-      e = launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream, r0, r1);
+      e = gate_resident(c, [&] {
+        return launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream, r0, r1);
+      });
       if (e == hipSuccess) e = hipEventSynchronize(r1);
       float ms = 0.f;
       if (e == hipSuccess) e = hipEventElapsedTime(&ms, r0, r1);

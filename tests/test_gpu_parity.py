@@ -435,6 +435,44 @@ def test_resident_shapes_match_streaming(N, m, n_it, window):
         assert da <= 1e-8 and db <= 1e-8
 
 
+@pytest.mark.timeout(120)
+def test_resident_contexts_on_several_streams():
+    """Contexts of two threads on streams of their own, each with a window that fills
+    the chip: their resident kernels take turns (neither could finish while the
+    other holds part of the chip), and every run gives the bits of a run alone."""
+    import threading
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    N, m, n_it = 8192, 2048, 24
+    X = 0.06 * torch.randn((N, 64), generator=torch.Generator().manual_seed(5)).cuda()
+    ctx = P.slh_create(N, 64, m, 4, 4, 0)
+    P.slh_feature_map(ctx, X)
+    want = P.slh_lanczos(ctx, n_it)[0]
+    torch.cuda.synchronize()
+    got, errs = [], []
+
+    def work():
+        try:
+            s = torch.cuda.Stream()
+            c = P.slh_create(N, 64, m, 4, 4, 0)
+            P.slh_set_stream(c, s)
+            for _ in range(6):
+                P.slh_feature_map(c, X)
+                got.append(P.slh_lanczos(c, n_it)[0])
+            s.synchronize()
+        except Exception as e:  # reported by the main thread
+            errs.append(e)
+
+    ts = [threading.Thread(target=work) for _ in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errs, errs
+    assert len(got) == 12 and all(np.array_equal(g, want) for g in got)
+
+
 # ------------------------------------------------------------------ distinct rows
 def _repeating_rows(N, D, distinct, seed):
     """N bf16 rows that hold `distinct` different ones, a few of them very often."""
