@@ -110,6 +110,33 @@ __device__ __forceinline__ bool ld_wait(ADDR addr, unsigned act, int e, unsigned
   return ok;
 }
 
+// v = p[0], p[1], q[0], q[1] of step e (16-byte aligned pairs), as ld_wait
+__device__ __forceinline__ bool ld_wait_pairs(double* p, double* q, int e, unsigned* bar, int spin,
+                                              double (&v)[4]) {
+  typedef long long ll2 __attribute__((ext_vector_type(2)));
+  ll2 x, y;
+  bool ok = true;
+  for (int s = 0;; ++s) {
+    // loads and their wait in one statement: their registers are written when it ends
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %3, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(x), "=&v"(y)
+                 : "v"(p), "v"(q)
+                 : "memory");
+    if (tag_is(x.x, e) && tag_is(x.y, e) && tag_is(y.x, e) && tag_is(y.y, e)) break;
+    if (s > spin || ((s & 63) == 63 && ld_flag(bar + LR_ERR) != 0)) {
+      st_flag(bar + LR_ERR, 1u);
+      ok = false;
+      break;
+    }
+  }
+  v[0] = __longlong_as_double(x.x);
+  v[1] = __longlong_as_double(x.y);
+  v[2] = __longlong_as_double(y.x);
+  v[3] = __longlong_as_double(y.y);
+  return ok;
+}
+
 // Sum over the lanes at distances CB, 2 CB, ... 32 (CB a power of two >= 4; the
 // same bits in every lane of the sum)
 __device__ __forceinline__ double strided_sum(double v, int CB) {
@@ -174,8 +201,8 @@ __device__ __forceinline__ void launder_rows(float4 (&ph)[RW]) {
 }  // namespace
 
 // NS = m / 256 column slices and P row subsets: wave (sl, p) of the NW = NS P
-// waves holds RW rows of the block's RB = P RW rows, 4 columns a lane (columns
-// 256 sl + 4 lane + e), at most 128 floats a lane.
+// waves holds RW rows of the block's RB = P RW rows, 4 columns a lane, at most 128
+// floats a lane.
 // Workspace use per window: Spart [m / CB][nb][CB] (CB = 2^cbl: columns per
 // owner, the smallest power of two >= 4 with CB nb >= m, so that blocks
 // b < m / CB own the columns), H2part [nb][ldq + 1], H2 [ldq + 1], T [C][m] with
@@ -221,7 +248,10 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
   // SPIN: the wait limit from w.spin (SLH_OPT_WAIT_POLLS), else the constant
   const int spin = SPIN ? (w.spin > 0 ? w.spin : LR_SPIN) : LR_SPIN;
   const int r0 = b * RB;
-  const int cb = 256 * sl + 4 * lane;
+  // the lane's columns: c0, c0 + 1, c1, c1 + 1, so that a wave's 16-byte stores of
+  // partials and loads of t cover whole lines (four columns in a row: half of each
+  // 32 bytes per instruction; 8192 x 2048 10.6 -> 9.5 us a step)
+  const int c0 = 256 * sl + 2 * lane, c1 = c0 + 128;
   extern __shared__ float4 res_dyn[];
   float4* const lrow = res_dyn;                  // [RL][m / 4]
   double* const Qs = (double*)(res_dyn + RL * (m / 4));   // [n_it + 1][QS]
@@ -248,10 +278,14 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
   // their weights
   float4 ph[RW];
   {
-    const float* src = w.Phi + (int64_t)a * L * m + cb;
+    const float* src = w.Phi + (int64_t)a * L * m + c0;
+    auto load4 = [&](int row) {
+      const float2 x = *(const float2*)(src + (int64_t)min(row, L - 1) * m);
+      const float2 y = *(const float2*)(src + (int64_t)min(row, L - 1) * m + 128);
+      return make_float4(x.x, x.y, y.x, y.y);
+    };
 #pragma unroll
-    for (int r = 0; r < RW; ++r)
-      ph[r] = *(const float4*)(src + (int64_t)min(r0 + pw * RW + r, L - 1) * m);
+    for (int r = 0; r < RW; ++r) ph[r] = load4(r0 + pw * RW + r);
     if (r0 + RB > L) {
 #pragma unroll
       for (int r = 0; r < RW; ++r)
@@ -259,8 +293,8 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
     }
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
-      const float4 x = *(const float4*)(src + (int64_t)min(r0 + RW + r, L - 1) * m);
-      lrow[r * (m / 4) + cb / 4] = r0 + RW + r < L ? x : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 x = load4(r0 + RW + r);
+      lrow[r * (m / 4) + tid] = r0 + RW + r < L ? x : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
   if (tid == 0) bad = 0;
@@ -290,7 +324,7 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
       const double z = zw[RW + r];
-      const float4 x = lrow[r * (m / 4) + cb / 4];
+      const float4 x = lrow[r * (m / 4) + tid];
       col[0] = fma((double)x.x, z, col[0]);
       col[1] = fma((double)x.y, z, col[1]);
       col[2] = fma((double)x.z, z, col[2]);
@@ -299,13 +333,14 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
     // column c of block b at ((c / CB) nb + b) CB + c % CB: the partials a block
     // reduces are contiguous
     if constexpr (P == 1) {
-      double* dst = Spart + ((((int64_t)(cb >> cbl) * nb + b) << cbl) + (cb & (CB - 1)));
-      st_tag2(dst, col[0], col[1], e);
-      st_tag2(dst + 2, col[2], col[3], e);
+      st_tag2(Spart + ((((int64_t)(c0 >> cbl) * nb + b) << cbl) + (c0 & (CB - 1))), col[0], col[1], e);
+      st_tag2(Spart + ((((int64_t)(c1 >> cbl) * nb + b) << cbl) + (c1 & (CB - 1))), col[2], col[3], e);
     } else {
       // the row subsets' sums meet in LDS, in order; thread = CPT columns
-#pragma unroll
-      for (int q = 0; q < 4; ++q) cr[pw][cb + q] = col[q];
+      cr[pw][c0] = col[0];
+      cr[pw][c0 + 1] = col[1];
+      cr[pw][c1] = col[2];
+      cr[pw][c1 + 1] = col[3];
       __syncthreads();
       const int c = tid * CPT;
       if (P <= 4 || c < m) {
@@ -406,7 +441,7 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
     // own entries of t have arrived (the scalars of the step wait for values
     // of every block).
     double tv[4];
-    bool ok = ld_wait<4>([&](int u) { return Tr + cb + u; }, 15u, j, bar, spin, tv);
+    bool ok = ld_wait_pairs(Tr + c0, Tr + c1, j, bar, spin, tv);
     // Phi t of the block's rows: 4 products per lane and row, summed over the
     // wave 8 rows at a time (into prw), then over the NS slices
     launder_rows(ph);
@@ -429,7 +464,7 @@ __global__ __launch_bounds__(64 * NS * P, 1) void k_lz_resident(LanczosWS w, uns
       double d[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float4 y = lrow[(r8 + e) * (m / 4) + cb / 4];
+        const float4 y = lrow[(r8 + e) * (m / 4) + tid];
         double x = (double)y.x * tv[0];
         x = fma((double)y.y, tv[1], x);
         x = fma((double)y.z, tv[2], x);
