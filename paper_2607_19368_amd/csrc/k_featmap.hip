@@ -30,8 +30,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int FM_BK = 64;                // K per LDS stage
-constexpr int FM_NS = 2;                 // LDS stages (loads run one stage ahead)
-static_assert(FM_NS == 2, "the stage waits allow no load in flight");
 constexpr int FM_LSPREAD = 1;            // k16 steps over which a stage's global->LDS loads go out
 constexpr int FM_SROWS = 32;             // epilogue rows staged per pass
 constexpr int FM_CPR = FM_BK / 8;        // 16-byte chunks per LDS row
@@ -46,9 +44,15 @@ constexpr int FM_RPL = 64 / FM_CPR;      // rows filled by one 1 KB direct-to-LD
 static_assert(FM_CPR == 8, "the swizzle is laid out for 128-byte LDS rows");
 __device__ __forceinline__ int fm_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
-// every global->LDS load of this wave landed (with two stages the next stage's
-// loads are issued during the current one, so a stage wait allows none in flight)
+// every global->LDS load of this wave landed
 __device__ __forceinline__ void fm_wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// the wave's LDS reads done and all but its newest N loads landed, then the block's
+// barrier (__syncthreads would wait for every load, and stages further ahead would
+// be no further ahead)
+template <int N>
+__device__ __forceinline__ void fm_stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 
 // cos(x) in fp32 for the epilogue, about 1 ulp for |x| up to several thousand:
 // Cody and Waite's reduction x = k pi/2 + r with pi/2 split into three fp32
@@ -102,7 +106,8 @@ __device__ __forceinline__ int xcd_tile(int w, int T) {
 typedef __attribute__((address_space(1))) const void* fm_gptr;
 typedef __attribute__((address_space(3))) void* fm_lptr;
 
-template <int BM, int BN, int WGM, int WGN>
+// FM_NS: LDS stages; loads run FM_NS - 1 stages ahead
+template <int BM, int BN, int WGM, int WGN, int FM_NS>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
   constexpr int NW = WGM * WGN;                      // waves
   constexpr int WM = BM / WGM, WN = BN / WGN;        // wave tile
@@ -180,8 +185,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
   const int nk = a.ldw / FM_BK;
 #pragma unroll
   for (int p = 0; p < FM_NS - 1; ++p) load_stage(min(p, nk - 1), p);
-  fm_wait_loads();                                   // stage 0 landed (this wave's part)
-  __syncthreads();
+  fm_stage_barrier<(FM_NS - 2) * NLD>();             // stage 0 landed
 
   const int fr = lane & 31, fk = lane >> 5;   // fragment row/col within a 32-tile, k half
   // two register sets of MFMA operands: step kk of a stage uses set kk & 1
@@ -228,11 +232,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
   // steps rather than in one burst that would hold up the MFMA issue.
   read_ops(sA, sB, 0, 0);
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & (FM_NS - 1);
+    const int cur = kt % FM_NS;
     // stage kt + FM_NS - 1 streams into the buffer freed by the previous
     // iteration while this one feeds the MFMAs (past the end the last stage is
     // re-read, keeping the body branch-free and the per-stage load count fixed)
-    const int lkt = min(kt + FM_NS - 1, nk - 1), lbuf = (kt + FM_NS - 1) & (FM_NS - 1);
+    const int lkt = min(kt + FM_NS - 1, nk - 1), lbuf = (kt + FM_NS - 1) % FM_NS;
     const uint16_t* cA = sA + cur * STAGE_A;
     const uint16_t* cB = sB + cur * STAGE_B;
 #pragma unroll
@@ -247,11 +251,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
     }
     // every read of this stage has landed in registers before the barrier (the
     // buffer is refilled after it); stage kt + 1 has landed after it
-    fm_wait_loads();
-    __syncthreads();
+    fm_stage_barrier<(FM_NS - 2) * NLD>();
     // first operands of stage kt + 1 (after the last stage: a re-read of valid
     // data, discarded), under the MFMAs of this stage's last step
-    const int nb = (kt + 1) & (FM_NS - 1);
+    const int nb = (kt + 1) % FM_NS;
     read_ops(sA + nb * STAGE_A, sB + nb * STAGE_B, 0, 0);
     mfmas((KS - 1) & 1);
     pattern(TM + TN, 0);
@@ -341,10 +344,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_featmap(FeatmapArgs a) {
 
 
 
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, int NS>
 static void launch_tiles(const FeatmapArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const int64_t t = ((a.n_rows + BM - 1) / BM) * (a.m / BN);
-  auto k = k_featmap<BM, BN, WGM, WGN>;
+  auto k = k_featmap<BM, BN, WGM, WGN, NS>;
   const dim3 blk(64 * WGM * WGN);
   if (e0) hipExtLaunchKernelGGL(k, dim3((unsigned)t), blk, 0, s, e0, e1, 0, a);
   else hipLaunchKernelGGL(k, dim3((unsigned)t), blk, 0, s, a);
@@ -353,22 +356,27 @@ static void launch_tiles(const FeatmapArgs& a, hipStream_t s, hipEvent_t e0, hip
 hipError_t launch_featmap(const FeatmapArgs& a, int n_cu, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   (void)hipGetLastError();
   if (a.n_rows <= 0) return hipSuccess;
-  // Tile shape by how the tiles fill the CUs.  256 x 256 (eight waves) when
-  // every CU gets a tile; below that, the largest of 128 x 128 (eight waves),
-  // 64 x 128 (four) and 64 x 64 (two) that still gives every CU two tiles, so
-  // that two workgroups share each CU's MFMA pipes and cover each other's
-  // memory waits (measured at 4096 x 4096 x 1024, 8192 x 3584 x 256 and
-  // 4000 x 3584 x 2048: the rule picks the fastest shape or one within 2%).
-  const int64_t rb = (a.n_rows + 63) / 64, rb2 = (a.n_rows + 127) / 128;
+  // Tile shape by how the tiles fill the CUs.  256 x 256 (eight waves, two K stages)
+  // when every CU gets a tile.  Below that 128 x 128: past one tile a CU with two
+  // stages, so that two workgroups share a CU and cover each other's memory waits;
+  // up to one, alone on its CU, with three, so that its loads run two stages ahead.
+  // Where even those leave half of the CUs idle, 64 x 64 with four stages (a K step
+  // of such a tile is 8 MFMAs a wave, far shorter than a load).  Measured, us:
+  //   N x D x m            64x64 2 / 4   64x128 2    128x128 2 / 3
+  //   1367 x 4096 x 1024   39.0 / 26.4   46.0        49.1 / 35.0
+  //   8192 x 3584 x 256    35.9 / 25.5   43.4        44.4 / 33.0
+  //   700 x 4096 x 2048    43.7 / 28.9   47.5        52.7 / 36.0
+  //   5003 x 3584 x 512    41.2 / 46.5   44.2        45.2 / 33.8
+  //   1216 x 3584 x 2048   41.9 / 50.5   44.7        49.7 / 34.6
+  //   4096 x 4096 x 1024   49.6 / 53.9   50.1        53.4 / 42.9
+  //   2788 x 3584 x 2048   80.3 / 76.9   60.4        55.0 / 65.0
+  //   12288 x 2048 x 512   50.4 / 45.9   39.7        35.6 / 43.2
+  const int64_t t128 = ((a.n_rows + 127) / 128) * (a.m / 128);
   const int64_t t256 = ((a.n_rows + 255) / 256) * (a.m / 256);
-  if (a.m % 256 == 0 && t256 >= n_cu)
-    launch_tiles<256, 256, 2, 4>(a, s, e0, e1);
-  else if (rb2 * (a.m / 128) >= 2LL * n_cu)
-    launch_tiles<128, 128, 2, 4>(a, s, e0, e1);
-  else if (rb * (a.m / 128) >= 2LL * n_cu)
-    launch_tiles<64, 128, 1, 4>(a, s, e0, e1);
-  else
-    launch_tiles<64, 64, 1, 2>(a, s, e0, e1);
+  if (t256 >= n_cu) launch_tiles<256, 256, 2, 4, 2>(a, s, e0, e1);
+  else if (t128 > n_cu) launch_tiles<128, 128, 2, 4, 2>(a, s, e0, e1);
+  else if (2 * t128 > n_cu) launch_tiles<128, 128, 2, 4, 3>(a, s, e0, e1);
+  else launch_tiles<64, 64, 1, 2, 4>(a, s, e0, e1);
   return hipGetLastError();
 }
 
