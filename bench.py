@@ -269,6 +269,10 @@ def main():
     # register-only bf16 MFMA loop
     peaks = None
     if a.timing:
+        # rows per window of the operator: the window length, or the most distinct
+        # rows of a window plus one where equal rows are taken once (every figure
+        # below counts the work on these rows alone)
+        L = ctx.operator_rows
         phi_bytes = ctx.n_spectral * L * wl.m * 4
         big = torch.empty(2**30, dtype=torch.uint8, device="cuda")
         hbm = P.slh_peak_read(big, reps=10)
@@ -292,6 +296,7 @@ def main():
                                "frac_of_measured": fm_tf / peaks["mfma_bf16_tflops"]}
         out["stages_ms"] = {k: v / K for k, v in stage_sum.items() if k != "phi_pass_count"}
         out["stages_ms"]["ms_per_step_with_events"] = ms2
+        out["operator_rows"] = L
         if stage_sum["lanczos_resident"] > 0:
             # the resident kernel: one launch per run, all n_it steps; its duration
             # from slh_time_passes (PASS_REPS runs, each kernel between two events)
@@ -320,7 +325,7 @@ def main():
                                        "takes it from registers. achieved = the algorithmic bytes of "
                                        "every step's matvec over the kernel's duration",
                                "bytes_per_launch": alg, "avg_launch_ms": run_ms,
-                               "steps_per_launch": wl.n_it,
+                               "rows": L, "steps_per_launch": wl.n_it,
                                "timing": f"slh_time_passes: {PASS_REPS} runs of the kernel, each "
                                          "between two events, the first excluded",
                                "avg_launch_ms_events": ev_ms,

@@ -128,7 +128,8 @@ typedef struct slh_ctx slh_ctx;
 
 #define SLH_OPT_DISTINCT      13 /* 1 (default): slh_feature_map looks for equal rows of
                                     a bf16 X within each spectral window (of 33 to
-                                    131072 tokens) and, where they are many, Phi and
+                                    131072 tokens, Phi of 16 MB or more, 32 MB for
+                                    m < 1024) and, where they are many, Phi and
                                     Lanczos take each distinct row once, weighted by
                                     its count (the same operator on the span that
                                     the start vector reaches: the same T, Ritz

@@ -694,9 +694,9 @@ constexpr int res_subsets(int ns) { return ns == 1 ? 4 : ns <= 4 ? 2 : 1; }
 // can own), at most 256.
 // Preferred: the fewest rows a block (less work per step in each) while the
 // exchanged partials, nb m doubles a step and window, stay few: nb <= 128, or
-// nb m <= 2^17.  Measured, us a step (rows a block): 5003 x 512 6.5 (32) 6.8
-// (64); 1216 x 256 5.3 (32) 5.6 (64); 1367 x 1024 6.2 (16) 6.9 (32) 8.4 (64);
-// 4096 x 1024 7.4 (16) 7.1 (32) 8.6 (64); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
+// nb m <= 2^17.  Measured, us a step (rows a block): 5003 x 512 6.1 (32) 6.6
+// (64); 1216 x 256 5.2 (32) 5.6 (64); 1367 x 1024 6.2 (16) 6.8 (32) 8.4 (64);
+// 4096 x 1024 7.4 (16) 7.0 (32) 8.2 (64); 2788 x 2048 9.0 (16) 8.9 (32); 1367 x 2048 7.3
 // (16) 8.1 (32); 3001 x 768 7.2 (16) 7.0 (32) 8.5 (64).
 int res_shapes(const LanczosWS& w, int n_cu, ResShape (&out)[4]) {
   if (w.n_act < 1 || w.m % 256 != 0 || w.m < 256 || w.m > 2048 || w.n_it > 256 || w.n_it < 1) return 0;
@@ -779,7 +779,7 @@ namespace {
 // per compute unit), else the one that takes the fewest launches of as many
 // windows as are (p = 0: none).  A step of a launch that fills the chip takes
 // up to 10 us, one of the streaming path 9 us + its read of Phi at 5.5 TB/s (32
-// windows of 850 x 1024: two launches 17.3 us a step against 29).
+// windows of 850 x 1024: two launches 15.8 us a step against 29).
 ResShape res_shape(const LanczosWS& w, int n_cu) {
   ResShape sh[4], best{};
   const int n = res_shapes(w, n_cu, sh);

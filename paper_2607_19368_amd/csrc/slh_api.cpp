@@ -446,10 +446,12 @@ int ensure_q1(slh_ctx* c) {
   return SLH_OK;
 }
 
-// Below this many entries of Phi (8 MB) the spectral step is bound by latency,
-// whatever the rows (3001 x 256: 218 us a prompt, of which equal rows could save
-// 25, and finding them takes 35).
-constexpr int64_t GROUP_MIN_PHI = (int64_t)1 << 21;
+// Below this many entries of Phi (16 MB; 32 MB where m < 1024) the spectral step is
+// bound by latency, whatever the rows, and looking for equal ones costs more than it
+// saves.  us a prompt, every row / distinct rows: 2048 x 512 264 / 290, 3001 x 256
+// 194 / 222, 2048 x 1024 399 / 423, 8192 x 512 351 / 371, 4096 x 1024 482 / 458,
+// 8192 x 2048 1310 / 1140.
+int64_t group_min_phi(int64_t m) { return (int64_t)1 << (m < 1024 ? 23 : 22); }
 
 // Groups the equal rows of each active window of a bf16 X (fp32 X holds hidden
 // states, where no two rows agree).  Sets phi_g and Lphi: the groups are taken
@@ -461,7 +463,7 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   c->phi_g = -1;
   c->Lphi = L;
   if (!c->distinct || dtype != SLH_BF16 || na < 1 || L <= 32 || L > GROUP_L_MAX ||
-      na * L * c->m < GROUP_MIN_PHI || c->N > 0x7FFFFFFF)
+      na * L * c->m < group_min_phi(c->m) || c->N > 0x7FFFFFFF)
     return SLH_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {

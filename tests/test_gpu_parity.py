@@ -517,9 +517,9 @@ def test_distinct_rows_match_every_row(case):
     N, D, m, distinct, window, n_it, kw = {
         "one": (4096, 512, 1024, 700, 0, 24, {}),
         "one_streaming": (4096, 512, 1024, 700, 0, 24, dict(resident=0)),
-        "windows": (8 * 1111, 256, 512, 300, 1111, 24, {}),
-        "normalised": (4096, 256, 512, 900, 0, 16, dict(normalise=1)),
-        "ragged": (8191, 264, 512, 1001, 0, 24, {}),      # the last word of the bit map part full
+        "windows": (16 * 1111, 256, 512, 300, 1111, 24, {}),
+        "normalised": (4096, 256, 1024, 900, 0, 16, dict(normalise=1)),
+        "ragged": (8191, 264, 1024, 1001, 0, 24, {}),      # the last word of the bit map part full
         "wide": (2051, 2056, 2048, 1500, 0, 24, {}),      # D past one 2048-value stretch
     }[case]
     X = _repeating_rows(N, D, distinct, 3)
