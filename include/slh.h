@@ -305,7 +305,13 @@ int slh_copy_out(slh_ctx *ctx, int32_t which, void *dst_host, int64_t bytes);
  *                  first n_it - 1 are T's off-diagonal)
  *   SLH_OUT_Q      n_act*(n_it+1)*L doubles -> the basis, vector-major
  *                  (after alpha, beta and Q the next call may be slh_eigh_ritz)
- *   SLH_OUT_CODES  N uint32          -> codes; the next call may be slh_merge
+ *   SLH_OUT_CODES  N uint32          -> codes; the next call may be slh_merge.
+ *                  A code of a spectral window may have more than `bits` bits
+ *                  (the 0xFFFFFFFF of slh_simhash among them): tokens are
+ *                  sorted by its low 8 ceil(bits / 8) bits and a run of equal
+ *                  codes is one macro-token.  No window may hold more than
+ *                  min(L, 2^bits) runs, which is what slh_merge_capacity
+ *                  allows for
  * Asynchronous (device-to-device copy on the context stream), except that
  * SLH_OUT_ALPHA synchronises the stream.
  */

@@ -54,22 +54,16 @@ __device__ __forceinline__ int block_incl_scan_1024(int v, int* wsum, int& total
   return v + pre;
 }
 
-__global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
-  const int win = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Book-keeping of one spectral window by one 1024-thread block in global memory
+// (kmask: the bits of a code that the window's one-block sort compares).
+// Returns the window's macro count.
+__device__ __forceinline__ int mg_book_window(const MergeWS& w, int win, uint32_t kmask) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int L = w.L;
   const int64_t base = (int64_t)win * L;
   __shared__ int hist[256];
   __shared__ int wcnt[16][256];
   __shared__ int wsum[16];
-  if (!w.route[win]) {
-    const int k = w.chunk_k;
-    for (int s = tid; s < L; s += 1024) {
-      w.sval[base + s] = (int)(base + s);
-      w.sloc[base + s] = s / k;
-    }
-    if (tid == 0) w.mw[win] = (L + k - 1) / k;
-    return;
-  }
   const int npass = (w.bits + 7) / 8;
   uint32_t* kb[2] = {w.keyA + base, w.keyB + base};
   int* vb[2] = {w.valA + base, w.valB + base};
@@ -97,7 +91,7 @@ __global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
       uint32_t key = 0;
       int val = 0;
       if (valid) {
-        key = kin[i];
+        key = kin[i] & kmask;
         val = vin ? vin[i] : (int)(base + i);
       }
       const int d = valid ? (int)((key >> shift) & 255) : 256;
@@ -181,7 +175,23 @@ __global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
     w.sval[base + s] = V[s];
     w.sloc[base + s] = segk[segid[s]];
   }
-  if (tid == 0) w.mw[win] = nseg;
+  return nseg;
+}
+
+__global__ __launch_bounds__(1024) void k_mg_book(MergeWS w) {
+  const int win = blockIdx.x, tid = threadIdx.x;
+  const int64_t base = (int64_t)win * w.L;
+  if (!w.route[win]) {
+    const int k = w.chunk_k;
+    for (int s = tid; s < w.L; s += 1024) {
+      w.sval[base + s] = (int)(base + s);
+      w.sloc[base + s] = s / k;
+    }
+    if (tid == 0) w.mw[win] = (w.L + k - 1) / k;
+    return;
+  }
+  const int M = mg_book_window(w, win, ~0u);
+  if (tid == 0) w.mw[win] = M;
 }
 
 // Stable sort of the L <= 16384 keys of buf[0] by the bits from tb up (LSD radix,
@@ -450,6 +460,10 @@ __device__ __forceinline__ int block_incl_max_1024(int v, int* wsum, int& total)
 //                  macro indices, token map and positions too)
 // Measured (all four and the zero fill): 32768 tokens x 14 bits 36 us against 310,
 // 49157 35 us against 473.
+// The tables hold 2^bits codes.  slh_load takes codes as they are given, so a tile
+// that meets a larger one marks its window, counts by the code's low bits alone (in
+// bounds), and k_mgl_rank sorts the marked window in one workgroup as k_mg_book does,
+// by the whole code.
 constexpr int MT = 4096, MTB = 12;                    // tokens of a tile
 __host__ __device__ inline int mgl_tiles(int64_t L) { return (int)((L + MT - 1) / MT); }
 __host__ __device__ inline int mgl_words(int64_t L) { return (int)((L + 31) / 32); }
@@ -460,6 +474,11 @@ __host__ __device__ inline int64_t mgl_code_ints(int64_t L, int bits) {
   return 2 * C + (C + 255) / 256 + mgl_words(L);
 }
 
+// window marks (a code past the tables), behind the bit maps
+__device__ __forceinline__ uint32_t* mgl_marks(const MergeWS& w) {
+  return w.lbits + (int64_t)w.n_win * mgl_words(w.L);
+}
+
 __global__ __launch_bounds__(1024) void k_mgl_tile(MergeWS w) {
   __shared__ uint32_t bufA[MT], bufB[MT];
   __shared__ MgSort srt;
@@ -468,7 +487,14 @@ __global__ __launch_bounds__(1024) void k_mgl_tile(MergeWS w) {
   if (!w.route[win]) return;
   const int64_t base = (int64_t)win * w.L + (int64_t)tile * MT;
   const int n = min(MT, w.L - tile * MT);
-  for (int i = tid; i < n; i += 1024) bufA[i] = (w.codes[base + i] << MTB) | (uint32_t)i;
+  const uint32_t cmask = (1u << w.bits) - 1u;
+  bool past = false;
+  for (int i = tid; i < n; i += 1024) {
+    const uint32_t x = w.codes[base + i];
+    past |= x > cmask;
+    bufA[i] = ((x & cmask) << MTB) | (uint32_t)i;
+  }
+  if (past) mgl_marks(w)[win] = 1u;
   const uint32_t* src = mg_sort_lds(bufA, bufB, n, MTB, w.bits, srt) ? bufB : bufA;
   __syncthreads();
   // four sorted positions a thread; the neighbours' codes across threads
@@ -566,6 +592,15 @@ __global__ __launch_bounds__(1024) void k_mgl_rank(MergeWS w, MergeOut o) {
     }
     return;
   }
+  if (mgl_marks(w)[win]) {
+    // up to 16384 tokens the one-block sort packs code and token in 32 bits
+    const int M = mg_book_window(w, win, L <= 16384 ? (1u << 18) - 1u : ~0u);
+    if (tid == 0) {
+      if constexpr (FIN) mg_totals(w, M, o);
+      else w.mw[win] = M;
+    }
+    return;
+  }
   const int nblk = (C + 255) / 256, nword = mgl_words(L);     // nblk <= 256
   int* blk = w.lcode + (int64_t)win * mgl_code_ints(L, w.bits) + 2 * C;
   int* pre = blk + nblk;
@@ -602,6 +637,15 @@ __global__ __launch_bounds__(256) void k_mgl_scatter(MergeWS w, MergeOut o) {
       if (s == L - 1 || (s + 1) % k == 0) o.P[g] = w.compact ? g : s;
     } else {
       w.sloc[base + s] = g;
+    }
+    return;
+  }
+  if (mgl_marks(w)[win]) {                                    // sorted by k_mgl_rank
+    if constexpr (FIN) {
+      const int g = w.sloc[s], tok = w.sval[s];
+      w.sseg[s] = g;
+      if (o.tok2macro) o.tok2macro[tok] = g;
+      if (s == L - 1 || w.sloc[s + 1] != g) o.P[g] = w.compact ? g : tok;
     }
     return;
   }
@@ -1402,7 +1446,7 @@ int64_t merge_tiled_ws(int n_win, int64_t L, int bits, int* ws, MergeWS* w) {
     w->lcnt = ws + code;
     w->lbits = (uint32_t*)(w->lcnt + cnt);
   }
-  return code + cnt + (int64_t)n_win * mgl_words(L);
+  return code + cnt + (int64_t)n_win * (mgl_words(L) + 1);
 }
 
 int merge_nchunks(int64_t N, int CH) { return (int)((N + CH - 1) / CH); }
@@ -1443,7 +1487,7 @@ hipError_t launch_merge(const MergeWS& w, const void* X, int dtype, int64_t ldx,
   } else if (tiled) {
     const int nt = mgl_tiles(w.L), C = 1 << w.bits;
     const dim3 gs((unsigned)((w.L + 255) / 256), w.n_win);
-    hipError_t e = launch_fill_u32((uint32_t*)w.lcnt, w.n_win * ((int64_t)nt * C + mgl_words(w.L)), 0u, s);
+    hipError_t e = launch_fill_u32((uint32_t*)w.lcnt, w.n_win * ((int64_t)nt * C + mgl_words(w.L) + 1), 0u, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mgl_tile, dim3(nt, w.n_win), dim3(1024), 0, s, w);
     hipLaunchKernelGGL(k_mgl_codes, dim3((C + 255) / 256, w.n_win), dim3(256), 0, s, w);

@@ -634,6 +634,47 @@ def test_merge_bookkeeping(N, bits, window, skew, compact):
     assert err.max() <= 2e-6
 
 
+@pytest.mark.parametrize("N,bits,window", [(9001, 12, 0), (20001, 10, 0), (3 * 8200, 9, 8200)])
+def test_merge_of_codes_past_the_tables(N, bits, window):
+    """slh_load takes codes as they are given: values of 2^bits and more (here of 16
+    bits, and the 0xFFFFFFFF that slh_simhash writes for tokens it does not hash) in
+    windows long enough for the tiled book-keeping, whose tables hold 2^bits codes.
+    They are grouped by the whole code as in a short window; of several windows, one
+    holds none.  Sums as in test_merge_bookkeeping."""
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    D, L = 16, window or N
+    rng = np.random.default_rng(N)
+    values = np.concatenate([rng.permutation(0xFFFF)[:150], [0xFFFFFFFF]])
+    codes = values[rng.integers(0, len(values), N)]
+    assert (codes >= 1 << bits).any()
+    if window:
+        codes[:L] = rng.integers(0, 100, L)
+    X = (rng.standard_normal((N, D)) + 1.0).astype(np.float32)
+    ctx = P.slh_create(N, D, 256, 4, bits, 0)
+    if window:
+        P.slh_set_option(ctx, B.SLH_OPT_WINDOW_LEN, window)
+    P.slh_load(ctx, B.SLH_OUT_CODES, torch.from_numpy(codes.astype(np.uint32).view(np.int32)).cuda())
+    E, pos, t2m, M = P.slh_merge(ctx, torch.from_numpy(X).cuda())
+    _, inv = np.unique(np.arange(N) // L * (1 << 33) + codes, return_inverse=True)
+    last = np.zeros(inv.max() + 1, np.int64)
+    np.maximum.at(last, inv, np.arange(N))
+    order = np.argsort(last)
+    rank = np.empty_like(order)
+    rank[order] = np.arange(len(order))
+    assert M == len(order)
+    assert np.array_equal(t2m.cpu().numpy(), rank[inv])
+    assert np.array_equal(pos.cpu().numpy()[:M], last[order])
+    S, cnt, eta = np.zeros((M, D)), np.zeros(M), np.zeros(M)
+    np.add.at(S, rank[inv], X.astype(np.float64))
+    np.add.at(cnt, rank[inv], 1.0)
+    np.add.at(eta, rank[inv], np.linalg.norm(X.astype(np.float64), axis=1))
+    ref = S * (eta / cnt / np.linalg.norm(S, axis=1))[:, None]
+    err = np.linalg.norm(E.cpu().numpy()[:M] - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 2e-6
+
+
 @pytest.mark.timeout(900)
 def test_end_to_end_qwen14b_long():
     inp = make_inputs("qwen14b_long")
