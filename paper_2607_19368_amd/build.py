@@ -41,6 +41,7 @@ FLAGS = [
     # packed fp32 instructions are kept out of all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-pass-failed",
+    "-Wshadow", "-Werror=shadow",       # a name hidden by another has cost a code path here
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

@@ -324,13 +324,13 @@ hipError_t launch_group(const GroupWS& w, const uint16_t* X, int64_t ldx, int D,
   (void)hipGetLastError();
   if (w.L < 2 || w.L > GROUP_L_MAX || w.n_act < 1) return hipErrorInvalidValue;
   const size_t table = 8 * GSLOT + 4 * (size_t)((w.L + 31) / 32), sums = 12 * (size_t)GROUP_MAX;
-  const size_t lds = table > sums ? table : sums;
+  const size_t bytes = table > sums ? table : sums;
   hipError_t e = hipFuncSetAttribute((const void*)k_grp_table,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_grp_hash, dim3((w.L + 15) / 16, w.n_act), dim3(256), 0, s, X, ldx, D,
                      w.winlist, w.L, w.hash);
-  hipLaunchKernelGGL(k_grp_table, dim3(w.n_act), dim3(GT), lds, s, w);
+  hipLaunchKernelGGL(k_grp_table, dim3(w.n_act), dim3(GT), bytes, s, w);
   hipLaunchKernelGGL(k_grp_verify, dim3((w.L + 3) / 4, w.n_act), dim3(256), 0, s, w, X, ldx, D);
   return hipGetLastError();
 }

@@ -389,9 +389,9 @@ __global__ __launch_bounds__(1024) void k_mg_book_lds(MergeWS w, int tb, MergeOu
   // scan of first_end over the block; -1 = none)
   int sf = first_end;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int q = __shfl_down(sf, o, 64);
-    if (lane + o < 64 && sf < 0) sf = q;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int q = __shfl_down(sf, d, 64);
+    if (lane + d < 64 && sf < 0) sf = q;
   }
   if (lane == 0) wend[wave] = sf;
   __syncthreads();                                   // also publishes R

@@ -229,20 +229,23 @@ void gate_stream(slh_ctx* c, hipStream_t s) {
   if (c->stream != s && g->live.size() > 1) g->settle = true;
   c->stream = s;
 }
+// the context's stream is under the caller's capture (or cannot be asked)
+bool capturing(const slh_ctx* c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
 // launch() between the waits and records that the contexts' streams call for
 template <class F>
 hipError_t gate_resident(slh_ctx* c, F launch) {
   ResidentGate* g = gate_of(c);
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (!g) return launch();
   std::lock_guard<std::mutex> lk(g->mu);
   bool several = false;
   for (const slh_ctx* o : g->live) several = several || o->stream != c->stream;
   if (!several) return launch();
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return launch();
-  }
+  if (capturing(c)) return launch();
   hipError_t e = hipSuccess;
   if (g->settle) {
     e = hipDeviceSynchronize();
@@ -465,11 +468,7 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   if (!c->distinct || dtype != SLH_BF16 || na < 1 || L <= 32 || L > GROUP_L_MAX ||
       na * L * c->m < group_min_phi(c->m) || c->N > 0x7FFFFFFF)
     return SLH_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return SLH_OK;
-  }
+  if (capturing(c)) return SLH_OK;
   int rc = ensure_q1(c);
   if (rc) return rc;
   if (c->grp_pin_n < na + 1) {
@@ -1009,15 +1008,15 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       // the resident kernel where every window's Phi fits in the register files
       const int res_nb = c->resident ? lanczos_resident_blocks(w, c->n_cu) : 0;
       const bool res = res_nb > 0;
-      const size_t grp = std::max(w.G3, res_nb);   // row groups of the partials
+      const size_t ng = std::max(w.G3, res_nb);    // row groups of the partials
       const size_t hs = (size_t)w.ldq + 1;
       ENSURE(c, c->Q, (size_t)na * w.ldq * Lr * 8);
       ENSURE(c, c->T, (size_t)na * w.ldq * c->m * 8);
       ENSURE(c, c->Apart, (size_t)na * (c->m / 16) * 8);   // |t|^2 partials
       ENSURE(c, c->Z1, (size_t)na * Lr * 8);
-      ENSURE(c, c->Spart, na * grp * c->m * 8);
+      ENSURE(c, c->Spart, na * ng * c->m * 8);
       ENSURE(c, c->Zs, (size_t)na * 2 * Lr * 8);
-      ENSURE(c, c->H2part, na * grp * hs * 8);
+      ENSURE(c, c->H2part, na * ng * hs * 8);
       ENSURE(c, c->H2, (size_t)na * hs * 8);
       ENSURE(c, c->alpha, (size_t)na * n_it * 8);
       ENSURE(c, c->beta, (size_t)na * n_it * 8);
@@ -1060,10 +1059,11 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
                                     P<double>(c->Seig), w.Q, w.L, w.ldq, P<double>(c->Z),
                                     c->n_cu, c->stream));
         HIP_TRY(c, hipEventRecord(c->ev[4], c->stream));
-      } else if (res || grp) {
+      } else if (res || grp || capturing(c)) {
         // the resident path is four kernels, launched directly: the end of a
         // graph costs a gap before the stream's next kernel.  Grouped rows: their
         // number is the prompt's own, so a graph would be captured for every one.
+        // Under the caller's capture the kernels join the caller's graph.
         if (res)
           HIP_TRY(c, gate_resident(c, [&] {
             return launch_lanczos_resident(w, q1act, P<unsigned>(c->lz_bar), c->n_cu, c->stream,

@@ -1,0 +1,119 @@
+"""The host side of the library (slh_api.cpp) against a stand-in for the HIP runtime
+and the kernels (host_stub.cpp): what is launched, on which stream, in which order,
+what is allocated and when the host waits.  No GPU."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2607_19368_amd import slh as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2607_19368_amd", "csrc")
+X = ctypes.c_void_p(1 << 20)          # never read by the stand-in
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    assert shutil.which("g++")
+    out = str(tmp_path_factory.mktemp("host") / "libhost.so")
+    cmd = ["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-w",
+           "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(CSRC, "slh_api.cpp"), os.path.join(ROOT, "tests", "host_stub.cpp"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    L = ctypes.CDLL(out)
+    L.stub_log.restype = ctypes.c_char_p
+    L.slh_last_error.restype = ctypes.c_char_p
+    L.slh_last_error.argtypes = [ctypes.c_void_p]
+    return L
+
+
+class Ctx:
+    """A context of the stand-in library; calls raise with its error text."""
+
+    def __init__(self, lib, N, D=64, m=1024, r=4, bits=8, **options):
+        self.lib, self.N = lib, N
+        self.h = ctypes.c_void_p()
+        assert lib.slh_create(ctypes.byref(self.h), ctypes.c_int64(N), ctypes.c_int64(D), ctypes.c_int64(m),
+                              r, bits, ctypes.c_uint64(0)) == 0
+        self.r, self.bits, self.D = r, bits, D
+        for k, v in options.items():
+            self.option(k, v)
+
+    def call(self, name, *args):
+        rc = getattr(self.lib, name)(self.h, *args)
+        if rc != 0:
+            raise B.SLHError(f"{name} {rc}: {self.lib.slh_last_error(self.h).decode()}")
+
+    def option(self, name, v):
+        self.call("slh_set_option", getattr(B, "SLH_OPT_" + name), ctypes.c_double(v))
+
+    def feature_map(self, dtype=B.SLH_BF16):
+        self.call("slh_feature_map", X, dtype, ctypes.c_int64(self.D))
+
+    def lanczos(self, n_it=16):
+        self.call("slh_lanczos", n_it, None, None)
+
+    def stream(self, s):
+        self.call("slh_set_stream", ctypes.c_void_p(s))
+
+    def destroy(self):
+        self.lib.slh_destroy(self.h)
+        self.h = None
+
+
+@pytest.fixture
+def stub(lib):
+    """The stand-in with its switches at rest; stub.log() gives and clears the log."""
+    lib.stub_groups(-1)
+    lib.stub_resident(0)
+    lib.stub_fail_resident(0)
+    lib.stub_capture(None, 0)
+    made = []
+
+    class S:
+        def ctx(self, *a, **k):
+            made.append(Ctx(lib, *a, **k))
+            return made[-1]
+
+        def log(self):
+            out = [tuple(int(x) if i else x for i, x in enumerate(t.split()))
+                   for t in lib.stub_log().decode().splitlines()]
+            lib.stub_clear()
+            return out
+
+        def names(self):
+            return [t[0] for t in self.log()]
+
+    s = S()
+    s.lib = lib
+    s.log()
+    yield s
+    lib.stub_capture(None, 0)
+    for c in made:
+        if c.h:
+            c.destroy()
+
+
+def test_streaming_run_is_one_graph(stub):
+    """Off the resident path a run on every row is captured once per configuration and
+    replayed as one graph; grouped rows, whose number is the prompt's own, are launched
+    directly."""
+    c = stub.ctx(20000)
+    c.feature_map(B.SLH_F32)
+    c.lanczos()
+    stub.log()
+    for _ in range(2):
+        c.feature_map(B.SLH_F32)
+        c.lanczos()
+        names = stub.names()
+        assert names.count("graph_launch") == 1 and "begin_capture" not in names
+        assert "lanczos" not in names and "eigh_ritz" not in names
+    stub.lib.stub_groups(5000)
+    c.feature_map()
+    c.lanczos()
+    names = stub.names()
+    assert "graph_launch" not in names and names.count("lanczos") == 1 and names.count("eigh_ritz") == 1
