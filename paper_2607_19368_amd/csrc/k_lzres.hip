@@ -807,6 +807,15 @@ ResShape res_shape(const LanczosWS& w, int n_cu) {
 
 int lanczos_resident_blocks(const LanczosWS& w, int n_cu) { return res_shape(w, n_cu).nb; }
 
+int lanczos_resident_most_blocks(const LanczosWS& w) {
+  // the blocks of every shape grow with the rows; the fewest rows a block give the most
+  const int ns = w.m / 256, rb = 8 * res_subsets(ns), nt = 64 * ns * res_subsets(ns);
+  const int cbmax = std::min(nt & -nt, 256);
+  int nb = 1;
+  while (nb < 256 && (nb * rb < w.L || nb * cbmax < w.m)) nb *= 2;
+  return nb;
+}
+
 size_t lanczos_resident_bar_words() {
   return (size_t)LR_ERR + 32;   // the error word on a line of its own
 }

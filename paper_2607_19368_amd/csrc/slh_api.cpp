@@ -483,9 +483,10 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
     c->grp_pin_n = na + 1;
   }
   const int set = c->q_g == 0 ? 1 : 0;
-  DevBuf& buf = set ? c->grpB : c->grpA;
+  DevBuf &buf = set ? c->grpB : c->grpA, &other = set ? c->grpA : c->grpB;
   const size_t n = (size_t)na * L;
   ENSURE(c, buf, n * 48 + (size_t)na * 4);
+  if (!other.p) ENSURE(c, other, n * 48 + (size_t)na * 4);   // the next prompt's
   GroupWS& w = c->grp[set];
   w.n_act = na;
   w.L = (int)L;
@@ -898,7 +899,11 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   const GroupWS* grp = c->phi_g >= 0 ? &c->grp[c->phi_g] : nullptr;
   const int64_t L = c->Lphi;        // rows per window
   const int64_t rows = (int64_t)c->n_act * L;
-  ENSURE(c, c->Phi, (size_t)std::max<int64_t>(rows, 1) * c->m * sizeof(float));
+  // Sized for every row, here and in slh_lanczos, also where distinct rows take
+  // less: the first call of a shape allocates for every prompt of it, and a captured
+  // call (which takes every row) finds what it needs.
+  const int64_t most = (int64_t)c->n_act * window_len(c);
+  ENSURE(c, c->Phi, (size_t)std::max<int64_t>(most, 1) * c->m * sizeof(float));
   FeatmapArgs a;
   a.rowsrc = grp ? grp->rowsrc : nullptr;
   a.ldr = window_len(c);
@@ -918,9 +923,10 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
                             c->timing ? c->ev[1] : nullptr));
   if (c->normalize && c->n_act > 0) {
     const int G = normalise_groups(c->n_act, (int)L, (int)c->m, c->n_cu);
-    ENSURE(c, c->nm_part, (size_t)c->n_act * G * c->m * 8);
+    const int Gmost = normalise_groups(c->n_act, (int)window_len(c), (int)c->m, c->n_cu);
+    ENSURE(c, c->nm_part, (size_t)c->n_act * std::max(G, Gmost) * c->m * 8);
     ENSURE(c, c->nm_csum, (size_t)c->n_act * c->m * 8);
-    ENSURE(c, c->rowsum, (size_t)rows * 8);
+    ENSURE(c, c->rowsum, (size_t)most * 8);
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[9], c->stream));
     c->row_g = c->phi_g;
     HIP_TRY(c, launch_normalise(P<float>(c->Phi), grp ? grp->wt : nullptr, window_len(c), c->n_act, (int)L, (int)c->m, G,
@@ -949,8 +955,8 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
     if (rc) return rc;
     const GroupWS* grp = c->phi_g >= 0 ? &c->grp[c->phi_g] : nullptr;
     const double* q1act = grp ? grp->q : P<double>(c->q1all);
+    if (na != c->n_win) ENSURE(c, c->q1act, (size_t)na * L * sizeof(double));
     if (!grp && na != c->n_win) {
-      ENSURE(c, c->q1act, (size_t)na * L * sizeof(double));
       HIP_TRY(c, launch_gather_windows(P<double>(c->q1act), P<double>(c->q1all), P<int>(c->winlist),
                                        L, na, c->stream));
       q1act = P<double>(c->q1act);
@@ -1008,14 +1014,22 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       // the resident kernel where every window's Phi fits in the register files
       const int res_nb = c->resident ? lanczos_resident_blocks(w, c->n_cu) : 0;
       const bool res = res_nb > 0;
-      const size_t ng = std::max(w.G3, res_nb);    // row groups of the partials
+      // row groups of the partials, at most for any number of rows up to L: a row
+      // group of the streaming path per chunk while these fit two per CU, else one per
+      // CU in all
+      LanczosWS full = w;
+      full.L = (int)L;
+      const size_t chunks = (size_t)(L + 15) / 16, ncu = std::max(1, c->n_cu);
+      const size_t g3 = std::min(chunks, std::max(2 * ncu / na, (ncu + na - 1) / na));
+      const size_t ng = std::max<size_t>({g3, (size_t)w.G3, (size_t)res_nb,
+                                          c->resident ? (size_t)lanczos_resident_most_blocks(full) : 0});
       const size_t hs = (size_t)w.ldq + 1;
-      ENSURE(c, c->Q, (size_t)na * w.ldq * Lr * 8);
+      ENSURE(c, c->Q, (size_t)na * w.ldq * L * 8);
       ENSURE(c, c->T, (size_t)na * w.ldq * c->m * 8);
       ENSURE(c, c->Apart, (size_t)na * (c->m / 16) * 8);   // |t|^2 partials
-      ENSURE(c, c->Z1, (size_t)na * Lr * 8);
+      ENSURE(c, c->Z1, (size_t)na * L * 8);
       ENSURE(c, c->Spart, na * ng * c->m * 8);
-      ENSURE(c, c->Zs, (size_t)na * 2 * Lr * 8);
+      ENSURE(c, c->Zs, (size_t)na * 2 * L * 8);
       ENSURE(c, c->H2part, na * ng * hs * 8);
       ENSURE(c, c->H2, (size_t)na * hs * 8);
       ENSURE(c, c->alpha, (size_t)na * n_it * 8);
@@ -1025,7 +1039,7 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       ENSURE(c, c->amax, (size_t)na * 2 * 8);
       ENSURE(c, c->theta, (size_t)na * c->r * 8);
       ENSURE(c, c->Seig, (size_t)na * n_it * c->r * 8);
-      ENSURE(c, c->Z, (size_t)na * Lr * c->r * 8);
+      ENSURE(c, c->Z, (size_t)na * L * c->r * 8);
       w.Phi = P<float>(c->Phi);
       w.Q = P<double>(c->Q);
       w.T = P<double>(c->T);
@@ -1040,7 +1054,7 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       w.neff = P<int>(c->neff);
       w.stop = P<int>(c->stop);
       w.amax = P<double>(c->amax);
-      if (res) ENSURE(c, c->lz_bar, lanczos_resident_bar_words() * sizeof(unsigned));
+      if (c->resident) ENSURE(c, c->lz_bar, lanczos_resident_bar_words() * sizeof(unsigned));
       if (c->timing) {
         // timing: launch the step sequence directly so that every pass over Phi
         // can be bracketed by events (events inside a captured graph cannot be timed)
@@ -1141,7 +1155,7 @@ int slh_eigh_ritz(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out
   if (na > 0) {
     ENSURE(c, c->theta, (size_t)na * c->r * 8);
     ENSURE(c, c->Seig, (size_t)na * n_it * c->r * 8);
-    ENSURE(c, c->Z, (size_t)na * L * c->r * 8);
+    ENSURE(c, c->Z, (size_t)na * window_len(c) * c->r * 8);
     HIP_TRY(c, launch_eigh_ritz(P<double>(c->alpha), P<double>(c->beta), P<int>(c->neff), na,
                                 n_it, c->r, P<double>(c->theta), P<double>(c->Seig),
                                 P<double>(c->Q), (int)L, n_it + 1, P<double>(c->Z), c->n_cu,
@@ -1336,7 +1350,7 @@ int slh_spectral_energy(slh_ctx* c, double* out) {
   const int64_t L = window_len(c);
   const int na = c->n_act;
   if (na == 0) return SLH_OK;
-  ENSURE(c, c->dg_rowsq, (size_t)na * c->Lphi * 8);
+  ENSURE(c, c->dg_rowsq, (size_t)na * L * 8);
   ENSURE(c, c->dg_energy, (size_t)na * 8);
   HIP_TRY(c, launch_energy(P<float>(c->Phi), c->phi_g >= 0 ? c->grp[c->phi_g].wt : nullptr, L,
                            P<double>(c->theta), na, (int)c->Lphi, (int)c->m, c->r,

@@ -118,6 +118,8 @@ hipError_t launch_lanczos_start(const LanczosWS& w, const double* q1_act, hipStr
 // 256) and every block of the kernel can be resident at once, else 0; Spart and
 // H2part hold that many row groups per window
 int lanczos_resident_blocks(const LanczosWS& w, int n_cu);
+// the most blocks per window that it can return for windows of at most w.L rows
+int lanczos_resident_most_blocks(const LanczosWS& w);
 // 32-bit words of the kernel's status buffer; its error word, at index
 // LZ_BAR_ERR, is nonzero after a wait between blocks timed out (the run's
 // results are then invalid)

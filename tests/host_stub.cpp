@@ -166,6 +166,7 @@ hipError_t launch_lanczos(const LanczosWS&, const double*, hipStream_t s, const 
 }
 hipError_t launch_lanczos_passes(const LanczosWS&, int, int, hipStream_t s) { return launched("passes", s); }
 int lanczos_resident_blocks(const LanczosWS&, int) { return g_resident; }
+int lanczos_resident_most_blocks(const LanczosWS&) { return 256; }
 size_t lanczos_resident_bar_words() { return (size_t)LZ_BAR_ERR + 32; }
 hipError_t launch_lanczos_resident(const LanczosWS&, const double*, unsigned*, int, hipStream_t s,
                                    hipEvent_t, hipEvent_t) {

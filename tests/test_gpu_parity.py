@@ -587,6 +587,56 @@ def test_distinct_rows_only_where_equal(case):
         assert np.abs(a["Z"] - b["Z"]).max() <= 1e-7
 
 
+@pytest.mark.parametrize("resident", [1, 0])
+def test_capture_after_a_grouped_warm_up(resident):
+    """Under stream capture every row is taken, also where the eager run before (which
+    sized the workspaces) grouped them; every replay, on new rows in the same buffer
+    and with eager runs in between, gives the bits of an eager run on every row."""
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    N, D, m, n_it = 4096, 512, 1024, 24
+    Xs = [_repeating_rows(N, D, 700, k) for k in (11, 12, 13)]
+    X = Xs[0].clone()
+    codes = torch.zeros(N, dtype=torch.int32, device="cuda")
+    s = torch.cuda.Stream()
+
+    def ctx(distinct):
+        c = P.slh_create(N, D, m, 12, 8, 0)
+        P.slh_set_option(c, B.SLH_OPT_RESIDENT, resident)
+        P.slh_set_option(c, B.SLH_OPT_DISTINCT, distinct)
+        P.slh_set_stream(c, s)
+        return c
+
+    def run(c):
+        P.slh_feature_map(c, X)
+        P.slh_lanczos(c, n_it, want=False)
+        P.slh_simhash(c, codes)
+
+    torch.cuda.synchronize()
+    a, every = ctx(1), ctx(0)
+    run(a)
+    assert a.operator_rows == 701
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        run(a)
+    assert a.operator_rows == N
+    for x in Xs + Xs[:1]:
+        X.copy_(x)
+        codes.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        s.synchronize()
+        got = codes.clone(), P.slh_copy_out(a, B.SLH_OUT_ALPHA), P.slh_copy_out(a, B.SLH_OUT_Z)
+        run(every)
+        s.synchronize()
+        assert torch.equal(got[0], codes)
+        assert np.array_equal(got[1], P.slh_copy_out(every, B.SLH_OUT_ALPHA))
+        assert np.array_equal(got[2], P.slh_copy_out(every, B.SLH_OUT_Z))
+
+
 # ------------------------------------------------------------------ merge of loaded codes
 @pytest.mark.parametrize("N,bits,window,skew,compact", [
     (4096 * 5 + 1, 7, 0, 3.0, 0),          # one token in the last tile

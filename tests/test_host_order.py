@@ -117,3 +117,30 @@ def test_streaming_run_is_one_graph(stub):
     c.lanczos()
     names = stub.names()
     assert "graph_launch" not in names and names.count("lanczos") == 1 and names.count("eigh_ritz") == 1
+
+
+@pytest.mark.parametrize("resident", [0, 128])
+@pytest.mark.parametrize("normalise", [0, 1])
+def test_first_call_of_a_shape_sizes_every_prompt(stub, resident, normalise):
+    """The workspaces follow the window length, not the prompt's distinct rows: prompts
+    with more of them than all before, or with none repeated, allocate nothing, and
+    neither does a call under the caller's capture, which takes every row."""
+    c = stub.ctx(8192, NORMALIZE=normalise)
+    c.stream(16)
+    stub.lib.stub_resident(resident)
+
+    def prompt(groups):
+        stub.lib.stub_groups(groups)
+        c.feature_map()
+        c.lanczos()
+        c.call("slh_simhash", None)
+        return stub.log()
+
+    assert any(t[0] == "malloc" for t in prompt(500))
+    for groups, rows in ((600, 601), (1500, 1501), (7000, 7001), (-1, 8192), (501, 502)):
+        log = prompt(groups)
+        assert not [t for t in log if t[0] in ("malloc", "free")], groups
+        assert ("featmap", 16, rows) in log
+    stub.lib.stub_capture(ctypes.c_void_p(16), 1)
+    log = prompt(500)
+    assert ("featmap", 16, 8192) in log and not [t for t in log if t[0] in ("malloc", "free", "group", "query")]
