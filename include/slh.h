@@ -117,7 +117,15 @@ typedef struct slh_ctx slh_ctx;
                                     persistent kernel that holds its rows of Phi in
                                     registers (the same recurrence; partial sums in
                                     a different grouping); 0: one pass over Phi per
-                                    step for every shape                             */
+                                    step for every shape.  Its blocks must all be on
+                                    the chip at once, so the runs of one process on
+                                    one device take turns, whatever their streams.
+                                    What the library does not order, and the caller
+                                    must: replays of a graph that captured such a
+                                    run, beside other runs or replays, and runs of
+                                    other processes on the same GPU.  Two that meet
+                                    end with SLH_EHIP after their waits gave up; set
+                                    0 where that can happen                         */
 #define SLH_OPT_WAIT_POLLS    12 /* polls after which a wait of the resident Lanczos
                                     kernel for a value of another block gives up
                                     (the blocks then leave and the call that reads

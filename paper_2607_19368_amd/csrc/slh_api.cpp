@@ -188,47 +188,6 @@ struct slh_ctx {
 
 namespace {
 
-// Resident Lanczos kernels of different streams must not run at once: each needs
-// all of its blocks on the chip, and two that each hold part of it would wait for
-// blocks that cannot start until their bounded waits gave up.  Per device, the live
-// contexts; where their streams differ, a resident launch waits for the event of
-// the one before it.  With one stream (its kernels run in order) no event is made.
-struct ResidentGate {
-  std::mutex mu;
-  std::vector<slh_ctx*> live;
-  hipEvent_t ev = nullptr;          // after the last resident launch made with several streams
-  hipStream_t last = nullptr;
-  bool recorded = false;
-  bool settle = false;              // launches without an event may be in flight
-};
-constexpr int GATE_DEVICES = 64;
-ResidentGate gates[GATE_DEVICES];
-ResidentGate* gate_of(const slh_ctx* c) {
-  return c->device >= 0 && c->device < GATE_DEVICES ? &gates[c->device] : nullptr;
-}
-void gate_enter(slh_ctx* c) {
-  if (ResidentGate* g = gate_of(c)) {
-    std::lock_guard<std::mutex> lk(g->mu);
-    g->live.push_back(c);
-    g->settle = g->settle || g->live.size() > 1;
-  }
-}
-void gate_leave(slh_ctx* c) {
-  if (ResidentGate* g = gate_of(c)) {
-    std::lock_guard<std::mutex> lk(g->mu);
-    g->live.erase(std::remove(g->live.begin(), g->live.end(), c), g->live.end());
-  }
-}
-void gate_stream(slh_ctx* c, hipStream_t s) {
-  ResidentGate* g = gate_of(c);
-  if (!g) {
-    c->stream = s;
-    return;
-  }
-  std::lock_guard<std::mutex> lk(g->mu);
-  if (c->stream != s && g->live.size() > 1) g->settle = true;
-  c->stream = s;
-}
 // the context's stream is under the caller's capture (or cannot be asked)
 bool capturing(const slh_ctx* c) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -236,29 +195,39 @@ bool capturing(const slh_ctx* c) {
   (void)hipGetLastError();
   return true;
 }
-// launch() between the waits and records that the contexts' streams call for
+
+// Resident Lanczos kernels of different streams must not run at once: each needs
+// all of its blocks on the chip, and two that each hold part of it would wait for
+// blocks that cannot start until their bounded waits gave up.  Per device, the event
+// behind the last resident launch and its stream; a launch on another stream waits
+// for it.  The event outlives contexts and streams, so neither a context that is
+// destroyed nor one that moves to another stream leaves a kernel unaccounted for.
+// Not under the caller's capture, where there is nothing yet to order.
+struct ResidentGate {
+  std::mutex mu;
+  hipEvent_t ev = nullptr;
+  hipStream_t last = nullptr;
+  bool recorded = false;
+};
+constexpr int GATE_DEVICES = 64;
+ResidentGate gates[GATE_DEVICES];
 template <class F>
 hipError_t gate_resident(slh_ctx* c, F launch) {
-  ResidentGate* g = gate_of(c);
-  if (!g) return launch();
-  std::lock_guard<std::mutex> lk(g->mu);
-  bool several = false;
-  for (const slh_ctx* o : g->live) several = several || o->stream != c->stream;
-  if (!several) return launch();
-  if (capturing(c)) return launch();
+  if (c->device < 0 || c->device >= GATE_DEVICES || capturing(c)) return launch();
+  ResidentGate& g = gates[c->device];
+  std::lock_guard<std::mutex> lk(g.mu);
   hipError_t e = hipSuccess;
-  if (g->settle) {
-    e = hipDeviceSynchronize();
-    g->settle = e != hipSuccess;
-    g->recorded = false;
-  }
-  if (e == hipSuccess && !g->ev) e = hipEventCreateWithFlags(&g->ev, hipEventDisableTiming);
-  if (e == hipSuccess && g->recorded && g->last != c->stream) e = hipStreamWaitEvent(c->stream, g->ev, 0);
-  if (e == hipSuccess) e = launch();
-  if (e == hipSuccess) e = hipEventRecord(g->ev, c->stream);
-  g->recorded = e == hipSuccess;
-  g->last = c->stream;
-  return e;
+  if (!g.ev) e = hipEventCreateWithFlags(&g.ev, hipEventDisableTiming | hipEventDisableSystemFence);
+  if (e == hipSuccess && g.recorded && g.last != c->stream) e = hipStreamWaitEvent(c->stream, g.ev, 0);
+  if (e != hipSuccess) return e;
+  e = launch();
+  // also behind a launch that failed: what went out before it, here or on the stream
+  // that this one waits for, is still to be waited for
+  const hipError_t r = hipEventRecord(g.ev, c->stream);
+  if (r != hipSuccess) (void)hipStreamSynchronize(c->stream);
+  g.recorded = r == hipSuccess;
+  g.last = c->stream;
+  return e != hipSuccess ? e : r;
 }
 
 int fail(slh_ctx* c, int code, const char* fmt, ...) {
@@ -671,14 +640,12 @@ int slh_create(slh_ctx** out, int64_t N, int64_t D, int64_t m, int32_t r, int32_
     slh_destroy(c);
     return SLH_EHIP;
   }
-  gate_enter(c);
   *out = c;
   return SLH_OK;
 }
 
 void slh_destroy(slh_ctx* c) {
   if (!c) return;
-  gate_leave(c);
   if (c->mq_head != c->mq_tail) (void)hipStreamSynchronize(c->stream);   // merges still in flight
   drop_graph(c);
   DevBuf* bufs[] = {&c->Wt, &c->psi, &c->R, &c->q1all, &c->q1act, &c->winlist, &c->route,
@@ -803,7 +770,7 @@ int slh_set_option(slh_ctx* c, int32_t key, double v) {
 
 int slh_set_stream(slh_ctx* c, void* s) {
   if (!c) return SLH_EINVAL;
-  gate_stream(c, (hipStream_t)s);
+  c->stream = (hipStream_t)s;
   return SLH_OK;
 }
 

@@ -3,6 +3,7 @@ and the kernels (host_stub.cpp): what is launched, on which stream, in which ord
 what is allocated and when the host waits.  No GPU."""
 import ctypes
 import os
+import random
 import shutil
 import subprocess
 
@@ -144,3 +145,70 @@ def test_first_call_of_a_shape_sizes_every_prompt(stub, resident, normalise):
     stub.lib.stub_capture(ctypes.c_void_p(16), 1)
     log = prompt(500)
     assert ("featmap", 16, 8192) in log and not [t for t in log if t[0] in ("malloc", "free", "group", "query")]
+
+
+def _all_in_turn(log):
+    """Every resident launch of the log is ordered behind all earlier ones: by its
+    stream, or by an event recorded behind them that its stream waits for."""
+    before, snap, made = {}, {}, 0
+    for name, stream, arg in log:
+        done = before.setdefault(stream, set())
+        if name == "record":
+            snap[arg] = set(done)
+        elif name == "wait":
+            done |= snap.get(arg, set())   # (an event of the contexts before this test)
+        elif name == "resident":
+            assert done == set(range(made)), (made, stream)
+            done.add(made)
+            made += 1
+    return made
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_resident_launches_take_turns(stub, seed):
+    """Contexts that are made, destroyed and moved between streams, some of whose
+    launches fail: no resident kernel can meet another, and no call waits for the
+    device."""
+    rng = random.Random(seed)
+    stub.lib.stub_resident(64)
+    live = []
+    for _ in range(150):
+        if not live or rng.random() < 0.15:
+            live.append(stub.ctx(64, m=256))
+            live[-1].stream(rng.randint(1, 4))
+            live[-1].feature_map(B.SLH_F32)
+        c = rng.choice(live)
+        what = rng.random()
+        if what < 0.1:
+            live.remove(c)
+            c.destroy()
+        elif what < 0.3:
+            c.stream(rng.randint(1, 4))
+        elif what < 0.4:
+            stub.lib.stub_fail_resident(1)
+            with pytest.raises(B.SLHError):
+                c.lanczos()
+        else:
+            c.lanczos()
+    log = stub.log()
+    assert _all_in_turn(log) > 50
+    assert not [t for t in log if t[0] == "device_sync"]
+
+
+def test_captured_resident_launch_joins_the_capture_alone(stub):
+    """Under the caller's capture a resident launch neither waits for nor records an
+    event of another stream (either would tie the capture to work outside it)."""
+    stub.lib.stub_resident(64)
+    a, b = stub.ctx(64, m=256), stub.ctx(64, m=256)
+    for c, s in ((a, 1), (b, 2)):
+        c.stream(s)
+        c.feature_map(B.SLH_F32)
+        c.lanczos()
+    stub.log()
+    stub.lib.stub_capture(ctypes.c_void_p(1), 1)
+    a.lanczos()
+    assert [t[0] for t in stub.log()] == ["resident", "eigh_ritz"]
+    stub.lib.stub_capture(None, 0)
+    b.lanczos()
+    a.lanczos()
+    assert [t[0] for t in stub.log()].count("wait") == 1
