@@ -56,7 +56,6 @@ __global__ __launch_bounds__(256) void k_grp_hash(const uint16_t* __restrict__ X
 constexpr int GT = 1024;                 // threads of k_grp_table
 constexpr int GSLOT = 16384;             // slots of its table
 constexpr int GB = 8;                    // rows of a thread whose loads go out together
-constexpr int GPROBE = 64;               // probes before it gives up
 constexpr double GFIX = 9007199254740992.0;      // 2^53
 constexpr double GFIX2 = 17592186044416.0;       // 2^44: at most 2^43 a row, 2^17 rows
 
@@ -69,10 +68,11 @@ __device__ __forceinline__ T ld_lds(T* p) {
 
 // Dynamic LDS: the table (tag and first row per slot, 128 KB) and the bit map of
 // first rows, then in its place the groups' sums of q_0 and their counts (12
-// bytes a group).  Bound by one CU's LDS atomics and barriers: 4096 rows 20 us,
-// 8192 rows 27 us, 32768 rows 98 us (a third of it the probes); all windows of a
-// batch run at once.  Summing a wave's most frequent groups in registers first
-// did not make it faster (8192 rows: 30 us).
+// bytes a group).  Bound by one CU's LDS atomics and barriers: 4096 rows 19 us,
+// 8192 rows 26 us, 32768 rows 97 us (a third of it the probes), and where no two
+// rows agree 9, 11 and 33 us (25, 42 and 228 with a limit on the probes of a row in
+// place of the count); all windows of a batch run at once.  Summing a wave's most
+// frequent groups in registers first did not make it faster (8192 rows: 30 us).
 __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
   extern __shared__ unsigned char lds[];
   unsigned* tag = (unsigned*)lds;                      // [GSLOT]
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
   unsigned* bits = (unsigned*)(lds + 8 * GSLOT);       // [ceil(L / 32)] first rows
   long long* qsum = (long long*)lds;                   // [GROUP_MAX]
   int* cnt = (int*)(lds + 8 * GROUP_MAX);              // [GROUP_MAX]
-  __shared__ int wtot[GT / 64], fail, ngrp;
+  __shared__ int wtot[GT / 64], made, ngrp;
   __shared__ double red[GT / 64];
   const int a = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int L = w.L, nword = (L + 31) / 32;
@@ -93,10 +93,25 @@ __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
     first[s] = 0x7FFFFFFF;
   }
   for (int s = tid; s < nword; s += GT) bits[s] = 0;
-  if (tid == 0) fail = 0;
+  if (tid == 0) made = 0;
   __syncthreads();
+  // More groups than this are not taken: past the table, or so many that they spare
+  // too little.  Every new slot is counted, so that whether the limit is passed does
+  // not depend on the order of the probes (a limit on a row's probes would: one set
+  // of 10000 groups in 40 and three of 12000 in four need more than 64 for some
+  // row), and the rows that are left are not looked at.  A full table is past the
+  // limit, so every probe ends.
+  const int lim = min(GROUP_MAX, 7 * L / 8 - 1);
+  int mk = 0;                                          // slots this thread made, not yet added
+  auto add_made = [&]() {                              // at most GB a thread: 4 bits
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) n += __popcll(__ballot((mk >> q) & 1)) << q;
+    if (n && lane == __ffsll((long long)__ballot(1)) - 1) atomicAdd(&made, n);
+    mk = 0;
+  };
   // a slot per hash (open addressing; tag 0 is free); its smallest row number
-  for (int i0 = tid; i0 < L; i0 += GB * GT) {
+  for (int i0 = tid; i0 < L && ld_lds(&made) <= lim; i0 += GB * GT) {
     unsigned t[GB], o[GB];
     unsigned sl[GB];
     unsigned pend = 0;
@@ -107,23 +122,29 @@ __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
       sl[u] = (unsigned)h & (nslot - 1);
       pend |= i0 + u * GT < L ? 1u << u : 0u;
     }
-    // the rows' probes side by side: a round reads every row's slot at once
-    for (int p = 0; pend != 0; ++p) {
-      if (p == GPROBE) {
-        fail = 1;
-        break;
-      }
+    // the rows' probes side by side: a round reads every row's slot at once.  The
+    // count is looked at after 1, 2, 4, 8, 16, 32, 64, 96, ... rounds.
+    for (int p = 1; pend != 0; ++p) {
 #pragma unroll
       for (int u = 0; u < GB; ++u) o[u] = ld_lds(&tag[sl[u]]);
 #pragma unroll
       for (int u = 0; u < GB; ++u) {
         if ((pend >> u) & 1) {
-          if (o[u] == 0) o[u] = atomicCAS(&tag[sl[u]], 0u, t[u]);
+          if (o[u] == 0) {
+            o[u] = atomicCAS(&tag[sl[u]], 0u, t[u]);
+            mk += o[u] == 0;
+          }
           if (o[u] == 0 || o[u] == t[u]) pend &= ~(1u << u);
           else sl[u] = (sl[u] + 1) & (nslot - 1);
         }
       }
+      if ((p & (p - 1)) == 0 || (p & 31) == 0) {
+        add_made();
+        if (ld_lds(&made) > lim) break;
+      }
     }
+    add_made();
+    if (pend != 0) break;
 #pragma unroll
     for (int u = 0; u < GB; ++u) o[u] = (unsigned)ld_lds(&first[sl[u]]);
 #pragma unroll
@@ -136,7 +157,7 @@ __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
     }
   }
   __syncthreads();
-  if (fail) {
+  if (made > lim) {
     if (tid == 0) w.n_dev[a] = w.n_out[a] = -1;
     return;
   }
@@ -165,11 +186,7 @@ __global__ __launch_bounds__(GT) void k_grp_table(GroupWS w) {
   if (tid == GT - 1) ngrp = base + inc;
   // the words' own bases, in the free tags (the numbering below reads them)
   __syncthreads();
-  const int n = ngrp;
-  if (n > GROUP_MAX) {
-    if (tid == 0) w.n_dev[a] = w.n_out[a] = -1;
-    return;
-  }
+  const int n = ngrp;                                  // <= lim
   unsigned* wbase = tag;                               // [nword <= GSLOT]
   {
     int run = excl;

@@ -587,6 +587,45 @@ def test_distinct_rows_only_where_equal(case):
         assert np.abs(a["Z"] - b["Z"]).max() <= 1e-7
 
 
+@pytest.mark.parametrize("N,distinct,taken", [
+    (32768, 12288, True),      # the most groups: three quarters of the table's slots
+    (32768, 12289, False),     # one more
+    (131072, 131072, False),   # far more rows than slots
+    (40000, 10000, True),
+    (8192 * 4, 4 * 7167, False)])
+def test_distinct_rows_up_to_the_table(N, distinct, taken):
+    """The number of distinct rows alone decides whether they are grouped, the same on
+    every call: up to 12288 in a window, however the table fills."""
+    import torch
+    import paper_2607_19368_amd as P
+    D, m = 64, 256
+    X = _repeating_rows(N, D, distinct, 6)
+    assert len(torch.unique(X.view(torch.int16), dim=0)) == distinct
+    ctx = P.slh_create(N, D, m, 4, 8, 0)
+    for _ in range(4):
+        P.slh_feature_map(ctx, X)
+        assert ctx.operator_rows == (distinct + 1 if taken else N)
+    if taken:
+        a, b = (_spectral_run(X, m, 12, 4, 8, k) for k in (1, 0))
+        assert np.array_equal(a["Phi"], b["Phi"])
+        assert np.abs(a["ritz"] / b["ritz"] - 1).max() <= 1e-9
+
+
+@pytest.mark.parametrize("N,window,distinct,taken", [(8192, 0, 7167, True), (8192, 0, 7168, False),
+                                                     (64 * 1024, 64, 55, True), (64 * 1024, 64, 56, False)])
+def test_distinct_rows_that_spare_an_eighth(N, window, distinct, taken):
+    """Rows are grouped where groups + 1 is at most 7/8 of the window."""
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    D, m, L = 64, 1024, window or N
+    X = _repeating_rows(L, D, distinct, 8).repeat(N // L, 1)
+    ctx = P.slh_create(N, D, m, 4, 8, 0)
+    if window:
+        P.slh_set_option(ctx, B.SLH_OPT_WINDOW_LEN, window)
+    P.slh_feature_map(ctx, X)
+    assert ctx.operator_rows == (distinct + 1 if taken else L)
+
+
 @pytest.mark.parametrize("resident", [1, 0])
 def test_capture_after_a_grouped_warm_up(resident):
     """Under stream capture every row is taken, also where the eager run before (which
