@@ -452,7 +452,8 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
     c->grp_pin_n = na + 1;
   }
   const int set = c->q_g == 0 ? 1 : 0;
-  DevBuf &buf = set ? c->grpB : c->grpA, &other = set ? c->grpA : c->grpB;
+  DevBuf& buf = set ? c->grpB : c->grpA;
+  DevBuf& other = set ? c->grpA : c->grpB;
   const size_t n = (size_t)na * L;
   ENSURE(c, buf, n * 48 + (size_t)na * 4);
   if (!other.p) ENSURE(c, other, n * 48 + (size_t)na * 4);   // the next prompt's
