@@ -141,9 +141,11 @@ typedef struct slh_ctx slh_ctx;
                                     Lanczos take each distinct row once, weighted by
                                     its count (the same operator on the span that
                                     the start vector reaches: the same T, Ritz
-                                    values, Z and codes up to rounding; the call
-                                    then waits for the stream, except under stream
-                                    capture, where every row is taken); 0: every row */
+                                    values, Z and codes up to rounding).  Many: at
+                                    least an eighth of the rows, and at most 12288
+                                    distinct ones.  The call then waits for the
+                                    search, except under stream capture, where every
+                                    row is taken.  0: every row, and no wait        */
 
 /*
  * Random parameters of the method, drawn from `seed` with Philox4x32-10
@@ -205,7 +207,11 @@ int slh_route(slh_ctx *ctx, const void *X, int32_t x_dtype, int64_t ldx,
  * X as for slh_route.  The row norms behind s(x) (and the member norms slh_merge
  * uses) are taken from X on every call, unless slh_route has just taken them
  * from the same X (pointer, type and stride) for this pass; a new prompt may
- * therefore be written into the same buffer between passes.  Asynchronous.
+ * therefore be written into the same buffer between passes.  Asynchronous, except
+ * where equal rows are looked for (SLH_OPT_DISTINCT: bf16 X of the sizes given
+ * there): the call then returns once their number is known, that is, after the work
+ * enqueued on the stream before it (a merge from slh_merge_async included) and the
+ * search itself, with the row norms and what follows still to run.
  */
 int slh_feature_map(slh_ctx *ctx, const void *X, int32_t x_dtype, int64_t ldx);
 

@@ -282,15 +282,23 @@ int ensure_pinned(slh_ctx* c, size_t bytes) {
   return SLH_OK;
 }
 
-// Wait for the work enqueued so far on the context stream by spinning on an
-// event (a woken-up stream synchronisation costs tens of microseconds).
-int wait_stream(slh_ctx* c) {
-  hipError_t e = hipEventRecord(c->ev_host, c->stream);
-  if (e != hipSuccess) return fail(c, SLH_EHIP, "hipEventRecord: %s", hipGetErrorString(e));
+// mark_host: the point of the context stream that wait_host then waits for, by
+// spinning on an event (a woken-up stream synchronisation costs tens of
+// microseconds); wait_stream: for the work enqueued so far.
+int mark_host(slh_ctx* c) {
+  const hipError_t e = hipEventRecord(c->ev_host, c->stream);
+  return e == hipSuccess ? SLH_OK : fail(c, SLH_EHIP, "hipEventRecord: %s", hipGetErrorString(e));
+}
+int wait_host(slh_ctx* c) {
+  hipError_t e;
   while ((e = hipEventQuery(c->ev_host)) == hipErrorNotReady) {
   }
   if (e != hipSuccess) return fail(c, SLH_EHIP, "hipEventQuery: %s", hipGetErrorString(e));
   return SLH_OK;
+}
+int wait_stream(slh_ctx* c) {
+  const int rc = mark_host(c);
+  return rc ? rc : wait_host(c);
 }
 
 #define ENSURE(c, b, bytes)                   \
@@ -426,14 +434,15 @@ int ensure_q1(slh_ctx* c) {
 int64_t group_min_phi(int64_t m) { return (int64_t)1 << (m < 1024 ? 23 : 22); }
 
 // Groups the equal rows of each active window of a bf16 X (fp32 X holds hidden
-// states, where no two rows agree).  Sets phi_g and Lphi: the groups are taken
-// where they leave at most 7/8 of the rows.  Waits for the stream (the host sizes
-// the feature map and Lanczos by the count), so not under stream capture.
-int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
+// states, where no two rows agree).  The host sizes the feature map and Lanczos by
+// their number, so it has to wait for it (and under stream capture every row is
+// taken): group_rows enqueues the search and marks its end, set >= 0 where there is
+// one; group_take waits for that mark and sets phi_g and Lphi.  The groups are taken
+// where they leave at most 7/8 of the rows.
+int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, int& set) {
   const int64_t L = window_len(c);
   const int na = c->n_act;
-  c->phi_g = -1;
-  c->Lphi = L;
+  set = -1;
   if (!c->distinct || dtype != SLH_BF16 || na < 1 || L <= 32 || L > GROUP_L_MAX ||
       na * L * c->m < group_min_phi(c->m) || c->N > 0x7FFFFFFF)
     return SLH_OK;
@@ -451,13 +460,13 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
     }
     c->grp_pin_n = na + 1;
   }
-  const int set = c->q_g == 0 ? 1 : 0;
-  DevBuf& buf = set ? c->grpB : c->grpA;
-  DevBuf& other = set ? c->grpA : c->grpB;
+  const int g = c->q_g == 0 ? 1 : 0;
+  DevBuf& buf = g ? c->grpB : c->grpA;
+  DevBuf& other = g ? c->grpA : c->grpB;
   const size_t n = (size_t)na * L;
   ENSURE(c, buf, n * 48 + (size_t)na * 4);
   if (!other.p) ENSURE(c, other, n * 48 + (size_t)na * 4);   // the next prompt's
-  GroupWS& w = c->grp[set];
+  GroupWS& w = c->grp[g];
   w.n_act = na;
   w.L = (int)L;
   w.winlist = na == c->n_win ? nullptr : P<int>(c->winlist);
@@ -475,13 +484,22 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   w.differ = c->grp_pin + na;
   *w.differ = 0;                    // the last prompt's kernels are done: this call waited for them
   HIP_TRY(c, launch_group(w, (const uint16_t*)X, ldx, (int)c->D, c->stream));
-  if ((rc = wait_stream(c))) return rc;
+  if ((rc = mark_host(c))) return rc;
+  set = g;
+  return SLH_OK;
+}
+int group_take(slh_ctx* c, int set) {
+  c->phi_g = -1;
+  c->Lphi = window_len(c);
+  if (set < 0) return SLH_OK;
+  if (int rc = wait_host(c)) return rc;
+  const GroupWS& w = c->grp[set];
   int most = 0;
-  for (int a = 0; a < na; ++a) {
+  for (int a = 0; a < w.n_act; ++a) {
     if (w.n_out[a] < 0) return SLH_OK;
     most = std::max(most, w.n_out[a]);
   }
-  if (*w.differ || 8 * (int64_t)(most + 1) > 7 * L) return SLH_OK;
+  if (*w.differ || 8 * (int64_t)(most + 1) > 7 * w.L) return SLH_OK;
   c->phi_g = set;
   c->Lphi = most + 1;
   return SLH_OK;
@@ -860,10 +878,15 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
   int rc = check_x(c, X, dtype, ldx);
   if (rc) return rc;
   if ((rc = ensure_routing(c))) return rc;
-  if (!(c->norms_fresh && norms_match(c, X, dtype, ldx)))
-    if ((rc = prep_norms(c, X, dtype, ldx))) return rc;
+  // the norms behind the row search, so that the GPU has them to do while the host
+  // waits for the number of groups
+  int set = -1;
+  if ((rc = group_rows(c, X, dtype, ldx, set))) return rc;
+  const bool norms = !(c->norms_fresh && norms_match(c, X, dtype, ldx));
+  rc = norms ? prep_norms(c, X, dtype, ldx) : SLH_OK;
   c->norms_fresh = false;
-  if ((rc = group_rows(c, X, dtype, ldx))) return rc;
+  const int grc = group_take(c, set);          // also where the norms failed: its kernels are out
+  if (rc || grc) return rc ? rc : grc;
   const GroupWS* grp = c->phi_g >= 0 ? &c->grp[c->phi_g] : nullptr;
   const int64_t L = c->Lphi;        // rows per window
   const int64_t rows = (int64_t)c->n_act * L;

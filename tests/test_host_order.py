@@ -147,6 +147,20 @@ def test_first_call_of_a_shape_sizes_every_prompt(stub, resident, normalise):
     assert ("featmap", 16, 8192) in log and not [t for t in log if t[0] in ("malloc", "free", "group", "query")]
 
 
+def test_norms_run_while_the_host_waits_for_the_groups(stub):
+    """The row search goes out first, the row norms behind the event that the host
+    waits for: the GPU is not idle until the host has sized the feature map."""
+    c = stub.ctx(8192)
+    stub.lib.stub_groups(500)
+    c.feature_map()
+    stub.log()
+    c.feature_map()
+    assert stub.names() == ["group", "record", "rownorm", "query", "featmap"]
+    c.option("DISTINCT", 0)
+    c.feature_map()
+    assert stub.names() == ["rownorm", "featmap"]      # asynchronous
+
+
 def _all_in_turn(log):
     """Every resident launch of the log is ordered behind all earlier ones: by its
     stream, or by an event recorded behind them that its stream waits for."""
