@@ -172,6 +172,8 @@ struct slh_ctx {
   int* grp_pin = nullptr;           // pinned: group counts, then the differ word
   int grp_pin_n = 0;
   int phi_g = -1, q_g = -1, row_g = -1;   // set behind Phi, behind Q and Z, behind rowsum (-1: every row)
+  int64_t grp_made[2] = {0, 0};     // searches made into each set
+  int64_t row_made = 0, Lrow = 0;   // that count and the rows per window when rowsum was formed
   int64_t Lphi = 0, Lq = 0;         // rows per window of Phi, of Q and Z
   const double* lz_q1 = nullptr;    // start vectors of the last Lanczos run
   DevBuf dg_rowsq, dg_energy;
@@ -466,6 +468,7 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, int& set) 
   const size_t n = (size_t)na * L;
   ENSURE(c, buf, n * 48 + (size_t)na * 4);
   if (!other.p) ENSURE(c, other, n * 48 + (size_t)na * 4);   // the next prompt's
+  ++c->grp_made[g];
   GroupWS& w = c->grp[g];
   w.n_act = na;
   w.L = (int)L;
@@ -920,6 +923,8 @@ int slh_feature_map(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx) {
     ENSURE(c, c->rowsum, (size_t)most * 8);
     if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[9], c->stream));
     c->row_g = c->phi_g;
+    c->row_made = c->row_g >= 0 ? c->grp_made[c->row_g] : 0;
+    c->Lrow = L;
     HIP_TRY(c, launch_normalise(P<float>(c->Phi), grp ? grp->wt : nullptr, window_len(c), c->n_act, (int)L, (int)c->m, G,
                                 P<double>(c->nm_part), P<double>(c->nm_csum),
                                 P<double>(c->rowsum), c->stream));
@@ -1591,8 +1596,10 @@ int slh_copy_out(slh_ctx* c, int32_t which, void* dst, int64_t bytes) {
     // held for the groups of equal rows: formed for every row here
     const GroupWS& w = c->grp[g];
     const bool q = which == SLH_OUT_Q || which == SLH_OUT_Z;
-    const int64_t Lg = q ? c->Lq : c->Lphi, per = want / (na * L * 4);   // words a row
-    if (w.L != L || w.n_act != na || (which == SLH_OUT_ROWSUM && c->row_g != c->phi_g) || !b->p ||
+    const int64_t Lg = q ? c->Lq : which == SLH_OUT_PHI ? c->Lphi : c->Lrow;
+    const int64_t per = want / (na * L * 4);   // words a row
+    // the groups of the row sums may since have been made anew for another prompt
+    if (w.L != L || w.n_act != na || (which == SLH_OUT_ROWSUM && c->row_made != c->grp_made[g]) || !b->p ||
         (int64_t)b->bytes < na * Lg * per * 4)
       return fail(c, SLH_ESTATE, "output %d not computed", which);
     ENSURE(c, c->xpand, (size_t)want);

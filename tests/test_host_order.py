@@ -161,6 +161,31 @@ def test_norms_run_while_the_host_waits_for_the_groups(stub):
     assert stub.names() == ["rownorm", "featmap"]      # asynchronous
 
 
+@pytest.mark.parametrize("run", [False, True])
+def test_row_sums_keep_to_their_own_groups(stub, run):
+    """Row sums of grouped rows are expanded by the groups they were formed on: after
+    another prompt's search into the same set they are refused; where that search took
+    the other set (the first stays behind Q) they are still there."""
+    c = stub.ctx(8192, NORMALIZE=1)
+    stub.lib.stub_groups(500)
+    c.feature_map()
+    out = (ctypes.c_double * 8192)()
+    sums = (B.SLH_OUT_ROWSUM, out, ctypes.c_int64(8 * 8192))
+    c.call("slh_copy_out", *sums)
+    if run:
+        c.lanczos()
+    c.option("NORMALIZE", 0)
+    stub.lib.stub_groups(400)
+    c.feature_map()
+    stub.log()
+    if run:
+        c.call("slh_copy_out", *sums)
+        assert stub.names().count("group_copy") == 1
+    else:
+        with pytest.raises(B.SLHError, match="not computed"):
+            c.call("slh_copy_out", *sums)
+
+
 def _all_in_turn(log):
     """Every resident launch of the log is ordered behind all earlier ones: by its
     stream, or by an event recorded behind them that its stream waits for."""
