@@ -528,6 +528,11 @@ bool target_budgets(const slh_ctx* c, std::vector<int>& tw) {
   return true;
 }
 
+// the groups of set g (-1: every row) are those of the present windows and routing
+bool groups_current(const slh_ctx* c, int g) {
+  return g < 0 || (c->grp[g].L == window_len(c) && c->grp[g].n_act == c->n_act);
+}
+
 int64_t capacity(const slh_ctx* c) {
   const int64_t L = window_len(c);
   const int64_t per_spec = std::min<int64_t>(L, (int64_t)1 << c->bits);
@@ -957,8 +962,8 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
                                        L, na, c->stream));
       q1act = P<double>(c->q1act);
     }
-    if (!c->Phi.p || (int64_t)c->Phi.bytes < na * c->Lphi * c->m * 4 ||
-        (grp ? grp->L != L || grp->n_act != na : c->Lphi != L))
+    if (!grp) c->Lphi = L;
+    if (!c->Phi.p || (int64_t)c->Phi.bytes < na * c->Lphi * c->m * 4 || !groups_current(c, c->phi_g))
       return fail(c, SLH_ESTATE, "slh_lanczos before slh_feature_map");
     c->q_g = c->phi_g;
     c->Lq = c->Lphi;
@@ -1146,7 +1151,9 @@ int slh_eigh_ritz(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out
     return fail(c, SLH_ESTATE, "slh_eigh_ritz needs slh_lanczos or slh_load of alpha, beta and Q");
   if (n_it != c->n_it)
     return fail(c, SLH_EINVAL, "n_it %d differs from the tridiagonal's order %d", n_it, c->n_it);
-  const int64_t L = c->Lq;          // rows per window of Q
+  if (!groups_current(c, c->q_g))
+    return fail(c, SLH_ESTATE, "slh_eigh_ritz: the basis is of other windows");
+  const int64_t L = c->q_g >= 0 ? c->Lq : window_len(c);   // rows per window of Q
   const int na = c->n_act;
   if (na > 0) {
     ENSURE(c, c->theta, (size_t)na * c->r * 8);
@@ -1175,6 +1182,8 @@ int slh_simhash(slh_ctx* c, uint32_t* codes_out) {
   if (c->stage < 2) return fail(c, SLH_ESTATE, "slh_simhash before slh_lanczos");
   const int64_t L = window_len(c);
   const int na = c->n_act;
+  if (na > 0 && !groups_current(c, c->q_g))
+    return fail(c, SLH_ESTATE, "slh_simhash: the Ritz coordinates are of other windows");
   ENSURE(c, c->codes, (size_t)c->Ntot * 4);
   ENSURE(c, c->proj, (size_t)std::max(na, 1) * L * c->bits * 8);
   if (c->timing) HIP_TRY(c, hipEventRecord(c->ev[5], c->stream));
@@ -1346,10 +1355,13 @@ int slh_spectral_energy(slh_ctx* c, double* out) {
   const int64_t L = window_len(c);
   const int na = c->n_act;
   if (na == 0) return SLH_OK;
+  if (!groups_current(c, c->phi_g))
+    return fail(c, SLH_ESTATE, "slh_spectral_energy: the rows of Phi are of other windows");
+  const int64_t Lp = c->phi_g >= 0 ? c->Lphi : L;
   ENSURE(c, c->dg_rowsq, (size_t)na * L * 8);
   ENSURE(c, c->dg_energy, (size_t)na * 8);
   HIP_TRY(c, launch_energy(P<float>(c->Phi), c->phi_g >= 0 ? c->grp[c->phi_g].wt : nullptr, L,
-                           P<double>(c->theta), na, (int)c->Lphi, (int)c->m, c->r,
+                           P<double>(c->theta), na, (int)Lp, (int)c->m, c->r,
                            P<double>(c->dg_rowsq), P<double>(c->dg_energy), c->stream));
   HIP_TRY(c, hipMemcpyAsync(out, c->dg_energy.p, (size_t)na * 8, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1599,7 +1611,7 @@ int slh_copy_out(slh_ctx* c, int32_t which, void* dst, int64_t bytes) {
     const int64_t Lg = q ? c->Lq : which == SLH_OUT_PHI ? c->Lphi : c->Lrow;
     const int64_t per = want / (na * L * 4);   // words a row
     // the groups of the row sums may since have been made anew for another prompt
-    if (w.L != L || w.n_act != na || (which == SLH_OUT_ROWSUM && c->row_made != c->grp_made[g]) || !b->p ||
+    if (!groups_current(c, g) || (which == SLH_OUT_ROWSUM && c->row_made != c->grp_made[g]) || !b->p ||
         (int64_t)b->bytes < na * Lg * per * 4)
       return fail(c, SLH_ESTATE, "output %d not computed", which);
     ENSURE(c, c->xpand, (size_t)want);

@@ -186,6 +186,26 @@ def test_row_sums_keep_to_their_own_groups(stub, run):
             c.call("slh_copy_out", *sums)
 
 
+def test_groups_of_other_windows_are_refused(stub):
+    """Loaded codes let a caller go on after the windows changed: what is still there
+    of grouped rows, with fewer rows per window than the windows now have, is refused
+    rather than read past its end."""
+    c = stub.ctx(8192)
+    stub.lib.stub_groups(500)
+    c.feature_map()
+    c.lanczos()
+    c.option("WINDOW_LEN", 1024)
+    codes = (ctypes.c_uint32 * 8192)()
+    c.call("slh_load", B.SLH_OUT_CODES, codes, ctypes.c_int64(4 * 8192))
+    stub.log()
+    energy = (ctypes.c_double * 8)()
+    for call in (("slh_simhash", None), ("slh_eigh_ritz", 16, None, None), ("slh_spectral_energy", energy),
+                 ("slh_lanczos", 16, None, None)):
+        with pytest.raises(B.SLHError):
+            c.call(*call)
+    assert not set(stub.names()) & {"simhash", "eigh_ritz", "energy", "lanczos", "graph_launch"}
+
+
 def _all_in_turn(log):
     """Every resident launch of the log is ordered behind all earlier ones: by its
     stream, or by an event recorded behind them that its stream waits for."""
