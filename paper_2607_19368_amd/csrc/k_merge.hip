@@ -1140,10 +1140,21 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
   for (int q = 0; q < PPT; ++q)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0f;
-  // a batch's rows are summed by themselves first: a chunk of 64 rows then rounds
-  // no more than one of 16 summed row by row
+  constexpr int DEPTH = (8 / (PPT * (DT + 1))) > 0 ? 8 / (PPT * (DT + 1)) : 1;
+  // Rows are summed by themselves first, a batch (bf16) or eight rows (fp32) at a
+  // time: a chunk of 64 rows then rounds no more than one of 16 summed row by row.
+  // Error against 64 bits at 26000 rows, buckets of about 51: fp32 D = 2048 6.4e-8
+  // (chunks of 16, row by row), 6.5e-8 (64, batches of four), 6.1e-8 (64, eights);
+  // D = 8192 6.3e-8, 7.6e-8 (batches of two), 6.1e-8; D = 12288 6.5e-8, 9.5e-8 (row
+  // by row), 6.1e-8; bf16 the same within 1e-3 for all of them, D to 20480.  fp32
+  // rows past D = 16384, where the second sum's 64 registers would spill, come in
+  // chunks of 16.
+  constexpr bool BSUM = DT == 0 ? DEPTH > 1 : PPT <= 4;
+  constexpr int FLUSH = DT == 0 ? 1 : 8 / DEPTH;      // batches between two flushes
   float bsum[PPT][8] = {};
+  float (&rsum)[PPT][8] = BSUM ? bsum : acc;
   auto flush = [&]() {
+    if constexpr (!BSUM) return;
 #pragma unroll
     for (int q = 0; q < PPT; ++q)
 #pragma unroll
@@ -1152,7 +1163,6 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
         bsum[q][k] = 0.0f;
       }
   };
-  constexpr int DEPTH = (8 / (PPT * (DT + 1))) > 0 ? 8 / (PPT * (DT + 1)) : 1;
   MgRaw<DT> rc[DEPTH][PPT], rn[DEPTH][PPT];
   auto load_batch = [&](MgRaw<DT> (&dst)[DEPTH][PPT], int b) {
 #pragma unroll
@@ -1197,7 +1207,7 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
       if (s < n) {
 #pragma unroll
         for (int q = 0; q < PPT; ++q)
-          if (cin[q]) mg_add<DT>(bsum[q], rc[e][q]);
+          if (cin[q]) mg_add<DT>(rsum[q], rc[e][q]);
         nsum += snrm[s];
         const int g = ssg[s];
         if (s == n - 1 || ssg[s + 1] != g) {
@@ -1246,7 +1256,7 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
         }
       }
     }
-    flush();
+    if (FLUSH == 1 || (b + 1) % FLUSH == 0) flush();
 #pragma unroll
     for (int e = 0; e < DEPTH; ++e)
 #pragma unroll
@@ -1431,8 +1441,11 @@ hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64
 // again, and a shorter chain to sum for the most common bucket; they take rows
 // enough to fill the chip.  Measured at 16 / 32 / 64: 32768 tokens 2465 / 2413 /
 // 2347 us a call, 49157 668 / 644 / 642, 8192 1144 / 1140 / 1153, 512 241 / 246 /
-// 256, 64 windows of 2048 365 / 366 / 381.
-int merge_chunk(int64_t L) { return L >= 24576 ? 64 : L >= 8192 ? 32 : 16; }
+// 256, 64 windows of 2048 365 / 366 / 381.  fp32 rows past D = 16384 are summed one
+// by one, 16 at most.
+int merge_chunk(int64_t L, int64_t D, int dtype) {
+  return dtype == 1 && D > 16384 ? 16 : L >= 24576 ? 64 : L >= 8192 ? 32 : 16;
+}
 
 int64_t merge_tiled_ws(int n_win, int64_t L, int bits, int* ws, MergeWS* w) {
   // From 8193 tokens a window: us a merge (D = 512), one workgroup / tiles: 4096 68 /

@@ -1216,7 +1216,7 @@ int slh_merge_async(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, float
   if (cap < need) return fail(c, SLH_EINVAL, "cap %lld < required %lld", (long long)cap, (long long)need);
   const int64_t L = window_len(c);
   const int64_t N = c->N;
-  const int CH = merge_chunk(L);
+  const int CH = merge_chunk(L, c->D, dtype == SLH_BF16 ? 0 : 1);
   const int nch = merge_nchunks(N, CH);
   ENSURE(c, c->keyA, N * 4);
   ENSURE(c, c->keyB, N * 4);

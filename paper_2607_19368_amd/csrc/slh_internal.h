@@ -208,7 +208,7 @@ int merge_nchunks(int64_t N, int CH);
 // ints of workspace for windows whose book-keeping is tiled, else 0; with w the
 // workspace ws is laid out in it
 int64_t merge_tiled_ws(int n_win, int64_t L, int bits, int* ws, MergeWS* w);
-int merge_chunk(int64_t L);              // CH for windows of L tokens
+int merge_chunk(int64_t L, int64_t D, int dtype);   // CH for windows of L tokens of width D
 // preserved suffix: tail tokens N .. N + K - 1 become macro-tokens *Mtot .. *Mtot + K - 1
 hipError_t launch_merge_tail(const void* X, int dtype, int64_t ldx, int D, int64_t N, int K,
                              const int* Mtot, int compact, float* E, int* P, int* tok2macro,

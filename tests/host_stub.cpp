@@ -205,7 +205,7 @@ hipError_t launch_purity(const void*, int, int64_t, int, const int*, const int*,
 hipError_t launch_fill_u32(uint32_t*, int64_t, uint32_t, hipStream_t s) { return launched("fill", s); }
 int merge_nchunks(int64_t N, int CH) { return (int)((N + CH - 1) / CH); }
 int64_t merge_tiled_ws(int, int64_t, int, int*, MergeWS*) { return 0; }
-int merge_chunk(int64_t) { return 16; }
+int merge_chunk(int64_t, int64_t, int) { return 16; }
 hipError_t launch_merge(const MergeWS&, const void*, int, int64_t, float*, const MergeOut&, hipStream_t s) {
   return launched("merge", s);
 }

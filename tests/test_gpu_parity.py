@@ -723,6 +723,43 @@ def test_merge_bookkeeping(N, bits, window, skew, compact):
     assert err.max() <= 2e-6
 
 
+@pytest.mark.parametrize("D,dtype", [(2056, "fp32"), (4104, "fp32"), (8200, "fp32"), (16392, "fp32"),
+                                     (4104, "bf16"), (8200, "bf16"), (16392, "bf16")])
+def test_merge_sums_of_wide_rows(D, dtype):
+    """Sums of 51 rows a bucket in a window long enough for the longest chunks, at the
+    widths where a thread's share of a row and the batches change: no less accurate
+    than chunks of 16 rows summed one by one.  The sum of k rows of mean 1 is about k,
+    so each of its roundings has a standard deviation of about 2^-24 k / sqrt(3), and a
+    bucket of n rows an error of 2^-24 / (n sqrt(3)) times the root of the sum of k^2
+    over its roundings: for n = 51 6.9e-8 with chunks of 16 (k = 2 .. 16 in each, then
+    the chunks' sums), 6.6e-8 with sums of eight rows in a chunk of 64, but 1.1e-7 with
+    sums of two and 1.4e-7 row by row."""
+    import torch
+    import paper_2607_19368_amd as P
+    from paper_2607_19368_amd import slh as B
+    N, bits = 24600, 9
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D)
+    X = torch.randn((N, D), generator=g, device="cuda") + 1.0
+    if dtype == "bf16":
+        X = X.bfloat16()
+    codes = torch.randint(0, 1 << bits, (N,), generator=g, device="cuda")
+    ctx = P.slh_create(N, D, 256, 4, bits, 0)
+    P.slh_load(ctx, B.SLH_OUT_CODES, codes.int())
+    E, _, t2m, M = P.slh_merge(ctx, X)
+    S = torch.zeros((M, D), dtype=torch.float64, device="cuda")
+    eta = torch.zeros(M, dtype=torch.float64, device="cuda")
+    at = t2m.long()
+    for i in range(0, N, 2048):
+        x = X[i:i + 2048].double()
+        S.index_add_(0, at[i:i + 2048], x)
+        eta.index_add_(0, at[i:i + 2048], x.norm(dim=1))
+    ref = S * (eta / torch.bincount(at, minlength=M) / S.norm(dim=1))[:, None]
+    err = float((E[:M].double() - ref).norm() / ref.norm())
+    _say(f"[merge wide] {dtype} D={D}: {err:.2e}")
+    assert err <= 6.9e-8
+
+
 @pytest.mark.parametrize("N,bits,window", [(9001, 12, 0), (20001, 10, 0), (3 * 8200, 9, 8200)])
 def test_merge_of_codes_past_the_tables(N, bits, window):
     """slh_load takes codes as they are given: values of 2^bits and more (here of 16
