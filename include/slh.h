@@ -443,7 +443,7 @@ int slh_peak_mfma(int32_t reps, void *sink, void *stream, double *tflops_out);
  * streams) race, and the caller must serialise them.  SLH_EHIP if the array's
  * device address cannot be obtained or a launch fails.
  */
-#define SLH_NOALLOC_BYTES 17355008
+#define SLH_NOALLOC_BYTES 17125632
 int slh_merge_noalloc(const void *X, int32_t x_dtype, int64_t ldx, int64_t N, int64_t D,
                       const uint32_t *codes, int32_t bits, float *emb_out, int32_t *pos_out,
                       int32_t *tok2macro_out, int64_t cap, int64_t *M_out, void *stream);

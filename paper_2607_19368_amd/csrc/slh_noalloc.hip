@@ -16,15 +16,13 @@ namespace {
 
 constexpr int64_t NA_NMAX = 8192;           // tokens
 constexpr int64_t NA_DMAX = 4096;           // embedding width
-constexpr int NA_CH = 16;                   // sorted positions per reduction chunk (as slh_merge)
+constexpr int NA_CH = 16;                   // sorted positions per reduction chunk, at least
 constexpr int64_t NA_NCH = (NA_NMAX + NA_CH - 1) / NA_CH;
 
 // byte offsets of the workspaces inside the array (each 256-byte aligned)
 constexpr int64_t na_al(int64_t b) { return (b + 255) & ~(int64_t)255; }
 constexpr int64_t NA_INTS = 0;                                   // 10 int arrays of NMAX
-constexpr int64_t NA_NRM = NA_INTS + na_al(10 * NA_NMAX * 4);    // not used (row norms: formed with the sums)
-constexpr int64_t NA_RSC = NA_NRM + na_al(3 * NA_NMAX * 8);      // not used
-constexpr int64_t NA_SMALL = NA_RSC + na_al(NA_NMAX * 4);        // mw, wbase[2], Mtot, route
+constexpr int64_t NA_SMALL = NA_INTS + na_al(10 * NA_NMAX * 4);  // mw, wbase[2], Mtot, route
 constexpr int64_t NA_PSEG = NA_SMALL + 256;                      // part_seg, part_cnt, part_end
 constexpr int64_t NA_PNS = NA_PSEG + na_al(3 * 2 * NA_NCH * 4);  // part_nsum (double)
 constexpr int64_t NA_PART = NA_PNS + na_al(2 * NA_NCH * 8);      // part (float, 2 NCH x DMAX)
@@ -106,7 +104,7 @@ extern "C" int slh_merge_noalloc(const void* X, int32_t dtype, int64_t ldx, int6
   w.part_cnt = pseg + 2 * NA_NCH;
   w.part_end = pseg + 4 * NA_NCH;
   w.part_nsum = (double*)(b + NA_PNS);
-  w.CH = NA_CH;
+  w.CH = std::max(NA_CH, merge_chunk(N, D, dtype == SLH_BF16 ? 0 : 1));   // as slh_merge
   w.scheme = 0;
   w.posv = nullptr;
   w.pre = nullptr;

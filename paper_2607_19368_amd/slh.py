@@ -22,7 +22,7 @@ SLH_OPT_TARGET_LEN, SLH_OPT_RESIDENT, SLH_OPT_WAIT_POLLS, SLH_OPT_DISTINCT = 10,
 SLH_OUT_PHI, SLH_OUT_ALPHA, SLH_OUT_BETA, SLH_OUT_Z = 1, 2, 3, 4
 SLH_OUT_PROJ, SLH_OUT_CODES, SLH_OUT_THETA, SLH_OUT_Q, SLH_OUT_WINDOWS = 5, 6, 7, 8, 9
 SLH_OUT_ROWSUM = 10
-SLH_NOALLOC_BYTES = 17355008
+SLH_NOALLOC_BYTES = 17125632
 
 EXPORTS = [
     "slh_gen_params", "slh_gen_start", "slh_create", "slh_destroy", "slh_last_error",
