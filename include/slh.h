@@ -123,9 +123,10 @@ typedef struct slh_ctx slh_ctx;
                                     What the library does not order, and the caller
                                     must: replays of a graph that captured such a
                                     run, beside other runs or replays, and runs of
-                                    other processes on the same GPU.  Two that meet
-                                    end with SLH_EHIP after their waits gave up; set
-                                    0 where that can happen                         */
+                                    other processes on the same GPU.  Two that meet,
+                                    or one beside a kernel that holds compute units
+                                    for about a second, end with SLH_EHIP after
+                                    their waits gave up; set 0 where that can happen */
 #define SLH_OPT_WAIT_POLLS    12 /* polls after which a wait of the resident Lanczos
                                     kernel for a value of another block gives up
                                     (the blocks then leave and the call that reads

@@ -204,7 +204,9 @@ bool capturing(const slh_ctx* c) {
 // behind the last resident launch and its stream; a launch on another stream waits
 // for it.  The event outlives contexts and streams, so neither a context that is
 // destroyed nor one that moves to another stream leaves a kernel unaccounted for.
-// Not under the caller's capture, where there is nothing yet to order.
+// (hipStreamPerThread names a stream of each thread, so its launches always wait.)
+// Where an event cannot be recorded or waited for, the host waits instead.  Not
+// under the caller's capture, where there is nothing yet to order.
 struct ResidentGate {
   std::mutex mu;
   hipEvent_t ev = nullptr;
@@ -220,15 +222,21 @@ hipError_t gate_resident(slh_ctx* c, F launch) {
   std::lock_guard<std::mutex> lk(g.mu);
   hipError_t e = hipSuccess;
   if (!g.ev) e = hipEventCreateWithFlags(&g.ev, hipEventDisableTiming | hipEventDisableSystemFence);
-  if (e == hipSuccess && g.recorded && g.last != c->stream) e = hipStreamWaitEvent(c->stream, g.ev, 0);
+  if (e == hipSuccess && g.recorded && (g.last != c->stream || c->stream == hipStreamPerThread)) {
+    e = hipStreamWaitEvent(c->stream, g.ev, 0);
+    if (e != hipSuccess) e = hipEventSynchronize(g.ev);
+  }
   if (e != hipSuccess) return e;
   e = launch();
   // also behind a launch that failed: what went out before it, here or on the stream
   // that this one waits for, is still to be waited for
-  const hipError_t r = hipEventRecord(g.ev, c->stream);
-  if (r != hipSuccess) (void)hipStreamSynchronize(c->stream);
+  hipError_t r = hipEventRecord(g.ev, c->stream);
   g.recorded = r == hipSuccess;
   g.last = c->stream;
+  if (r != hipSuccess) {
+    (void)hipGetLastError();
+    r = hipStreamSynchronize(c->stream);
+  }
   return e != hipSuccess ? e : r;
 }
 

@@ -20,6 +20,7 @@ long g_events = 0;
 int g_groups = -1;                    // distinct rows that launch_group reports (-1: none taken)
 int g_resident = 0;                   // blocks per window of the resident kernel (0: streaming)
 int g_fail_resident = 0;              // launches of it that fail
+int g_fail_events = 0;                // event records and waits that fail
 void* g_capturing = nullptr;          // stream under the caller's capture
 bool g_capture_on = false;
 long g_own_capture = 0;               // the library's own capture
@@ -46,6 +47,7 @@ void stub_clear() { g_log.clear(); }
 void stub_groups(int n) { g_groups = n; }
 void stub_resident(int nb) { g_resident = nb; }
 void stub_fail_resident(int n) { g_fail_resident = n; }
+void stub_fail_events(int n) { g_fail_events = n; }
 void stub_capture(void* s, int on) {
   g_capturing = s;
   g_capture_on = on != 0;
@@ -113,8 +115,12 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
 }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { return launched("record", s, id(e)); }
-hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { return launched("wait", s, id(e)); }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  return g_fail_events > 0 ? (--g_fail_events, hipErrorInvalidHandle) : launched("record", s, id(e));
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  return g_fail_events > 0 ? (--g_fail_events, hipErrorInvalidHandle) : launched("wait", s, id(e));
+}
 hipError_t hipEventQuery(hipEvent_t e) { return launched("query", nullptr, id(e)); }
 hipError_t hipEventSynchronize(hipEvent_t e) { return launched("event_sync", nullptr, id(e)); }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {

@@ -72,6 +72,7 @@ def stub(lib):
     lib.stub_groups(-1)
     lib.stub_resident(0)
     lib.stub_fail_resident(0)
+    lib.stub_fail_events(0)
     lib.stub_capture(None, 0)
     made = []
 
@@ -209,13 +210,18 @@ def test_groups_of_other_windows_are_refused(stub):
 def _all_in_turn(log):
     """Every resident launch of the log is ordered behind all earlier ones: by its
     stream, or by an event recorded behind them that its stream waits for."""
-    before, snap, made = {}, {}, 0
+    before, snap, made, host = {}, {}, 0, set()
     for name, stream, arg in log:
         done = before.setdefault(stream, set())
+        done |= host
         if name == "record":
             snap[arg] = set(done)
         elif name == "wait":
             done |= snap.get(arg, set())   # (an event of the contexts before this test)
+        elif name == "event_sync":         # the host waited: everything after it is behind
+            host |= snap.get(arg, set())
+        elif name == "stream_sync":
+            host |= done
         elif name == "resident":
             assert done == set(range(made)), (made, stream)
             done.add(made)
@@ -234,7 +240,7 @@ def test_resident_launches_take_turns(stub, seed):
     for _ in range(150):
         if not live or rng.random() < 0.15:
             live.append(stub.ctx(64, m=256))
-            live[-1].stream(rng.randint(1, 4))
+            live[-1].stream(rng.randint(11, 14))
             live[-1].feature_map(B.SLH_F32)
         c = rng.choice(live)
         what = rng.random()
@@ -242,16 +248,30 @@ def test_resident_launches_take_turns(stub, seed):
             live.remove(c)
             c.destroy()
         elif what < 0.3:
-            c.stream(rng.randint(1, 4))
+            c.stream(rng.randint(11, 14))
         elif what < 0.4:
             stub.lib.stub_fail_resident(1)
             with pytest.raises(B.SLHError):
                 c.lanczos()
         else:
+            stub.lib.stub_fail_events(1 if what > 0.95 else 0)
             c.lanczos()
+    stub.lib.stub_fail_events(0)
     log = stub.log()
     assert _all_in_turn(log) > 50
     assert not [t for t in log if t[0] == "device_sync"]
+
+
+def test_streams_of_each_thread_always_wait(stub):
+    """hipStreamPerThread is one value for a stream of each thread."""
+    stub.lib.stub_resident(64)
+    c = stub.ctx(64, m=256)
+    c.stream(2)
+    c.feature_map(B.SLH_F32)
+    c.lanczos()
+    stub.log()
+    c.lanczos()
+    assert stub.names().count("wait") == 1
 
 
 def test_captured_resident_launch_joins_the_capture_alone(stub):
@@ -259,12 +279,12 @@ def test_captured_resident_launch_joins_the_capture_alone(stub):
     event of another stream (either would tie the capture to work outside it)."""
     stub.lib.stub_resident(64)
     a, b = stub.ctx(64, m=256), stub.ctx(64, m=256)
-    for c, s in ((a, 1), (b, 2)):
+    for c, s in ((a, 11), (b, 12)):
         c.stream(s)
         c.feature_map(B.SLH_F32)
         c.lanczos()
     stub.log()
-    stub.lib.stub_capture(ctypes.c_void_p(1), 1)
+    stub.lib.stub_capture(ctypes.c_void_p(11), 1)
     a.lanczos()
     assert [t[0] for t in stub.log()] == ["resident", "eigh_ritz"]
     stub.lib.stub_capture(None, 0)
