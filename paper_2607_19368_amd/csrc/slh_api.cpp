@@ -190,20 +190,23 @@ struct slh_ctx {
 
 namespace {
 
-// the context's stream is under the caller's capture (or cannot be asked)
-bool capturing(const slh_ctx* c) {
+// the stream is under the caller's capture (or cannot be asked)
+bool capturing(hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
   (void)hipGetLastError();
   return true;
 }
 
 // Resident Lanczos kernels of different streams must not run at once: each needs
 // all of its blocks on the chip, and two that each hold part of it would wait for
-// blocks that cannot start until their bounded waits gave up.  Per device, the event
-// behind the last resident launch and its stream; a launch on another stream waits
-// for it.  The event outlives contexts and streams, so neither a context that is
-// destroyed nor one that moves to another stream leaves a kernel unaccounted for.
+// blocks that cannot start until their bounded waits gave up.  Per device, the stream
+// of the last resident launch and, once a second stream has been seen, an event behind
+// every launch, which a launch on another stream waits for.  Nothing here belongs to a
+// context, so neither one that is destroyed nor one that moves to another stream
+// leaves a kernel unaccounted for.  While every launch comes from one stream there is
+// no event (its record costs 1 to 2.5 us a call, 1% of the smallest); the second
+// stream's first launch then waits for all that the first one holds.
 // (hipStreamPerThread names a stream of each thread, so its launches always wait.)
 // Where an event cannot be recorded or waited for, the host waits instead.  Not
 // under the caller's capture, where there is nothing yet to order.
@@ -211,22 +214,39 @@ struct ResidentGate {
   std::mutex mu;
   hipEvent_t ev = nullptr;
   hipStream_t last = nullptr;
-  bool recorded = false;
+  bool any = false, several = false, recorded = false;
 };
 constexpr int GATE_DEVICES = 64;
 ResidentGate gates[GATE_DEVICES];
 template <class F>
 hipError_t gate_resident(slh_ctx* c, F launch) {
-  if (c->device < 0 || c->device >= GATE_DEVICES || capturing(c)) return launch();
+  if (c->device < 0 || c->device >= GATE_DEVICES || capturing(c->stream)) return launch();
   ResidentGate& g = gates[c->device];
   std::lock_guard<std::mutex> lk(g.mu);
+  const bool same = g.any && g.last == c->stream && c->stream != hipStreamPerThread;
+  if (!g.several && (!g.any || same)) {
+    g.any = true;
+    g.last = c->stream;
+    return launch();
+  }
   hipError_t e = hipSuccess;
   if (!g.ev) e = hipEventCreateWithFlags(&g.ev, hipEventDisableTiming | hipEventDisableSystemFence);
-  if (e == hipSuccess && g.recorded && (g.last != c->stream || c->stream == hipStreamPerThread)) {
+  if (e != hipSuccess) return e;
+  if (!g.several) {
+    // (a stream that was destroyed, is being captured or is another thread's: the device)
+    g.recorded = g.last != hipStreamPerThread && !capturing(g.last) &&
+                 hipEventRecord(g.ev, g.last) == hipSuccess;
+    if (!g.recorded) {
+      (void)hipGetLastError();
+      if ((e = hipDeviceSynchronize()) != hipSuccess) return e;
+    }
+    g.several = true;
+  }
+  if (g.recorded && !same) {
     e = hipStreamWaitEvent(c->stream, g.ev, 0);
     if (e != hipSuccess) e = hipEventSynchronize(g.ev);
+    if (e != hipSuccess) return e;
   }
-  if (e != hipSuccess) return e;
   e = launch();
   // also behind a launch that failed: what went out before it, here or on the stream
   // that this one waits for, is still to be waited for
@@ -456,7 +476,7 @@ int group_rows(slh_ctx* c, const void* X, int32_t dtype, int64_t ldx, int& set) 
   if (!c->distinct || dtype != SLH_BF16 || na < 1 || L <= 32 || L > GROUP_L_MAX ||
       na * L * c->m < group_min_phi(c->m) || c->N > 0x7FFFFFFF)
     return SLH_OK;
-  if (capturing(c)) return SLH_OK;
+  if (capturing(c->stream)) return SLH_OK;
   int rc = ensure_q1(c);
   if (rc) return rc;
   if (c->grp_pin_n < na + 1) {
@@ -1082,7 +1102,7 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
                                     P<double>(c->Seig), w.Q, w.L, w.ldq, P<double>(c->Z),
                                     c->n_cu, c->stream));
         HIP_TRY(c, hipEventRecord(c->ev[4], c->stream));
-      } else if (res || grp || capturing(c)) {
+      } else if (res || grp || capturing(c->stream)) {
         // the resident path is four kernels, launched directly: the end of a
         // graph costs a gap before the stream's next kernel.  Grouped rows: their
         // number is the prompt's own, so a graph would be captured for every one.

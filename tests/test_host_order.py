@@ -17,7 +17,7 @@ X = ctypes.c_void_p(1 << 20)          # never read by the stand-in
 
 
 @pytest.fixture(scope="module")
-def lib(tmp_path_factory):
+def built(tmp_path_factory):
     assert shutil.which("g++")
     out = str(tmp_path_factory.mktemp("host") / "libhost.so")
     cmd = ["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-w",
@@ -25,7 +25,13 @@ def lib(tmp_path_factory):
            os.path.join(CSRC, "slh_api.cpp"), os.path.join(ROOT, "tests", "host_stub.cpp"), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    L = ctypes.CDLL(out)
+    return out
+
+
+@pytest.fixture
+def lib(built, tmp_path):
+    """A copy of its own for each test: the library's state per device starts afresh."""
+    L = ctypes.CDLL(shutil.copy(built, tmp_path))
     L.stub_log.restype = ctypes.c_char_p
     L.slh_last_error.restype = ctypes.c_char_p
     L.slh_last_error.argtypes = [ctypes.c_void_p]
@@ -81,11 +87,11 @@ def stub(lib):
             made.append(Ctx(lib, *a, **k))
             return made[-1]
 
-        def log(self):
+        def log(self, memory=False):
             out = [tuple(int(x) if i else x for i, x in enumerate(t.split()))
                    for t in lib.stub_log().decode().splitlines()]
             lib.stub_clear()
-            return out
+            return [t for t in out if memory or t[0] not in ("malloc", "free")]
 
         def names(self):
             return [t[0] for t in self.log()]
@@ -136,7 +142,7 @@ def test_first_call_of_a_shape_sizes_every_prompt(stub, resident, normalise):
         c.feature_map()
         c.lanczos()
         c.call("slh_simhash", None)
-        return stub.log()
+        return stub.log(memory=True)
 
     assert any(t[0] == "malloc" for t in prompt(500))
     for groups, rows in ((600, 601), (1500, 1501), (7000, 7001), (-1, 8192), (501, 502)):
@@ -217,11 +223,13 @@ def _all_in_turn(log):
         if name == "record":
             snap[arg] = set(done)
         elif name == "wait":
-            done |= snap.get(arg, set())   # (an event of the contexts before this test)
+            done |= snap[arg]
         elif name == "event_sync":         # the host waited: everything after it is behind
-            host |= snap.get(arg, set())
+            host |= snap[arg]
         elif name == "stream_sync":
             host |= done
+        elif name == "device_sync":
+            host |= set(range(made))
         elif name == "resident":
             assert done == set(range(made)), (made, stream)
             done.add(made)
@@ -232,8 +240,7 @@ def _all_in_turn(log):
 @pytest.mark.parametrize("seed", range(6))
 def test_resident_launches_take_turns(stub, seed):
     """Contexts that are made, destroyed and moved between streams, some of whose
-    launches fail: no resident kernel can meet another, and no call waits for the
-    device."""
+    launches fail: no resident kernel can meet another."""
     rng = random.Random(seed)
     stub.lib.stub_resident(64)
     live = []
@@ -257,9 +264,54 @@ def test_resident_launches_take_turns(stub, seed):
             stub.lib.stub_fail_events(1 if what > 0.95 else 0)
             c.lanczos()
     stub.lib.stub_fail_events(0)
+    assert _all_in_turn(stub.log()) > 50
+
+
+def test_one_stream_needs_no_event(stub):
+    """While every resident launch comes from one stream nothing is recorded; the first
+    launch on a second one goes behind all that the first holds, then each has its
+    event."""
+    stub.lib.stub_resident(64)
+    a, b = stub.ctx(64, m=256), stub.ctx(64, m=256)
+    for c in (a, b):
+        c.stream(11)
+        c.feature_map(B.SLH_F32)
+    stub.log()
+    for c in (a, b, a):
+        c.lanczos()
+    assert stub.names() == ["resident", "eigh_ritz"] * 3
+    b.stream(12)
+    for c in (b, b, a):
+        c.lanczos()
     log = stub.log()
-    assert _all_in_turn(log) > 50
-    assert not [t for t in log if t[0] == "device_sync"]
+    ev = log[0][2]
+    assert log[:4] == [("record", 11, ev), ("wait", 12, ev), ("resident", 12, 0), ("record", 12, ev)]
+    assert [t[:2] for t in log[5:7]] == [("resident", 12), ("record", 12)]
+    assert log[8:] == [("wait", 11, ev), ("resident", 11, 0), ("record", 11, ev), ("eigh_ritz", 11, 0)]
+
+
+@pytest.mark.parametrize("why", ["destroyed", "captured"])
+def test_a_first_stream_that_cannot_be_asked(stub, why):
+    """Where no event can go behind the first stream's launches, the host waits once."""
+    stub.lib.stub_resident(64)
+    a, b = stub.ctx(64, m=256), stub.ctx(64, m=256)
+    for c, s in ((a, 11), (b, 12)):
+        c.stream(s)
+        c.feature_map(B.SLH_F32)
+    stub.lib.stub_resident(0)
+    b.lanczos()                        # its workspaces (none can be made during a capture)
+    stub.lib.stub_resident(64)
+    a.lanczos()
+    stub.log()
+    if why == "destroyed":
+        stub.lib.stub_fail_events(1)
+    else:
+        stub.lib.stub_capture(ctypes.c_void_p(11), 1)
+    b.lanczos()
+    stub.lib.stub_capture(None, 0)
+    assert [t[0] for t in stub.log()] == ["device_sync", "resident", "record", "eigh_ritz"]
+    a.lanczos()
+    assert stub.names() == ["wait", "resident", "record", "eigh_ritz"]
 
 
 def test_streams_of_each_thread_always_wait(stub):
@@ -271,7 +323,9 @@ def test_streams_of_each_thread_always_wait(stub):
     c.lanczos()
     stub.log()
     c.lanczos()
-    assert stub.names().count("wait") == 1
+    assert stub.names() == ["device_sync", "resident", "record", "eigh_ritz"]
+    c.lanczos()
+    assert stub.names() == ["wait", "resident", "record", "eigh_ritz"]
 
 
 def test_captured_resident_launch_joins_the_capture_alone(stub):
@@ -286,8 +340,8 @@ def test_captured_resident_launch_joins_the_capture_alone(stub):
     stub.log()
     stub.lib.stub_capture(ctypes.c_void_p(11), 1)
     a.lanczos()
-    assert [t[0] for t in stub.log()] == ["resident", "eigh_ritz"]
+    assert stub.names() == ["resident", "eigh_ritz"]
     stub.lib.stub_capture(None, 0)
     b.lanczos()
     a.lanczos()
-    assert [t[0] for t in stub.log()].count("wait") == 1
+    assert stub.names().count("wait") == 1
