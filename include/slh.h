@@ -112,12 +112,17 @@ typedef struct slh_ctx slh_ctx;
                                     explicit L x L operator Phi_w Phi_w^T (the same
                                     operator and recurrence; section 3.5 local
                                     backend); 0: the general path for every L          */
-#define SLH_OPT_RESIDENT      11 /* 1 (default): windows whose Phi fit in the register
-                                    files together (n_it <= 256) run the whole Lanczos loop of Algorithm 2 as one
-                                    persistent kernel that holds its rows of Phi in
-                                    registers (the same recurrence; partial sums in
-                                    a different grouping); 0: one pass over Phi per
-                                    step for every shape.  Its blocks must all be on
+#define SLH_OPT_RESIDENT      11 /* 1 (default): the whole Lanczos loop of Algorithm 2
+                                    as one persistent kernel that holds its rows of
+                                    Phi in registers (the same recurrence; partial
+                                    sums in a different grouping), for n_it <= 256
+                                    and windows of at most 16384 rows (m > 1024:
+                                    8192, or 10240 while Q leaves LDS for eight more
+                                    rows a block), distinct rows where
+                                    SLH_OPT_DISTINCT took these; windows that do not
+                                    fit on the chip together in several launches,
+                                    where that beats a pass over Phi per step.
+                                    0: one pass over Phi per step for every shape.  Its blocks must all be on
                                     the chip at once, so the runs of one process on
                                     one device take turns, whatever their streams.
                                     What the library does not order, and the caller

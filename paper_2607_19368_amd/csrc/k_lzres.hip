@@ -1,6 +1,7 @@
 // Implicit Lanczos with full re-orthogonalization (Algorithm 2; operator of
-// Eq. 4, A v = Phi (Phi^T v)) for windows whose Phi fit in the register files of
-// the device together, as one persistent kernel for the whole run.
+// Eq. 4, A v = Phi (Phi^T v)) for windows of at most 256 blocks of at most 64 rows
+// (res_shapes: 16384 rows, 10240 for m > 1024), held in the register files of the
+// device, as one persistent kernel for the whole run.
 //
 // Block b of a window's nb holds rows [RB b, RB b + RB) of Phi in registers for
 // the whole run, loaded once, and its rows of the basis Q in LDS.  Each step is
