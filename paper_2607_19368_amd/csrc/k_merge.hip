@@ -1104,8 +1104,10 @@ __device__ __forceinline__ float mg_block_sum(float v, float* red) {
 // NRM: the rows' norms are taken here from the values loaded for the sums (fp64,
 // two barriers a batch) rather than read from w.nrm_x; the merge alone then reads
 // X once instead of twice.
+// Up to D = 8192 at most 128 registers, so that four waves share a SIMD (two fp32
+// values spill; with 132 and three waves 26000 rows of 4104 took 206 us, so 168).
 template <int DT, int PPT, bool NRM>
-__global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
+__global__ __launch_bounds__(512, PPT <= 2 ? 4 : 2) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
                                                    int64_t ldx, float* __restrict__ E) {
   const int c = blockIdx.x, tid = threadIdx.x;
   const int D = w.D;
@@ -1141,16 +1143,17 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0f;
   constexpr int DEPTH = (8 / (PPT * (DT + 1))) > 0 ? 8 / (PPT * (DT + 1)) : 1;
-  // Rows are summed by themselves first, a batch (bf16) or eight rows (fp32) at a
-  // time: a chunk of 64 rows then rounds no more than one of 16 summed row by row.
-  // Error against 64 bits at 26000 rows, buckets of about 51: fp32 D = 2048 6.4e-8
-  // (chunks of 16, row by row), 6.5e-8 (64, batches of four), 6.1e-8 (64, eights);
-  // D = 8192 6.3e-8, 7.6e-8 (batches of two), 6.1e-8; D = 12288 6.5e-8, 9.5e-8 (row
-  // by row), 6.1e-8; bf16 the same within 1e-3 for all of them, D to 20480.  fp32
-  // rows past D = 16384, where the second sum's 64 registers would spill, come in
-  // chunks of 16.
+  // Rows are summed by themselves first, a batch at a time (eight rows where fp32
+  // batches are of two or one and chunks of more than 16): a chunk of 64 rows then
+  // rounds no more than one of 16 summed row by row.  Error against 64 bits at 26000
+  // fp32 rows, buckets of about 51: D = 8192 6.3e-8 (chunks of 16, row by row), 7.6e-8
+  // (64, batches of two), 6.1e-8 (64, eights); D = 12288 6.5e-8, 9.5e-8 (row by row),
+  // 6.1e-8; D = 4096 6.4e-8, 6.5e-8 (batches of four; less at most other sizes).  bf16
+  // the same within 1e-3 for all of them, D to 20480.  fp32 rows past D = 16384, where
+  // the second sum's 64 registers would spill, come in chunks of 16.
   constexpr bool BSUM = DT == 0 ? DEPTH > 1 : PPT <= 4;
-  constexpr int FLUSH = DT == 0 ? 1 : 8 / DEPTH;      // batches between two flushes
+  constexpr int FLUSH = DT == 0 || DEPTH >= 4 ? 1 : 8 / DEPTH;   // batches between two flushes
+  const int flast = w.CH > 16 ? FLUSH - 1 : 0;
   float bsum[PPT][8] = {};
   float (&rsum)[PPT][8] = BSUM ? bsum : acc;
   auto flush = [&]() {
@@ -1256,7 +1259,7 @@ __global__ __launch_bounds__(512) void k_mg_reduce(MergeWS w, const void* __rest
         }
       }
     }
-    if (FLUSH == 1 || (b + 1) % FLUSH == 0) flush();
+    if (FLUSH == 1 || (b & flast) == flast) flush();
 #pragma unroll
     for (int e = 0; e < DEPTH; ++e)
 #pragma unroll
