@@ -1043,23 +1043,23 @@ int slh_lanczos(slh_ctx* c, int32_t n_it, double* ritz_out, int32_t* iters_out) 
       // the resident kernel where every window's Phi fits in the register files
       const int res_nb = c->resident ? lanczos_resident_blocks(w, c->n_cu) : 0;
       const bool res = res_nb > 0;
-      // row groups of the partials, at most for any number of rows up to L: a row
-      // group of the streaming path per chunk while these fit two per CU, else one per
-      // CU in all
+      // row groups of the partials, of all windows, at most for any number of rows up
+      // to L: the streaming path's (a window's one per chunk while these fit two per
+      // CU, else one per CU in all), or the blocks of a resident launch (two per CU)
       LanczosWS full = w;
       full.L = (int)L;
       const size_t chunks = (size_t)(L + 15) / 16, ncu = std::max(1, c->n_cu);
       const size_t g3 = std::min(chunks, std::max(2 * ncu / na, (ncu + na - 1) / na));
-      const size_t ng = std::max<size_t>({g3, (size_t)w.G3, (size_t)res_nb,
-                                          c->resident ? (size_t)lanczos_resident_most_blocks(full) : 0});
+      const size_t rb = c->resident ? std::max(res_nb, lanczos_resident_most_blocks(full)) : 0;
+      const size_t ng = std::max(na * std::max<size_t>(g3, w.G3), std::min(na * rb, 2 * ncu));
       const size_t hs = (size_t)w.ldq + 1;
       ENSURE(c, c->Q, (size_t)na * w.ldq * L * 8);
       ENSURE(c, c->T, (size_t)na * w.ldq * c->m * 8);
       ENSURE(c, c->Apart, (size_t)na * (c->m / 16) * 8);   // |t|^2 partials
       ENSURE(c, c->Z1, (size_t)na * L * 8);
-      ENSURE(c, c->Spart, na * ng * c->m * 8);
+      ENSURE(c, c->Spart, ng * c->m * 8);
       ENSURE(c, c->Zs, (size_t)na * 2 * L * 8);
-      ENSURE(c, c->H2part, na * ng * hs * 8);
+      ENSURE(c, c->H2part, ng * hs * 8);
       ENSURE(c, c->H2, (size_t)na * hs * 8);
       ENSURE(c, c->alpha, (size_t)na * n_it * 8);
       ENSURE(c, c->beta, (size_t)na * n_it * 8);

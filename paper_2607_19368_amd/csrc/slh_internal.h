@@ -115,8 +115,8 @@ hipError_t launch_lanczos_start(const LanczosWS& w, const double* q1_act, hipStr
 // files together, the whole run as one persistent kernel (rows of Phi held in registers;
 // the blocks exchange step-tagged values instead of meeting at barriers) ----
 // blocks per window when the shape qualifies (every window's rows fit, n_it <=
-// 256) and every block of the kernel can be resident at once, else 0; Spart and
-// H2part hold that many row groups per window
+// 256) and every block of a launch can be resident at once, else 0; Spart and
+// H2part hold the row groups of a launch (at most two blocks per compute unit)
 int lanczos_resident_blocks(const LanczosWS& w, int n_cu);
 // the most blocks per window that it can return for windows of at most w.L rows
 int lanczos_resident_most_blocks(const LanczosWS& w);
