@@ -1106,7 +1106,7 @@ __device__ __forceinline__ float mg_block_sum(float v, float* red) {
 // X once instead of twice.
 // Up to D = 8192 at most 128 registers, so that four waves share a SIMD (two fp32
 // values spill; with 132 and three waves 26000 rows of 4104 took 206 us, so 168).
-template <int DT, int PPT, bool NRM>
+template <int DT, int PPT, bool NRM, bool EIGHT>
 __global__ __launch_bounds__(512, PPT <= 2 ? 4 : 2) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
                                                    int64_t ldx, float* __restrict__ E) {
   const int c = blockIdx.x, tid = threadIdx.x;
@@ -1143,17 +1143,16 @@ __global__ __launch_bounds__(512, PPT <= 2 ? 4 : 2) void k_mg_reduce(MergeWS w, 
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0f;
   constexpr int DEPTH = (8 / (PPT * (DT + 1))) > 0 ? 8 / (PPT * (DT + 1)) : 1;
-  // Rows are summed by themselves first, a batch at a time (eight rows where fp32
-  // batches are of two or one and chunks of more than 16): a chunk of 64 rows then
-  // rounds no more than one of 16 summed row by row.  Error against 64 bits at 26000
+  // Rows are summed by themselves first, a batch at a time (EIGHT: eight rows, for fp32
+  // batches of two or one in chunks of more than 16): a chunk of 64 rows then rounds
+  // no more than one of 16 summed row by row.  Error against 64 bits at 26000
   // fp32 rows, buckets of about 51: D = 8192 6.3e-8 (chunks of 16, row by row), 7.6e-8
   // (64, batches of two), 6.1e-8 (64, eights); D = 12288 6.5e-8, 9.5e-8 (row by row),
   // 6.1e-8; D = 4096 6.4e-8, 6.5e-8 (batches of four; less at most other sizes).  bf16
   // the same within 1e-3 for all of them, D to 20480.  fp32 rows past D = 16384, where
   // the second sum's 64 registers would spill, come in chunks of 16.
-  constexpr bool BSUM = DT == 0 ? DEPTH > 1 : PPT <= 4;
-  constexpr int FLUSH = DT == 0 || DEPTH >= 4 ? 1 : 8 / DEPTH;   // batches between two flushes
-  const int flast = w.CH > 16 ? FLUSH - 1 : 0;
+  constexpr bool BSUM = DEPTH > 1 || EIGHT;
+  constexpr int FLUSH = EIGHT ? 8 / DEPTH : 1;        // batches between two flushes
   float bsum[PPT][8] = {};
   float (&rsum)[PPT][8] = BSUM ? bsum : acc;
   auto flush = [&]() {
@@ -1259,7 +1258,7 @@ __global__ __launch_bounds__(512, PPT <= 2 ? 4 : 2) void k_mg_reduce(MergeWS w, 
         }
       }
     }
-    if (FLUSH == 1 || (b & flast) == flast) flush();
+    if (FLUSH == 1 || (b + 1) % FLUSH == 0) flush();
 #pragma unroll
     for (int e = 0; e < DEPTH; ++e)
 #pragma unroll
@@ -1379,8 +1378,10 @@ __global__ __launch_bounds__(512) void k_mg_combine(MergeWS w, float* __restrict
 template <int DT, int PPT>
 static void launch_reduce_combine(const MergeWS& w, const void* X, int64_t ldx, float* E,
                                   int nchunks, hipStream_t s) {
-  if (w.nrm_x) hipLaunchKernelGGL((k_mg_reduce<DT, PPT, false>), dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
-  else hipLaunchKernelGGL((k_mg_reduce<DT, PPT, true>), dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
+  auto k = w.nrm_x ? k_mg_reduce<DT, PPT, false, false> : k_mg_reduce<DT, PPT, true, false>;
+  if constexpr (DT == 1 && (PPT == 2 || PPT == 4))
+    if (w.CH > 16) k = w.nrm_x ? k_mg_reduce<DT, PPT, false, true> : k_mg_reduce<DT, PPT, true, true>;
+  hipLaunchKernelGGL(k, dim3(nchunks), dim3(512), 0, s, w, X, ldx, E);
   hipLaunchKernelGGL((k_mg_combine<PPT>), dim3(nchunks), dim3(512), 0, s, w, E, nchunks);
 }
 
