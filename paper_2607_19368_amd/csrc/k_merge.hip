@@ -1104,10 +1104,10 @@ __device__ __forceinline__ float mg_block_sum(float v, float* red) {
 // NRM: the rows' norms are taken here from the values loaded for the sums (fp64,
 // two barriers a batch) rather than read from w.nrm_x; the merge alone then reads
 // X once instead of twice.
-// Up to D = 8192 at most 128 registers, so that four waves share a SIMD (two fp32
+// EIGHT up to D = 8192: at most 128 registers, so that four waves share a SIMD (two
 // values spill; with 132 and three waves 26000 rows of 4104 took 206 us, so 168).
 template <int DT, int PPT, bool NRM, bool EIGHT>
-__global__ __launch_bounds__(512, PPT <= 2 ? 4 : 2) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
+__global__ __launch_bounds__(512, EIGHT && PPT == 2 ? 4 : 1) void k_mg_reduce(MergeWS w, const void* __restrict__ X,
                                                    int64_t ldx, float* __restrict__ E) {
   const int c = blockIdx.x, tid = threadIdx.x;
   const int D = w.D;
